@@ -34,6 +34,7 @@
 #include <math.h>
 
 #include "eval.hpp"
+#include "lanesum.hpp"
 #include "walk.hpp"
 
 namespace glm {
@@ -213,15 +214,6 @@ __device__ inline int nth_set_bit(uint64_t m, int c)
     return pos;
 }
 
-// Orders this wavefront's LDS accesses around a hand-over between its lanes
-// (LDS operations of one wavefront complete in program order).
-__device__ inline void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The rays of a wavefront that take part in a particle pass, packed in the
 // wavefront's LDS slice: ray slot s (s < popcount(rays)) is the s-th set bit.
 struct RayTable {
@@ -324,115 +316,6 @@ __device__ inline void particles_grad(const PRec* __restrict__ rec, uint64_t sel
         for (int q = 0; q < C; ++q) sel &= sel - 1; // drop this pass's particles
     }
     wave_lds_sync(); // the slice is written again by the next user
-}
-
-// The words of one lane handed to the lane that DPP control CTRL names, within
-// its 16-lane row.
-template <int CTRL>
-__device__ inline float row_peer(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-
-// One halving step inside the rows: the M words of each lane become ceil(M / 2).
-// Partner lanes (as DPP control CTRL pairs them) keep opposite words of each
-// pair (hi: the second) and add the partner's copy; an odd last word is summed
-// over both partners, who then hold the same total.
-template <int M, int CTRL>
-__device__ inline void row_halve(float* v, bool hi)
-{
-    constexpr int NP = M / 2;
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        const float keep = hi ? v[2 * p + 1] : v[2 * p];
-        const float send = hi ? v[2 * p] : v[2 * p + 1];
-        v[p] = keep + row_peer<CTRL>(send);
-    }
-    if constexpr ((M & 1) != 0) v[NP] = v[M - 1] + row_peer<CTRL>(v[M - 1]);
-}
-
-// The halving steps inside a row pair lane j with j ^ 8 (row_ror:8), with
-// 7 - j inside its 8-lane half (row_half_mirror), then with j ^ 2 and j ^ 1
-// (quad_perm); lane bit 3, 2, 1, 0 in turn picks the word kept.
-constexpr int kRowStep[4] = {0x128, 0x141, 0x04E, 0x0B1};
-
-// Totals over the wavefront of NA per-lane words (NA even), by recursive
-// halving across the lanes, in registers.  The 32-lane halves swap the half of
-// the words that the other one keeps (v_permlane32_swap: lane i < 32 exchanges
-// its second operand with the first operand of lane i + 32) and add, so that
-// half h holds words h H .. h H + H - 1 (H = NA / 2), each summed over two
-// lanes; the two 16-lane rows of each half do the same with v_permlane16_swap,
-// so that row R = 2 h + r holds words h H + r Q .. h H + r Q + Q - 1
-// (Q = ceil(H / 2), a zero word filling an odd H) summed over four lanes; four
-// halving steps inside the rows complete the sums over each row's 16 lanes.
-// A lane's total is that of the word word_slot names.  Every lane of the
-// wavefront takes part.
-template <int NA>
-__device__ inline float word_totals(const float* a)
-{
-    static_assert(NA % 2 == 0 && NA <= 64, "an even number of words");
-    constexpr int H = NA / 2;
-    constexpr int Q = (H + 1) / 2;
-    constexpr int M2 = (Q + 1) / 2, M3 = (M2 + 1) / 2, M4 = (M3 + 1) / 2;
-    static_assert((M4 + 1) / 2 == 1, "one word per lane after four steps");
-    float b[H];
-#pragma unroll
-    for (int k = 0; k < H; ++k) {
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[k]), __float_as_uint(a[H + k]), false,
-                                                        false);
-        b[k] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    float c[Q];
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
-        const float hi = k + Q < H ? b[k + Q] : 0.0f;
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[k]), __float_as_uint(hi), false, false);
-        c[k] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    const int j = (int)__lane_id() & 15;
-    row_halve<Q, kRowStep[0]>(c, (j >> 3) & 1);
-    row_halve<M2, kRowStep[1]>(c, (j >> 2) & 1);
-    row_halve<M3, kRowStep[2]>(c, (j >> 1) & 1);
-    row_halve<M4, kRowStep[3]>(c, j & 1);
-    return c[0];
-}
-
-// The word whose total word_totals leaves in this lane: the same halving
-// steps applied to word indices.  -1 where the lane holds no word, or a copy of
-// a total that another lane holds too (only one lane adds it).
-template <int NA>
-__device__ inline int word_slot(int lane)
-{
-    constexpr int H = NA / 2;
-    constexpr int Q = (H + 1) / 2;
-    const int j = lane & 15, R = lane >> 4;
-    int wd[Q];
-    bool own[Q];
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
-        wd[k] = k;
-        own[k] = true;
-    }
-    int m = Q;
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-        const bool hi = ((j >> (3 - st)) & 1) != 0;
-        const int np = m / 2;
-#pragma unroll
-        for (int p = 0; p < Q / 2; ++p) {
-            if (p < np) {
-                wd[p] = hi ? wd[2 * p + 1] : wd[2 * p];
-                own[p] = hi ? own[2 * p + 1] : own[2 * p];
-            }
-        }
-        if (m & 1) {
-            wd[np] = wd[m - 1];
-            own[np] = own[m - 1] && !hi;
-        }
-        m = np + (m & 1);
-    }
-    const int i = (R & 1) * Q + wd[0];
-    return own[0] && i < H ? (R >> 1) * H + i : -1;
 }
 
 // Cotangent arrays of the rays (input order); any may be NULL (zero).

@@ -1208,6 +1208,7 @@ glm_status build_tree_device(TreeStorage& ts, const double* x, const double* y, 
     ts.dev.order = p;
     ts.dev.kind = kind;
     ts.dev.invC = (float)norm; // per-unit-mass normalisation: 1/C, or 1/g(c) for halos
+    ts.dev.theta = (float)prm.theta;
     ts.dev.q = q;
     ts.dev.psiK = kind == kKindNfw ? nfw_H(q * q, (q - 1.0) * (q + 1.0)) : ein_host(0.5 * q * q);
     ts.dev.einTerms = ein_terms(0.5 * q * q);

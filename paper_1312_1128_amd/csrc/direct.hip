@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kBlock) void k_direct32(const double* __restrict__ 
     a1[r] = (float)alpha1(A);
     a2[r] = (float)alpha2(A);
     if (!AONLY) {
-        ka[r] = A.k;
+        ka[r] = (float)A.k;
         g1[r] = (float)A.g1;
         g2[r] = (float)A.g2;
     }

@@ -14,13 +14,14 @@ namespace glm {
 // on this chip, and is cheaper than compensated FP32 summation).  The
 // point-mass terms of big-list particles that a ray lies inside (added once
 // with each sign, see leaf_particle) thus cancel there without leaving FP32
-// rounding of size m / r behind.  kappa, a sum of positive terms, stays FP32.
+// rounding of size m / r behind.  kappa is summed in FP64 too, so that a
+// ray's result does not depend on how its terms were grouped into partial sums.
 // The debug mode without FP64 alpha sums the alpha terms in plain FP32 (p1,
 // p2) and keeps only the balanced point terms in a1, a2.
 struct Acc {
     double a1, a2;
-    float p1, p2, k;
-    double g1, g2;
+    float p1, p2;
+    double k, g1, g2;
     double ps; // lensing potential (FP64 sum of FP32 terms), when asked for
 };
 
@@ -379,7 +380,7 @@ __device__ inline void leaf_particle(const PRec& pr, double X, double Y, Acc& A,
         profile_terms<KIND>(pr, r2, r2f, ir2, &Ag, &Gg, &Kg);
         coef = gauss ? Ag : pm;
         Gam = gauss ? Gg : pm;
-        if (!AONLY) A.k += gauss ? Kg : 0.0f;
+        if (!AONLY) A.k += (double)(gauss ? Kg : 0.0f);
     }
     if constexpr (F64A) {
         // alpha = coef d with the FP64 offset; a balanced point term (coef = pm)
@@ -438,7 +439,7 @@ __device__ inline void list_particle(const PRec& pr, double X, double Y, Acc& A,
     }
     hits++;
     if (!AONLY) {
-        A.k += Kg;
+        A.k += (double)Kg;
         A.g1 -= (double)P[2];
         A.g2 -= (double)P[3];
     }
@@ -455,7 +456,7 @@ __device__ inline void list_particle(const PRec& pr, double X, double Y, Acc& A,
 template <int P, bool AONLY, bool F64A, bool PSI = false>
 __device__ inline void eval_box(const float* __restrict__ mo, double w1, double w2, Acc& A)
 {
-    const float M = mo[0], rcm = mo[1];
+    const float M = uniform_ld(mo, 0), rcm = uniform_ld(mo, 1);
     const float f1 = (float)w1, f2 = (float)w2;
     const float inv = __builtin_amdgcn_rcpf(fmaf(f1, f1, f2 * f2));
     const float v1 = f1 * inv, v2 = -f2 * inv;
@@ -464,14 +465,14 @@ __device__ inline void eval_box(const float* __restrict__ mo, double w1, double 
     // each complex multiply-add as two FMAs per component
     float b1 = M, b2 = 0.0f, c1 = 0.0f, c2 = 0.0f;
     if constexpr (P >= 2) {
-        b1 = mo[2 + 2 * (P - 2)];
-        b2 = mo[3 + 2 * (P - 2)];
+        b1 = uniform_ld(mo, 2 + 2 * (P - 2));
+        b2 = uniform_ld(mo, 3 + 2 * (P - 2));
         c1 = b1; // first step: c = 0 * t + b
         c2 = b2;
 #pragma unroll
         for (int k = P - 1; k >= 0; --k) {
-            const float q1 = k >= 2 ? mo[2 + 2 * (k - 2)] : (k == 0 ? M : 0.0f);
-            const float q2 = k >= 2 ? mo[3 + 2 * (k - 2)] : 0.0f;
+            const float q1 = k >= 2 ? uniform_ld(mo, 2 + 2 * (k - 2)) : (k == 0 ? M : 0.0f);
+            const float q2 = k >= 2 ? uniform_ld(mo, 3 + 2 * (k - 2)) : 0.0f;
             const float n1 = fmaf(b1, t1, fmaf(-b2, t2, q1));
             const float n2 = fmaf(b1, t2, fmaf(b2, t1, q2));
             b1 = n1;
@@ -504,8 +505,8 @@ __device__ inline void eval_box(const float* __restrict__ mo, double w1, double 
             float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
             for (int k = P; k >= 2; --k) {
-                const float q1 = mo[2 + 2 * (k - 2)] * (1.0f / (float)k);
-                const float q2 = mo[3 + 2 * (k - 2)] * (1.0f / (float)k);
+                const float q1 = uniform_ld(mo, 2 + 2 * (k - 2)) * (1.0f / (float)k);
+                const float q2 = uniform_ld(mo, 3 + 2 * (k - 2)) * (1.0f / (float)k);
                 const float n1 = fmaf(s1, t1, fmaf(-s2, t2, q1)), n2 = fmaf(s1, t2, fmaf(s2, t1, q2));
                 s1 = n1;
                 s2 = n2;
@@ -619,6 +620,16 @@ __device__ inline bool walk_task(int b, int w, int64_t groups, int K, int* k, in
     const int64_t slot = wj % gx;
     *group = ((slot / c) * kXcds + b % kXcds) * c + slot % c;
     return *k < K && *group < groups;
+}
+
+// One workgroup per group: the grid, and the group of workgroup b (false for
+// the workgroups of the padded grid that have none).
+inline int64_t group_grid(int64_t groups) { return kXcds * walk_slots(groups); }
+__device__ inline bool group_task(int b, int64_t groups, int64_t* group)
+{
+    const int64_t c = walk_chunk(groups), slot = b / kXcds;
+    *group = ((slot / c) * kXcds + b % kXcds) * c + slot % c;
+    return *group < groups;
 }
 
 __device__ inline double wave_min(double v)

@@ -1,0 +1,194 @@
+// Local expansion of far boxes over one 64-ray group.
+//
+// A box that every ray of the group accepts, with centre of mass at distance d
+// from the group's centre, has no singularity of its series nearer than
+// d (its sources: d - r_cm), so over the group (radius a) its field is a power
+// series in z = delta / a (delta: a ray's offset from the group's centre),
+//   alpha1 - i alpha2 = F(w0 + delta) = sum_j L_j z^j,
+//   L_j = v e^j sum_k C(k + j, j) u_k,  v = 1 / w0, e = -a v, u_k = (Q_k / r_cm^k) t^k, t = r_cm v,
+// the exact re-expansion of the box's own multipole series (order P), cut at
+// order kFarOrder where (a / (d - r_cm))^j has fallen below FP32 rounding: with
+// a / (d - r_cm) <= kFarRatio = 0.3 and order 15 the first term left out is
+// 4e-9 of the field and 7e-8 of its derivative at the group's edge.  Every
+// ray's decisions are unchanged; only the evaluation of accepted boxes is.
+//
+// Per ray a box costs about 95 instructions of a wavefront; here the lanes are
+// boxes, 64 at a time cost about 600, so a box costs about 10.
+#pragma once
+
+#include "eval.hpp"
+#include "lanesum.hpp"
+
+namespace glm {
+
+constexpr int kFarOrder = 15;
+constexpr int kFarWords = 2 * (kFarOrder + 1);
+constexpr float kFarRatio = 0.3f;
+
+// One group of 64 rays: its bounding box, the lanes that carry a ray, its
+// centre and radius, and whether far boxes are expanded.
+struct RayGroup {
+    double gx0, gx1, gy0, gy1;
+    uint64_t full;
+    double ox, oy; // centre
+    float a, inva; // radius and its reciprocal
+    bool far;
+};
+
+__device__ inline RayGroup ray_group(double X, double Y, bool valid, bool far)
+{
+    RayGroup g{};
+    g.gx0 = wave_min(valid ? X : INFINITY);
+    g.gx1 = wave_max(valid ? X : -INFINITY);
+    g.gy0 = wave_min(valid ? Y : INFINITY);
+    g.gy1 = wave_max(valid ? Y : -INFINITY);
+    g.full = __ballot(valid);
+    g.far = far;
+    if (far) {
+        g.ox = 0.5 * (g.gx0 + g.gx1);
+        g.oy = 0.5 * (g.gy0 + g.gy1);
+        const double d1 = X - g.ox, d2 = Y - g.oy;
+        g.a = (float)sqrt(wave_max(valid ? d1 * d1 + d2 * d2 : 0.0));
+        g.inva = 1.0f / g.a;
+        g.far = g.a > 1e-30f; // (rays at one point: no scale to expand on)
+    }
+    return g;
+}
+
+// Whether a box that every ray accepts may go through the local expansion:
+// a / (d - r_cm) < kFarRatio, r_cm = theta r_cut.  (Strict, so that a group
+// with an infinite coordinate has no far boxes.)
+__device__ inline bool is_far(const RayGroup& g, const CellHdr& h, float theta)
+{
+    if (!g.far) return false;
+    const float f1 = (float)(g.ox - h.cx), f2 = (float)(g.oy - h.cy);
+    const float need = g.a * (1.0f / kFarRatio) + theta * sqrtf((float)h.rcut2);
+    return fmaf(f1, f1, f2 * f2) > need * need;
+}
+
+__host__ __device__ constexpr float far_binomial(int k, int j)
+{
+    double r = 1.0;
+    for (int i = 1; i <= j; ++i) r = r * (double)(k + i) / (double)i; // C(k + j, j)
+    return (float)r;
+}
+
+// Offset of the group's centre from box c's centre of mass, per lane: v = 1/w0
+// (0 on lanes without a box) and |w0|^2.
+struct FarOffset {
+    float v1, v2, r2;
+};
+__device__ inline FarOffset far_offset(const TreeDev& T, const RayGroup& g, int c, bool active)
+{
+    const double2 cm = *reinterpret_cast<const double2*>(&T.hdr[c].cx);
+    const float f1 = active ? (float)(g.ox - cm.x) : 1.0f, f2 = active ? (float)(g.oy - cm.y) : 0.0f;
+    FarOffset o;
+    o.r2 = fmaf(f1, f1, f2 * f2);
+    const float inv = active ? __builtin_amdgcn_rcpf(o.r2) : 0.0f;
+    o.v1 = f1 * inv;
+    o.v2 = -f2 * inv;
+    return o;
+}
+
+// The words L_0 .. L_kFarOrder (Re, Im) of the lane's box, and with PSI the
+// real part of its complex potential at the group's centre,
+// M ln|w0| - Re sum_{k>=2} u_k / k.
+template <int P, bool PSI>
+__device__ inline void far_words(const TreeDev& T, const RayGroup& g, int c, bool active, float* L, float* psi0)
+{
+    const FarOffset o = far_offset(T, g, c, active);
+    constexpr int ST = mom_stride(P);
+    float mo[ST];
+    const float4* mp = reinterpret_cast<const float4*>(T.mom + (size_t)c * ST);
+#pragma unroll
+    for (int i = 0; i < ST / 4; ++i) {
+        const float4 q = mp[i];
+        mo[4 * i] = q.x;
+        mo[4 * i + 1] = q.y;
+        mo[4 * i + 2] = q.z;
+        mo[4 * i + 3] = q.w;
+    }
+    const float M = mo[0], t1 = mo[1] * o.v1, t2 = mo[1] * o.v2;
+    float u1[P + 1], u2[P + 1];
+    float p1 = t1, p2 = t2;
+#pragma unroll
+    for (int k = 2; k <= P; ++k) {
+        const float n1 = fmaf(p1, t1, -p2 * t2), n2 = fmaf(p1, t2, p2 * t1);
+        p1 = n1;
+        p2 = n2;
+        const float q1 = mo[2 + 2 * (k - 2)], q2 = mo[3 + 2 * (k - 2)];
+        u1[k] = fmaf(q1, p1, -q2 * p2);
+        u2[k] = fmaf(q1, p2, q2 * p1);
+    }
+    if constexpr (PSI) {
+        float re = 0.0f;
+#pragma unroll
+        for (int k = P; k >= 2; --k) re = fmaf(u1[k], 1.0f / (float)k, re);
+        *psi0 = active ? fmaf(0.5f * M, __logf(o.r2), -re) : 0.0f;
+    }
+    const float e1 = -g.a * o.v1, e2 = -g.a * o.v2;
+    p1 = o.v1;
+    p2 = o.v2;
+#pragma unroll
+    for (int j = 0; j <= kFarOrder; ++j) {
+        float s1 = M, s2 = 0.0f;
+#pragma unroll
+        for (int k = 2; k <= P; ++k) {
+            s1 = fmaf(far_binomial(k, j), u1[k], s1);
+            s2 = fmaf(far_binomial(k, j), u2[k], s2);
+        }
+        L[2 * j] = fmaf(p1, s1, -p2 * s2);
+        L[2 * j + 1] = fmaf(p1, s2, p2 * s1);
+        const float n1 = fmaf(p1, e1, -p2 * e2), n2 = fmaf(p1, e2, p2 * e1);
+        p1 = n1;
+        p2 = n2;
+    }
+}
+
+// The group's local expansion at this lane's ray (L: the FP64 words in LDS),
+// added to its sums.  L_0 and L_1, the field and its derivative at the centre,
+// stay in FP64.
+template <bool AONLY, bool PSI>
+__device__ inline void far_eval(const RayGroup& g, const double* L, double X, double Y, Acc& A)
+{
+    const double dz1 = (X - g.ox) * (double)g.inva, dz2 = (Y - g.oy) * (double)g.inva;
+    const float z1 = (float)dz1, z2 = (float)dz2;
+    // b = sum_{j>=2} L_j z^(j-2), c = b'
+    float b1 = (float)L[2 * kFarOrder], b2 = (float)L[2 * kFarOrder + 1], c1 = 0.0f, c2 = 0.0f;
+#pragma unroll
+    for (int j = kFarOrder - 1; j >= 2; --j) {
+        if constexpr (!AONLY) {
+            const float m1 = fmaf(c1, z1, fmaf(-c2, z2, b1)), m2 = fmaf(c1, z2, fmaf(c2, z1, b2));
+            c1 = m1;
+            c2 = m2;
+        }
+        const float n1 = fmaf(b1, z1, fmaf(-b2, z2, (float)L[2 * j])), n2 = fmaf(b1, z2, fmaf(b2, z1, (float)L[2 * j + 1]));
+        b1 = n1;
+        b2 = n2;
+    }
+    // F = L_0 + z (L_1 + z b)
+    const float y1 = fmaf(z1, b1, fmaf(-z2, b2, (float)L[2])), y2 = fmaf(z1, b2, fmaf(z2, b1, (float)L[3]));
+    A.a1 += L[0] + (double)fmaf(z1, y1, -z2 * y2);
+    A.a2 -= L[1] + (double)fmaf(z1, y2, z2 * y1);
+    if constexpr (!AONLY) {
+        // a F' = L_1 + z (2 b + z c)
+        const float x1 = fmaf(z1, c1, fmaf(-z2, c2, 2.0f * b1)), x2 = fmaf(z1, c2, fmaf(z2, c1, 2.0f * b2));
+        A.g1 += (L[2] + (double)fmaf(z1, x1, -z2 * x2)) * (double)g.inva;
+        A.g2 -= (L[3] + (double)fmaf(z1, x2, z2 * x1)) * (double)g.inva;
+    }
+    if constexpr (PSI) {
+        // a sum_j L_j z^(j+1) / (j + 1), L_0's part in FP64
+        float s1 = 0.0f, s2 = 0.0f;
+#pragma unroll
+        for (int j = kFarOrder; j >= 1; --j) {
+            const float q1 = (float)L[2 * j] * (1.0f / (float)(j + 1)), q2 = (float)L[2 * j + 1] * (1.0f / (float)(j + 1));
+            const float n1 = fmaf(s1, z1, fmaf(-s2, z2, q1)), n2 = fmaf(s1, z2, fmaf(s2, z1, q2));
+            s1 = n1;
+            s2 = n2;
+        }
+        const float w1 = fmaf(z1, z1, -z2 * z2), w2 = 2.0f * z1 * z2;
+        A.ps += (double)g.a * (dz1 * L[0] - dz2 * L[1] + (double)fmaf(s1, w1, -s2 * w2));
+    }
+}
+
+} // namespace glm

@@ -1,0 +1,322 @@
+// Lane-parallel tree traversal of one 64-ray group, shared by the forward walk
+// and its adjoint.
+//
+// The traversal keeps a stack of (box, mask) items in LDS, the mask naming the
+// rays of the group that have accepted no ancestor of the box.  A round takes
+// many items, one per lane, and tests each box against the group's bounding
+// box: either every ray accepts it, or none does, or the decision differs
+// between rays (about one box in three) and is taken ray by ray, with lanes as
+// rays.  The bounding-box distances round monotonically (the same FP64
+// operations as the per-ray test, no contraction), so the decisions are
+// exactly those of a per-ray walk.  The boxes' work then goes to a visitor:
+//   box(c, acc, w1, w2)      rays `acc` accept box c (offset w per ray)
+//   leaf(pbeg, pend, opn)    rays `opn` sum these particles
+//   list(lbeg, lend, act)    rays `act` check these big-particle list entries
+// with wave-uniform arguments and lanes as rays.  A box that every ray of the
+// group accepts, far enough from the group, goes to
+//   far(c, active)           lanes as boxes
+// instead: its field over the group is a local expansion (farfield.hpp).
+//
+// A stackless preorder walk with lanes as rays (one box at a time, every box
+// tested per ray) spent a fifth of its instructions on the traversal, and a
+// dependent scalar load per box made it slow wherever few wavefronts run.
+//
+// One wavefront serves a group (SOLO), or W wavefronts of one workgroup do: they
+// share the stack, take interleaved items, and deal the resulting work among
+// themselves through LDS queues, so that a group with much work (the centre
+// of a halo, seen by few scattered rays) is not left to one wavefront.
+#pragma once
+
+#include "farfield.hpp"
+#include "walk.hpp"
+
+namespace glm {
+
+// Stack room that a descent box by box can need: three siblings per level.
+constexpr int kStackReserve = 3 * kMaxLevel;
+constexpr int kSoloStack = 448;   // items of a SOLO stack
+constexpr int kMaxGroupWaves = 16;
+constexpr int kFarQueue = 2 * kWave; // far boxes waiting for their pass
+
+// Items to take off a stack of `top` items: as many as leave the reserve after
+// their (at most four) children went on; one by one when there is no such room
+// (a depth-first descent then stays inside the reserve).
+__device__ inline int take_count(int top, int cap, int most)
+{
+    int n = (cap - top - kStackReserve) / 3;
+    n = n < 1 ? 1 : n;
+    n = n < most ? n : most;
+    return n < top ? n : top;
+}
+
+// LDS of one group (device pointers into dynamic LDS; queues only with W > 1).
+struct TravLds {
+    uint64_t* stkm;
+    uint64_t* qm;   // three queues of `qcap` masks: accepted boxes, open leaves, lists
+    int* stkb;
+    int* qb;        // the queues' boxes
+    int* cnt;       // 4 x kMaxGroupWaves item counts of a round
+    int* fq;        // this wavefront's far boxes
+    int cap, qcap;
+};
+
+__host__ __device__ constexpr int coop_stack(int W) { return W <= 4 ? 1024 : 2048; }
+__host__ __device__ constexpr int coop_queue(int W)
+{
+    const int by_stack = (coop_stack(W) - kStackReserve) / 3;
+    return kWave * W < by_stack ? kWave * W : by_stack;
+}
+__host__ __device__ constexpr size_t solo_lds_bytes() { return 12ull * kSoloStack + 4ull * kFarQueue; }
+__host__ __device__ constexpr size_t coop_lds_bytes(int W)
+{
+    return 12ull * coop_stack(W) + 36ull * coop_queue(W) + 16ull * kMaxGroupWaves + 4ull * kFarQueue * W;
+}
+
+__device__ inline TravLds solo_lds(char* base)
+{
+    TravLds L{};
+    L.cap = kSoloStack;
+    L.stkm = reinterpret_cast<uint64_t*>(base);
+    L.stkb = reinterpret_cast<int*>(base + 8 * kSoloStack);
+    L.fq = L.stkb + kSoloStack;
+    return L;
+}
+
+__device__ inline TravLds coop_lds(char* base, int w, int W)
+{
+    TravLds L;
+    L.cap = coop_stack(W);
+    L.qcap = coop_queue(W);
+    L.stkm = reinterpret_cast<uint64_t*>(base);
+    L.qm = L.stkm + L.cap;
+    L.stkb = reinterpret_cast<int*>(L.qm + 3 * L.qcap);
+    L.qb = L.stkb + L.cap;
+    L.cnt = L.qb + 3 * L.qcap;
+    L.fq = L.cnt + 4 * kMaxGroupWaves + w * kFarQueue;
+    return L;
+}
+
+__device__ inline uint64_t readlane64(uint64_t v, int k)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, k);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), k);
+    return ((uint64_t)hi << 32) | lo;
+}
+__device__ inline uint64_t uniform64(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+// lanes below this one whose bit is set in m
+__device__ inline int rank_in(uint64_t m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+// this lane's bit of a wave-uniform mask
+__device__ inline bool lane_bit(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// Smallest and largest FP64 squared distance of a point to the group's
+// bounding box; both round like the per-ray sqdist, so they bound its value for
+// every ray of the group.
+__device__ inline void box_dist2(const RayGroup& g, double cx, double cy, double* dn2, double* df2)
+{
+#pragma clang fp contract(off)
+    const double xa = g.gx0 - cx, xb = g.gx1 - cx, ya = g.gy0 - cy, yb = g.gy1 - cy;
+    const double nx = fmax(fmax(xa, -xb), 0.0), ny = fmax(fmax(ya, -yb), 0.0);
+    const double fx = fmax(fabs(xa), fabs(xb)), fy = fmax(fabs(ya), fabs(yb));
+    *dn2 = nx * nx + ny * ny;
+    *df2 = fx * fx + fy * fy;
+}
+
+// The traversal (see the file comment).  Every lane of the group's W
+// wavefronts calls it; X, Y is the lane's ray (the same in every wavefront).
+template <bool COOP, class V>
+__device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, double X, double Y, int lane, int w, int W,
+                                const TravLds& L)
+{
+    int top = 1;
+    if (w == 0 && lane == 0) {
+        L.stkb[0] = 0;
+        L.stkm[0] = g.full;
+    }
+    if constexpr (COOP) __syncthreads();
+    int rot = 0; // which wavefront takes the next queue item
+    int nf = 0;  // far boxes queued
+    while (top > 0) {
+        if constexpr (V::farfield)
+            if (nf >= kWave) {
+                nf -= kWave;
+                v.far(L.fq[nf + lane], true);
+            }
+        top = __builtin_amdgcn_readfirstlane(top);
+        const int n = take_count(top, L.cap, COOP ? (kWave * W < L.qcap ? kWave * W : L.qcap) : kWave);
+        const int idx = COOP ? lane * W + w : lane; // interleaved, so that every wavefront gets a share
+        const bool has = idx < n;
+        top -= n;
+        int c = 0;
+        uint64_t m = 0;
+        if (has) {
+            c = L.stkb[top + idx];
+            m = L.stkm[top + idx];
+        }
+        const CellHdr h = T.hdr[c];
+        double dn2, df2;
+        box_dist2(g, h.cx, h.cy, &dn2, &df2);
+        const bool all = has && dn2 > h.rcut2;
+        const bool mixed = has && !all && df2 > h.rcut2;
+        const bool leaf = (h.info & kInfoLeaf) != 0;
+        bool fa = false;
+        if constexpr (V::farfield) {
+            fa = all && m == g.full && is_far(g, h, T.theta);
+            const uint64_t fb = __ballot(fa);
+            if (fa) L.fq[nf + rank_in(fb)] = c;
+            nf += __popcll(fb);
+            if constexpr (V::stats) v.accepted(__popcll(fb));
+        }
+        if constexpr (V::stats) v.visited(__popcll(__ballot(has && m == g.full)));
+        // the boxes that only some rays accept, and (SOLO) all the work of the accepted ones
+        uint64_t am = all ? m : 0ull;
+        uint64_t todo = COOP ? __ballot(mixed) : __ballot(mixed || (all && !fa));
+        while (todo) {
+            const int k = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            const int ck = __builtin_amdgcn_readlane(c, k);
+            const bool act = lane_bit(readlane64(m, k));
+            const CellHdr hk = uniform_ld(T.hdr, ck);
+            double w1, w2;
+            const double d2 = sqdist(X, Y, hk.cx, hk.cy, &w1, &w2);
+            const bool acc = act && d2 > hk.rcut2;
+            const uint64_t ak = __ballot(acc);
+            if constexpr (!COOP)
+                if (ak) v.box(ck, acc, w1, w2);
+            if (lane == k) am = ak;
+        }
+        if constexpr (V::stats) {
+            uint64_t part = __ballot(has && m != g.full);
+            while (part) {
+                const int k = __ffsll((unsigned long long)part) - 1;
+                part &= part - 1;
+                v.visited_some(lane_bit(readlane64(m, k)));
+            }
+        }
+        const uint64_t om = m & ~am; // the rays that open the box
+        bool lr = false;
+        if (has && (h.info & kInfoList)) {
+            const double* q = T.lreach + 4 * (size_t)c;
+            lr = (g.gx1 >= q[0]) & (g.gx0 <= q[1]) & (g.gy1 >= q[2]) & (g.gy0 <= q[3]);
+        }
+        const bool opl = has && leaf && om != 0;
+        if constexpr (!COOP) {
+            CellExt e{};
+            if (lr || opl) e = T.ext[c];
+            uint64_t lt = __ballot(lr);
+            while (lt) {
+                const int k = __ffsll((unsigned long long)lt) - 1;
+                lt &= lt - 1;
+                v.list(__builtin_amdgcn_readlane(e.lbeg, k), __builtin_amdgcn_readlane(e.lend, k), kWave,
+                       readlane64(m, k));
+            }
+            uint64_t lf = __ballot(opl);
+            while (lf) {
+                const int k = __ffsll((unsigned long long)lf) - 1;
+                lf &= lf - 1;
+                v.leaf(__builtin_amdgcn_readlane(e.pbeg, k), __builtin_amdgcn_readlane(e.pend, k), readlane64(om, k));
+            }
+        }
+        // children of the opened boxes
+        const bool push = has && !leaf && om != 0;
+        int4 kc = make_int4(-1, -1, -1, -1);
+        if (push) kc = *reinterpret_cast<const int4*>(T.kids + 4 * (size_t)c);
+        const int kid[4] = {kc.x, kc.y, kc.z, kc.w};
+        uint64_t kb[4];
+        int nk = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            kb[u] = __ballot(kid[u] >= 0);
+            nk += __popcll(kb[u]);
+        }
+        int at = top; // where this wavefront's children go
+        if constexpr (COOP) {
+            const uint64_t qa[3] = {__ballot(am != 0 && !fa), __ballot(opl), __ballot(lr)};
+            if (lane == 0) {
+                L.cnt[w] = nk;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) L.cnt[(q + 1) * kMaxGroupWaves + w] = __popcll(qa[q]);
+            }
+            __syncthreads();
+            // lane 16 q + u: count q of wavefront u; inclusive sums along each row of 16
+            int cv = (lane & 15) < W ? L.cnt[lane] : 0;
+#pragma unroll
+            for (int o = 1; o < kMaxGroupWaves; o <<= 1) {
+                const int t = __shfl_up(cv, o, kMaxGroupWaves);
+                if ((lane & 15) >= o) cv += t;
+            }
+            at += __builtin_amdgcn_readlane(cv, w) - nk;
+            top += __builtin_amdgcn_readlane(cv, 15);
+            int qn[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const int me = __popcll(qa[q]);
+                const int off = __builtin_amdgcn_readlane(cv, 16 * (q + 1) + w) - me;
+                qn[q] = __builtin_amdgcn_readlane(cv, 16 * (q + 1) + 15);
+                if (lane_bit(qa[q])) {
+                    const int p = q * L.qcap + off + rank_in(qa[q]);
+                    L.qb[p] = c;
+                    L.qm[p] = q == 0 ? am : (q == 1 ? om : m);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (kid[u] >= 0) {
+                    const int p = at + rank_in(kb[u]);
+                    L.stkb[p] = kid[u];
+                    L.stkm[p] = om;
+                }
+                at += __popcll(kb[u]);
+            }
+            __syncthreads();
+            // the round's work, dealt item by item (W is a power of two)
+            for (int i = (w - rot) & (W - 1); i < qn[0]; i += W) {
+                const int ck = __builtin_amdgcn_readfirstlane(L.qb[i]);
+                const bool acc = lane_bit(uniform64(L.qm[i]));
+                const CellHdr hk = uniform_ld(T.hdr, ck);
+                v.box(ck, acc, X - hk.cx, Y - hk.cy);
+            }
+            rot += qn[0];
+            for (int i = (w - rot) & (W - 1); i < qn[1]; i += W) {
+                const CellExt e = uniform_ld(T.ext, __builtin_amdgcn_readfirstlane(L.qb[L.qcap + i]));
+                v.leaf(e.pbeg, e.pend, uniform64(L.qm[L.qcap + i]));
+            }
+            rot += qn[1];
+            // short lists go to one wavefront each, the chunks of a long one to all in turn
+            for (int i = 0; i < qn[2]; ++i) {
+                const int p = 2 * L.qcap + i;
+                const CellExt e = uniform_ld(T.ext, __builtin_amdgcn_readfirstlane(L.qb[p]));
+                const int my = (w - rot) & (W - 1);
+                const int chunks = (e.lend - e.lbeg + kWave - 1) / kWave;
+                rot += chunks;
+                if (my < chunks) v.list(e.lbeg + my * kWave, e.lend, kWave * W, uniform64(L.qm[p]));
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (kid[u] >= 0) {
+                    const int p = at + rank_in(kb[u]);
+                    L.stkb[p] = kid[u];
+                    L.stkm[p] = om;
+                }
+                at += __popcll(kb[u]);
+            }
+            top = at;
+        }
+    }
+    if constexpr (V::farfield)
+        while (nf > 0) { // at most two passes are left
+            const int n = nf < kWave ? nf : kWave;
+            nf -= n;
+            v.far(lane < n ? L.fq[nf + lane] : 0, lane < n);
+        }
+}
+
+} // namespace glm

@@ -1,249 +1,16 @@
-// Forward tree walk on gfx950 (Sec. 3.2) with ray staging.
-//
-// One wavefront walks the tree for a group of 64 rays that are neighbours in
-// Morton order.  The group shares one depth-first traversal of the preorder
-// box array without a stack: every lane keeps the preorder index at which it
-// becomes active again (after it accepted a box, it sleeps until the end of
-// that box's subtree), the wave descends into a box if any awake lane opens
-// it and jumps over the subtree otherwise.  Every decision is per ray, as in
-// the paper's walk: per lane FP64 opening test |x - x_cm|^2 > r_cut^2, per
-// lane FP64 inside test for each particle.  Box headers, moments and particle
-// records are wave-uniform and come through scalar loads; only the
-// big-particle lists are first filtered lane-parallel against the group's
-// bounding box.  Evaluation is FP32: the multipole series is a Horner scheme
-// in t = r_cm / w on moments normalised by M r_cm^k, alpha is accumulated with
-// FP64 accumulation of the FP32 terms.
+// Ray staging, and the launches of the forward walk (Sec. 3.2) and of the
+// batched walk of many lenses.  The walk itself is in traverse.hpp and
+// walk_fwd.hpp.
 #include <math.h>
 
 #include <algorithm>
 #include <vector>
 
-#include "eval.hpp"
-#include "walk.hpp"
+#include "walk_fwd.hpp"
 
 namespace glm {
 
 namespace {
-
-// The traversal of one 64-ray group (see the file comment).  Every lane of
-// the wave must call it; `valid` lanes carry a ray.
-// MODE: 0 = alpha summed in FP64 (the product walk), 1 = the same plus
-// per-ray interaction counts, 2 = plain FP32 sum of the alpha terms (debug).
-template <int MODE>
-struct WalkMode {
-    static constexpr bool f64a = MODE != 2;
-    static constexpr bool stats = MODE == 1;
-};
-
-template <int P, bool AONLY, int MODE, bool PSI = false, int KIND = kKindGauss>
-__device__ inline void walk_group(const TreeDev& T, double X, double Y, bool valid, int lane, Acc& A, int cnt[kCounts],
-                                  int c0, int c1)
-{
-    constexpr bool F64A = WalkMode<MODE>::f64a;
-    constexpr bool STATS = WalkMode<MODE>::stats;
-    const double gx0 = wave_min(valid ? X : INFINITY), gx1 = wave_max(valid ? X : -INFINITY);
-    const double gy0 = wave_min(valid ? Y : INFINITY), gy1 = wave_max(valid ? Y : -INFINITY);
-    int n_vis = 0, n_acc = 0, n_dir = 0, n_hit = 0, n_scan = 0, w_acc = 0, w_dir = 0, w_cand = 0;
-    int skip = valid ? 0 : 0x7fffffff;
-    if (c0 > 0 && c0 < c1) skip = ancestor_skip(T, X, Y, c0, skip); // (an empty range walks nothing)
-    int cur = c0;
-    while (cur < c1) {
-        cur = __builtin_amdgcn_readfirstlane(cur);
-        const CellHdr h = T.hdr[cur];
-        const bool act = cur >= skip;
-        if constexpr (STATS) n_vis += act;
-        if ((h.info & kInfoList) && list_reaches(T, cur, gx0, gx1, gy0, gy1)) {
-            const CellExt e = T.ext[cur];
-            for (int base = e.lbeg; base < e.lend; base += kWave) {
-                if constexpr (STATS) n_scan += (base + kWave < e.lend ? kWave : e.lend - base);
-                const int j = base + lane;
-                bool cand = false;
-                if (j < e.lend) {
-                    const PRec pr = T.lst[j];
-                    const double dx = fmax(fmax(gx0 - pr.x, pr.x - gx1), 0.0);
-                    const double dy = fmax(fmax(gy0 - pr.y, pr.y - gy1), 0.0);
-                    cand = dx * dx + dy * dy < pr.qs2 * (1.0 + 1e-9);
-                }
-                uint64_t cm = __ballot(cand);
-                if constexpr (STATS) w_cand += __popcll(cm);
-                while (cm) {
-                    const int k = __ffsll((unsigned long long)cm) - 1;
-                    cm &= cm - 1;
-                    const PRec pr = T.lst[__builtin_amdgcn_readfirstlane(base + k)];
-                    if (act) list_particle<AONLY, F64A, PSI, KIND>(pr, X, Y, A, n_hit, T.psiK, T.einTerms, T.invC);
-                }
-            }
-        }
-        double w1, w2;
-        const double d2 = sqdist(X, Y, h.cx, h.cy, &w1, &w2);
-        const bool acc = act && d2 > h.rcut2;
-        const bool opn = act && !acc;
-        if constexpr (STATS) n_acc += acc;
-        if (__any(acc)) {
-            if constexpr (STATS) ++w_acc;
-            if (acc) eval_box<P, AONLY, F64A, PSI>(T.mom + (size_t)cur * mom_stride(P), w1, w2, A);
-        }
-        if (h.info & kInfoLeaf) {
-            if (__any(opn)) {
-                const CellExt e = T.ext[cur];
-                if constexpr (STATS) {
-                    if (opn) n_dir += e.pend - e.pbeg;
-                    w_dir += e.pend - e.pbeg;
-                }
-                for (int j = e.pbeg; j < e.pend; ++j) {
-                    const PRec pr = T.prt[j];
-                    if (opn) leaf_particle<AONLY, F64A, PSI, KIND>(pr, X, Y, A, T.psiK, T.einTerms, T.invC);
-                }
-            }
-            cur = cur + 1;
-        } else if (__any(opn)) {
-            if (acc) skip = h.next;
-            cur = cur + 1;
-        } else {
-            cur = h.next > cur ? h.next : cur + 1; // preorder: the subtree ends after cur
-        }
-    }
-    cnt[0] = n_vis;
-    cnt[1] = n_acc;
-    cnt[2] = n_dir;
-    cnt[3] = n_hit;
-    cnt[4] = n_scan;
-    cnt[5] = w_acc;
-    cnt[6] = w_dir;
-    cnt[7] = w_cand;
-}
-
-template <bool AONLY, bool STATS, bool PSI = false>
-__device__ inline void write_out(const Acc& A, const int cnt[kCounts], int64_t o, const WalkOut& out)
-{
-    const double a1 = alpha1(A), a2 = alpha2(A);
-    out.a1[o] = (float)a1;
-    out.a2[o] = (float)a2;
-    if constexpr (PSI) {
-        out.psi[o] = (float)A.ps;
-        if (out.td) out.td[o] = (float)(0.5 * (a1 * a1 + a2 * a2) - A.ps); // Sec. 3.2: |alpha|^2 / 2 - psi
-    }
-    if (!AONLY) {
-        if (out.k) out.k[o] = A.k;
-        if (out.g1) out.g1[o] = (float)A.g1;
-        if (out.g2) out.g2[o] = (float)A.g2;
-    }
-    if (STATS && out.counts)
-        for (int i = 0; i < kCounts; ++i) out.counts[kCounts * o + i] = cnt[i];
-}
-
-template <int P, bool AONLY, int MODE, bool PSI = false, int KIND = kKindGauss>
-__global__ __launch_bounds__(kBlock) void k_walk(TreeDev T, const double* __restrict__ rxs,
-                                                const double* __restrict__ rys, const uint32_t* __restrict__ rperm,
-                                                int64_t nrays, WalkOut out, int K, Partial* __restrict__ parts,
-                                                const int* __restrict__ split_box)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t groups = (nrays + kWave - 1) / kWave;
-    // wave-uniform work item (kept in SGPRs): box range k, ray group grp
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    int k;
-    int64_t grp;
-    if (!walk_task(blockIdx.x, w, groups, K, &k, &grp)) return;
-    const int64_t r = grp * kWave + lane;
-    const bool valid = r < nrays;
-    const double X = valid ? rxs[r] : 0.0, Y = valid ? rys[r] : 0.0;
-    const int nc = T.ncells;
-    int c0, c1;
-    if (K > 1) {
-        const int B = __builtin_amdgcn_readfirstlane(*split_box);
-        if (B >= 0) {
-            split_range(k, K, B, T.hdr[B].next, nc, &c0, &c1);
-        } else { // no split: the first range takes every box
-            c0 = 0;
-            c1 = k == 0 ? nc : 0;
-        }
-    } else {
-        c0 = 0;
-        c1 = nc;
-    }
-    Acc A = {};
-    int cnt[kCounts];
-    walk_group<P, AONLY, MODE, PSI, KIND>(T, X, Y, valid, lane, A, cnt, c0, c1);
-    if (!valid) return;
-    if (K == 1) {
-        write_out<AONLY, WalkMode<MODE>::stats, PSI>(A, cnt, rperm ? (int64_t)rperm[r] : r, out);
-        return;
-    }
-    Partial q;
-    q.a1 = alpha1(A);
-    q.a2 = alpha2(A);
-    q.k = A.k;
-    q.g1 = A.g1;
-    q.g2 = A.g2;
-    for (int i = 0; i < kCounts; ++i) q.cnt[i] = WalkMode<MODE>::stats ? cnt[i] : 0;
-    parts[(int64_t)k * nrays + r] = q;
-}
-
-// Per ray, the partial sums of the K box ranges in range order.
-template <bool AONLY>
-__global__ __launch_bounds__(kBlock) void k_walk_merge(const Partial* __restrict__ parts, int K, int64_t nrays,
-                                                      const uint32_t* __restrict__ rperm, WalkOut out)
-{
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (r >= nrays) return;
-    double a1 = 0.0, a2 = 0.0, g1 = 0.0, g2 = 0.0;
-    float ka = 0.0f;
-    int c[kCounts] = {};
-    for (int k = 0; k < K; ++k) {
-        const Partial& q = parts[(int64_t)k * nrays + r];
-        a1 += q.a1;
-        a2 += q.a2;
-        ka += q.k;
-        g1 += q.g1;
-        g2 += q.g2;
-        for (int i = 0; i < kCounts; ++i) c[i] += q.cnt[i];
-    }
-    const int64_t o = rperm ? (int64_t)rperm[r] : r;
-    out.a1[o] = (float)a1;
-    out.a2[o] = (float)a2;
-    if (!AONLY) {
-        if (out.k) out.k[o] = ka;
-        if (out.g1) out.g1[o] = (float)g1;
-        if (out.g2) out.g2[o] = (float)g2;
-    }
-    if (out.counts)
-        for (int i = 0; i < kCounts; ++i) out.counts[kCounts * o + i] = c[i];
-}
-
-// Persistent walk over many lenses: every wavefront takes (lens, 64-ray group)
-// items from a device counter until the queue is empty.  Lenses are ranked by
-// estimated cost, so the largest ray groups start first.
-template <int P, bool AONLY, int MODE, int KIND>
-__global__ __launch_bounds__(kBlock) void k_walk_batched(const BatchLens* __restrict__ lenses, int nlens,
-                                                        const int64_t* __restrict__ gprefix, int* __restrict__ counter,
-                                                        const double* __restrict__ xs, const double* __restrict__ ys,
-                                                        const uint32_t* __restrict__ perm)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t total = gprefix[nlens];
-    for (;;) {
-        int it = 0;
-        if (lane == 0) it = atomicAdd(counter, 1);
-        it = __builtin_amdgcn_readfirstlane(__shfl(it, 0, kWave));
-        if (it >= total) break;
-        int lo = 0, hi = nlens; // largest l with gprefix[l] <= it
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (gprefix[mid] <= it) lo = mid;
-            else hi = mid;
-        }
-        const BatchLens& L = lenses[lo];
-        const int64_t rl = (int64_t)(it - gprefix[lo]) * kWave + lane;
-        const bool valid = rl < L.nrays;
-        const int64_t gi = L.ray_off + (valid ? rl : 0);
-        const double X = valid ? xs[gi] : 0.0, Y = valid ? ys[gi] : 0.0;
-        Acc A = {};
-        int cnt[kCounts];
-        walk_group<P, AONLY, MODE, false, KIND>(L.tree, X, Y, valid, lane, A, cnt, 0, L.tree.ncells);
-        if (valid) write_out<AONLY, false>(A, cnt, (int64_t)perm[gi] - L.ray_off, L.out);
-    }
-}
 
 // ------------------------------------------------------------ ray staging
 
@@ -372,69 +139,6 @@ __global__ void k_split_box(BoxArrays b, const int32_t* __restrict__ next, doubl
     *out = c < ncells ? c : 0;
 }
 
-template <int P, bool AONLY>
-void launch_walk(const TreeDev& T, const double* rxs, const double* rys, const uint32_t* rperm, int64_t nrays,
-                 const WalkOut& out, int mode, int K, Partial* parts, const int* split_box, hipStream_t st)
-{
-    const dim3 g((unsigned)walk_grid_blocks((nrays + kWave - 1) / kWave, K)), b(kBlock);
-#define GLM_WALK(MD, KD) \
-    hipLaunchKernelGGL((k_walk<P, AONLY, MD, false, KD>), g, b, 0, st, T, rxs, rys, rperm, nrays, out, K, parts, split_box)
-    if (T.kind == kKindNfw) {
-        if (mode == 1) GLM_WALK(1, kKindNfw);
-        else if (mode == 2) GLM_WALK(2, kKindNfw);
-        else GLM_WALK(0, kKindNfw);
-    } else {
-        if (mode == 1) GLM_WALK(1, kKindGauss);
-        else if (mode == 2) GLM_WALK(2, kKindGauss);
-        else GLM_WALK(0, kKindGauss);
-    }
-#undef GLM_WALK
-    if (K > 1)
-        hipLaunchKernelGGL((k_walk_merge<AONLY>), dim3(ceil_div(nrays, kBlock)), b, 0, st, parts, K, nrays, rperm, out);
-}
-
-// alpha and psi in one walk, no split (K = 1)
-template <int P>
-void launch_potential(const TreeDev& T, const double* rxs, const double* rys, const uint32_t* rperm, int64_t nrays,
-                      const WalkOut& out, hipStream_t st)
-{
-    const dim3 g((unsigned)walk_grid_blocks((nrays + kWave - 1) / kWave, 1)), b(kBlock);
-    if (T.kind == kKindNfw)
-        hipLaunchKernelGGL((k_walk<P, true, 0, true, kKindNfw>), g, b, 0, st, T, rxs, rys, rperm, nrays, out, 1, nullptr,
-                           nullptr);
-    else
-        hipLaunchKernelGGL((k_walk<P, true, 0, true, kKindGauss>), g, b, 0, st, T, rxs, rys, rperm, nrays, out, 1,
-                           nullptr, nullptr);
-}
-
-template <bool AONLY>
-void dispatch_walk(int p, const TreeDev& T, const double* rxs, const double* rys, const uint32_t* rperm,
-                   int64_t nrays, const WalkOut& out, int mode, int K, Partial* parts, const int* split_box,
-                   hipStream_t st)
-{
-#define GLM_CASE(PP) \
-    case PP: launch_walk<PP, AONLY>(T, rxs, rys, rperm, nrays, out, mode, K, parts, split_box, st); break;
-    switch (p) {
-        GLM_CASE(0) GLM_CASE(1) GLM_CASE(2) GLM_CASE(3) GLM_CASE(4) GLM_CASE(5) GLM_CASE(6)
-        GLM_CASE(7) GLM_CASE(8) GLM_CASE(9) GLM_CASE(10) GLM_CASE(11) GLM_CASE(12)
-        default: break;
-    }
-#undef GLM_CASE
-}
-
-void dispatch_potential(int p, const TreeDev& T, const double* rxs, const double* rys, const uint32_t* rperm,
-                        int64_t nrays, const WalkOut& out, hipStream_t st)
-{
-#define GLM_CASE(PP) \
-    case PP: launch_potential<PP>(T, rxs, rys, rperm, nrays, out, st); break;
-    switch (p) {
-        GLM_CASE(0) GLM_CASE(1) GLM_CASE(2) GLM_CASE(3) GLM_CASE(4) GLM_CASE(5) GLM_CASE(6)
-        GLM_CASE(7) GLM_CASE(8) GLM_CASE(9) GLM_CASE(10) GLM_CASE(11) GLM_CASE(12)
-        default: break;
-    }
-#undef GLM_CASE
-}
-
 } // namespace
 
 RayLayout ray_layout(int64_t nrays)
@@ -451,7 +155,6 @@ RayLayout ray_layout(int64_t nrays)
     L.part = a.take(sizeof(double) * 4 * (kRayBboxBlocks + 1));
     L.sbox = a.take(64);
     L.split = walk_split(nrays);
-    L.parts = a.take(sizeof(Partial) * (size_t)split_slots(nrays));
     L.bytes = a.size;
     return L;
 }
@@ -619,24 +322,6 @@ BatchLayout batch_layout(int nlens, int64_t total)
     return B;
 }
 
-template <int P, bool AONLY>
-void launch_batched(const BatchLens* table, int nlens, const int64_t* gpre, int* counter, const double* xs,
-                    const double* ys, const uint32_t* perm, int64_t items, int f64a, int kind, hipStream_t st)
-{
-    const int blocks = (int)std::min<int64_t>((items + 3) / 4, 256 * 8);
-#define GLM_WALK(MD, KD)                                                                                    \
-    hipLaunchKernelGGL((k_walk_batched<P, AONLY, MD, KD>), dim3(blocks), dim3(kBlock), 0, st, table, nlens, gpre, \
-                       counter, xs, ys, perm)
-    if (kind == kKindNfw) {
-        if (f64a) GLM_WALK(0, kKindNfw);
-        else GLM_WALK(2, kKindNfw);
-    } else {
-        if (f64a) GLM_WALK(0, kKindGauss);
-        else GLM_WALK(2, kKindGauss);
-    }
-#undef GLM_WALK
-}
-
 } // namespace
 
 size_t batch_workspace_bytes(int nlens, int64_t total) { return batch_layout(nlens, total).bytes; }
@@ -692,21 +377,9 @@ glm_status shoot_batched_device(const BatchLens* host_table, int nlens, int orde
     const uint64_t* ks = w ? k1 : k0;
     const uint32_t* perm = w ? v1 : v0;
     hipLaunchKernelGGL(k_batch_gather, dim3(g), dim3(kBlock), 0, st, dtab, droff, ks, perm, total, bits, xs, ys);
-    const int f64a = (flags & GLM_FP32_ALPHA) ? 0 : 1;
-    const int kind = host_table[0].tree.kind; // every lens of a batch has the same particle kind
-#define GLM_CASE(PP)                                                                                     \
-    case PP:                                                                                             \
-        if (flags & GLM_ALPHA_ONLY)                                                                      \
-            launch_batched<PP, true>(dtab, nlens, dgpre, counter, xs, ys, perm, items, f64a, kind, st); \
-        else                                                                                             \
-            launch_batched<PP, false>(dtab, nlens, dgpre, counter, xs, ys, perm, items, f64a, kind, st);\
-        break;
-    switch (order) {
-        GLM_CASE(0) GLM_CASE(1) GLM_CASE(2) GLM_CASE(3) GLM_CASE(4) GLM_CASE(5) GLM_CASE(6)
-        GLM_CASE(7) GLM_CASE(8) GLM_CASE(9) GLM_CASE(10) GLM_CASE(11) GLM_CASE(12)
-        default: return fail(GLM_EINVAL, "unsupported order");
-    }
-#undef GLM_CASE
+    // every lens of a batch has the same order and particle kind
+    launch_walk_batched(BatchArgs{dtab, nlens, dgpre, counter, xs, ys, perm, items, order, host_table[0].tree.kind,
+                                  (flags & GLM_ALPHA_ONLY) != 0, (flags & GLM_FP32_ALPHA) != 0, st});
     GLM_HIP(hipGetLastError());
     return GLM_OK;
 }
@@ -742,24 +415,13 @@ glm_status shoot_device(const TreeStorage& ts, const double* rx, const double* r
         glm_status rc = stage_rays(rx, ry, nrays, ws, L, &sr, st);
         if (rc != GLM_OK) return rc;
     }
-    // box ranges per group: never more than one range per 64 boxes
-    int K = L.split;
-    while (K > 1 && (int64_t)K * 64 > ts.ncells) --K;
-    if (K < 4) K = 1;
-    Partial* parts = K > 1 ? reinterpret_cast<Partial*>(static_cast<char*>(ws) + L.parts) : nullptr;
-    int* split_box = nullptr;
-    if (K > 1) {
-        glm_status rc = split_box_device(ts, rx, ry, nrays, ws, L, !(flags & GLM_RAYS_ORDERED), &split_box, st);
-        if (rc != GLM_OK) return rc;
-    }
+    const WalkArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, WalkOut{a1, a2, k, g1, g2, counts}, walk_waves(nrays), walk_far(nrays), st};
+    const bool aonly = (flags & GLM_ALPHA_ONLY) != 0;
     // counts requested: the product walk with counters; else the product or the plain-FP32 walk
-    const int mode = counts ? 1 : ((flags & GLM_FP32_ALPHA) ? 2 : 0);
-    if (flags & GLM_ALPHA_ONLY)
-        dispatch_walk<true>(ts.params.order, ts.dev, sr.xs, sr.ys, sr.perm, nrays,
-                            WalkOut{a1, a2, nullptr, nullptr, nullptr, counts}, mode, K, parts, split_box, st);
-    else
-        dispatch_walk<false>(ts.params.order, ts.dev, sr.xs, sr.ys, sr.perm, nrays, WalkOut{a1, a2, k, g1, g2, counts},
-                             mode, K, parts, split_box, st);
+    if (counts) launch_walk_counts(a, aonly);
+    else if (flags & GLM_FP32_ALPHA) launch_walk_fp32(a, aonly);
+    else if (aonly) launch_walk_alpha(a);
+    else launch_walk_full(a);
     GLM_HIP(hipGetLastError());
     return GLM_OK;
 }
@@ -777,7 +439,7 @@ glm_status potential_device(const TreeStorage& ts, const double* rx, const doubl
     WalkOut out{a1, a2, nullptr, nullptr, nullptr, nullptr};
     out.psi = psi;
     out.td = td;
-    dispatch_potential(ts.params.order, ts.dev, sr.xs, sr.ys, sr.perm, nrays, out, st);
+    launch_walk_potential(WalkArgs{ts.dev, sr.xs, sr.ys, sr.perm, nrays, out, walk_waves(nrays), walk_far(nrays), st});
     GLM_HIP(hipGetLastError());
     return GLM_OK;
 }

@@ -81,16 +81,6 @@ inline int walk_split(int64_t nrays)
     return (int)k;
 }
 
-// Partial-sum slots (K x rays) to reserve for up to nrays rays: a bound that
-// grows with nrays, so that a workspace sized for a launch also fits every
-// smaller one (K * groups < kSplitWaves + kSplitWaves / kMinSplit).
-inline int64_t split_slots(int64_t nrays)
-{
-    const int64_t groups = (nrays + 63) / 64;
-    const int64_t cap = kSplitWaves + kSplitWaves / kMinSplit;
-    return 64 * (kMaxSplit * groups < cap ? kMaxSplit * groups : cap);
-}
-
 // Per-ray counts of a walk: boxes visited (opening tests), boxes accepted,
 // leaf particles summed, list particles the ray falls inside; then counts of
 // its wavefront (the same for the 64 rays of a group): list entries tested
@@ -99,19 +89,9 @@ inline int64_t split_slots(int64_t nrays)
 // wavefront's give the lane use of each phase.
 constexpr int kCounts = 8;
 
-// Partial sums of one ray over one range of boxes (merged by k_walk_merge);
-// 72 bytes, so that the largest partial-sum region (20480 groups x 64 rays)
-// stays at 94 MB.
-struct alignas(8) Partial {
-    double a1, a2, g1, g2;
-    float k;
-    int32_t cnt[kCounts];
-};
-static_assert(sizeof(Partial) == 72, "partial-sum record size");
-
 // Byte offsets of the ray workspace pieces.
 struct RayLayout {
-    size_t k0, k1, v0, v1, xs, ys, hist, part, sbox, parts, bytes;
+    size_t k0, k1, v0, v1, xs, ys, hist, part, sbox, bytes;
     int split;
 };
 RayLayout ray_layout(int64_t nrays);
@@ -128,6 +108,23 @@ glm_status stage_rays(const double* rx, const double* ry, int64_t nrays, void* w
                       StagedRays* out, hipStream_t st);
 // The staged rays that stage_rays left in the workspace (no launch).
 StagedRays staged_rays_view(int64_t nrays, void* ws, const RayLayout& L);
+
+// Wavefronts that share one 64-ray group of a forward walk: a power of two, 1
+// to 16, so that about kGroupWaves wavefronts keep the chip busy.
+constexpr int64_t kGroupWaves = 8192;
+inline int walk_waves(int64_t nrays)
+{
+    const int64_t groups = (nrays + 63) / 64;
+    int w = 1;
+    while (w < 16 && w * groups < kGroupWaves) w *= 2;
+    return w;
+}
+
+// Whether a forward walk expands far boxes over its ray groups (farfield.hpp).
+// With fewer rays than this the groups of scattered rays are too wide to have
+// many far boxes, and a ray's result keeps not depending on its group.
+constexpr int64_t kFarRays = 65536;
+inline bool walk_far(int64_t nrays) { return nrays >= kFarRays; }
 
 // Index of the deepest box holding the rays' bounding box, written to the
 // workspace (computes the box unless stage_rays did).

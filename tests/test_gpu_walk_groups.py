@@ -1,0 +1,90 @@
+"""The forward walk at the launch sizes where it changes shape: the number of
+wavefronts that share a ray group (16 down to 1 as the launch grows), far
+boxes through the groups' local expansions (65,536 rays and more), ragged last
+groups, groups whose rays all sit at one point, and lists so long and ray groups
+so wide that a list pass takes its candidates ray by ray.  Against the FP64
+oracle tree: decision counts exactly, values to FP32 rounding (the bound of
+every tree test)."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_helpers import assert_matches_oracle_tree, build, dev, say, shoot
+
+pytestmark = pytest.mark.gpu
+
+
+def lens_of(n, seed):
+    lens = synth.gaussian_blobs(n, seed, s_lo=0.003, s_hi=0.2)
+    lens.s[synth.rng(seed + 1).random(n) < 0.2] = 0.0
+    return lens
+
+
+@pytest.mark.parametrize("nr", [1, 64, 65, 4097, 32_769, 65_535, 65_536, 131_073, 262_145, 524_225, 524_289])
+def test_walk_launch_sizes_match_oracle_tree(ora, nr):
+    lens = lens_of(3000, 601)
+    theta, leaf, order = 0.4, 8, 7
+    say(f"[gpu] walk of {nr} rays")
+    tree = build(lens, theta, leaf, order)
+    g0 = synth.rng(603 + nr)
+    # scattered rays, a dense patch (every box far from most of its groups), and 200 rays at one point
+    rx, ry = g0.uniform(-0.6, 0.6, nr), g0.uniform(-0.6, 0.6, nr)
+    k = nr // 2
+    rx[:k], ry[:k] = 0.11 + 0.01 * g0.random(k), -0.07 + 0.01 * g0.random(k)
+    if nr > 4000:
+        rx[k:k + 200], ry[k:k + 200] = 0.3, 0.2
+    T = ora.Tree(lens.x, lens.y, lens.m, lens.s, lens.q, theta, leaf, order)
+    idx = np.union1d(synth.sample_rays(rx, ry, 3000, 605), np.arange(k, min(nr, k + 70)))
+    idx = np.union1d(idx, np.arange(max(0, nr - 70), nr))
+    ref, rc = T.shoot(rx[idx], ry[idx], counts=True)
+    got = shoot(tree, rx, ry)[idx]
+    assert_matches_oracle_tree(got, ref)
+    withc, cnt = shoot(tree, rx, ry, counts=True)
+    np.testing.assert_array_equal(cnt[idx], rc[:, [0, 1, 2, 4]])
+    assert_matches_oracle_tree(withc[idx], ref)
+    ao = shoot(tree, rx, ry, alpha_only=True)[idx]
+    np.testing.assert_array_equal(ao, got[:, :2])
+    import paper_1312_1128_amd as g
+    import torch
+
+    o = g.shoot_potential(tree, dev(rx), dev(ry))
+    torch.cuda.synchronize()
+    psi, ref_psi = o["psi"].double().cpu().numpy()[idx], T.shoot_psi(rx[idx], ry[idx])
+    assert np.abs(psi - ref_psi).max() <= 2e-6 * np.abs(ref_psi).max()
+
+
+@pytest.mark.parametrize("order", range(13))
+def test_far_expansion_at_every_order(ora, order):
+    """70,000 rays in a small patch outside and inside the lens: most accepted
+    boxes go through the local expansion, at each multipole order, for Gaussians
+    and halos."""
+    lens = lens_of(1500, 611)
+    g0 = synth.rng(613)
+    rx, ry = 0.2 + 0.02 * g0.random(70_000), 0.1 + 0.02 * g0.random(70_000)
+    rx[:20_000] += 0.9
+    idx = np.arange(0, rx.size, 41)
+    say(f"[gpu] far expansion at order {order}")
+    T = ora.Tree(lens.x, lens.y, lens.m, lens.s, lens.q, 0.5, 4, order)
+    got = shoot(build(lens, 0.5, 4, order), rx, ry)[idx]
+    assert_matches_oracle_tree(got, T.shoot(rx[idx], ry[idx]))
+    import paper_1312_1128_amd as g
+
+    halos, c = synth.nfw_halo_field(800, 615)
+    tree = g.Tree().build(dev(halos.x), dev(halos.y), dev(halos.m), dev(halos.s), theta=0.5, q=c, leaf_size=4,
+                          order=order, nfw=True)
+    T = ora.Tree(halos.x, halos.y, halos.m, halos.s, c, 0.5, 4, order, nfw=True)
+    assert_matches_oracle_tree(shoot(tree, rx, ry)[idx], T.shoot(rx[idx], ry[idx]))
+
+
+def test_wide_groups_over_a_dense_core(ora):
+    """A few thousand scattered rays over a halo whose core is far denser than
+    the rays: lists of thousands of particles per group, each holding few rays."""
+    lens = synth.nfw_halo(40_000, 621)
+    rx, ry = synth.uniform_points(3001, 622)
+    say("[gpu] wide groups over a dense core")
+    tree = build(lens, 0.4, 8, 6)
+    T = ora.Tree(lens.x, lens.y, lens.m, lens.s, lens.q, 0.4, 8, 6)
+    ref, rc = T.shoot(rx, ry, counts=True)
+    got, cnt = shoot(tree, rx, ry, counts=True)
+    np.testing.assert_array_equal(cnt, rc[:, [0, 1, 2, 4]])
+    assert_matches_oracle_tree(got, ref)

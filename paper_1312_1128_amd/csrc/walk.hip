@@ -47,14 +47,25 @@ __global__ __launch_bounds__(kBlock) void k_ray_bbox(const double* __restrict__ 
         for (int k = 0; k < 4; ++k) part[blockIdx.x * 4 + k] = red[k][0];
 }
 
-__device__ inline uint32_t spread16(uint32_t v)
+// Position of cell (x, y) along the Hilbert curve over 2^bits x 2^bits cells
+// (quadrant by quadrant from the top: the curve's four quadrants in order,
+// then the frame of the one entered, transposed or turned).  64 rays in a row
+// along it always form one compact patch; along the Morton curve, which jumps,
+// a third of the groups of a grid that is not a power of two across straddled a
+// jump, and walking such a group costs several times a compact one: 837^2 rays
+// on 1e6 particles took 4.0 ms against 2.6 ms for the 1024^2 rays of an aligned grid.
+__device__ inline uint32_t hilbert_key(uint32_t x, uint32_t y, int bits)
 {
-    uint32_t x = v & 0xFFFFu;
-    x = (x | (x << 8)) & 0x00FF00FFu;
-    x = (x | (x << 4)) & 0x0F0F0F0Fu;
-    x = (x | (x << 2)) & 0x33333333u;
-    x = (x | (x << 1)) & 0x55555555u;
-    return x;
+    uint32_t d = 0;
+    for (int s = bits - 1; s >= 0; --s) {
+        const uint32_t rx = (x >> s) & 1u, ry = (y >> s) & 1u;
+        d = (d << 2) | ((3u * rx) ^ ry);
+        const uint32_t flip = (ry == 0u && rx != 0u) ? ~0u : 0u;
+        const uint32_t fx = x ^ flip, fy = y ^ flip;
+        x = ry == 0u ? fy : fx;
+        y = ry == 0u ? fx : fy;
+    }
+    return d;
 }
 
 // bounding box of the rays from the per-block partials
@@ -82,7 +93,7 @@ __global__ __launch_bounds__(kBlock) void k_ray_root(const double* __restrict__ 
     if (threadIdx.x < 4) bb[threadIdx.x] = red[threadIdx.x][0];
 }
 
-// Morton keys of the rays in their bounding square, `bits` (<= 16) per axis
+// Hilbert keys of the rays in their bounding square, `bits` (<= 16) per axis
 __global__ __launch_bounds__(kBlock) void k_ray_keys(const double* __restrict__ x, const double* __restrict__ y,
                                                     int64_t n, const double* __restrict__ bb, int bits,
                                                     uint32_t* __restrict__ key, uint32_t* __restrict__ val)
@@ -96,7 +107,7 @@ __global__ __launch_bounds__(kBlock) void k_ray_keys(const double* __restrict__ 
     const double sc = top / ext;
     const uint32_t qx = (uint32_t)fmin(fmax((x[i] - bx0) * sc, 0.0), top);
     const uint32_t qy = (uint32_t)fmin(fmax((y[i] - by0) * sc, 0.0), top);
-    key[i] = spread16(qx) | (spread16(qy) << 1);
+    key[i] = hilbert_key(qx, qy, bits);
     val[i] = (uint32_t)i;
 }
 
@@ -260,7 +271,7 @@ __device__ inline int find_lens(const int64_t* __restrict__ roff, int nlens, int
     return lo;
 }
 
-// key = lens rank << 32 | 16-bit-per-axis Morton code in the lens's ray box
+// key = lens rank << 2 bits | Hilbert key in the lens's ray box
 __global__ __launch_bounds__(kBlock) void k_batch_keys(const BatchLens* __restrict__ lenses, int nlens,
                                                       const int64_t* __restrict__ roff, const double* __restrict__ bb,
                                                       int64_t total, int bits, uint64_t* __restrict__ key,
@@ -277,7 +288,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_keys(const BatchLens* __restri
     const double sc = top / ext;
     const uint32_t qx = (uint32_t)fmin(fmax((lenses[l].rx[i] - bx0) * sc, 0.0), top);
     const uint32_t qy = (uint32_t)fmin(fmax((lenses[l].ry[i] - by0) * sc, 0.0), top);
-    key[gi] = ((uint64_t)l << (2 * bits)) | (uint64_t)(spread16(qx) | (spread16(qy) << 1));
+    key[gi] = ((uint64_t)l << (2 * bits)) | (uint64_t)hilbert_key(qx, qy, bits);
     val[gi] = (uint32_t)gi;
 }
 
@@ -364,7 +375,7 @@ glm_status shoot_batched_device(const BatchLens* host_table, int nlens, int orde
     hipLaunchKernelGGL(k_batch_bbox, dim3(nlens, kBboxSplit), dim3(kBlock), 0, st, dtab, bbpart);
     hipLaunchKernelGGL(k_batch_bbox_final, dim3(ceil_div(4 * nlens, 64)), dim3(64), 0, st, bbpart, nlens, bb);
     const int g = ceil_div(total, kBlock);
-    // per lens, about four Morton cells per ray (the largest lens sets the width)
+    // per lens, about four cells per ray (the largest lens sets the width)
     int64_t most = 0;
     for (int l = 0; l < nlens; ++l) most = std::max(most, host_table[l].nrays);
     int bits = 8;
@@ -415,7 +426,7 @@ glm_status shoot_device(const TreeStorage& ts, const double* rx, const double* r
         glm_status rc = stage_rays(rx, ry, nrays, ws, L, &sr, st);
         if (rc != GLM_OK) return rc;
     }
-    const WalkArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, WalkOut{a1, a2, k, g1, g2, counts}, walk_waves(nrays), walk_far(nrays), st};
+    const WalkArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, WalkOut{a1, a2, k, g1, g2, counts}, walk_shape(nrays, ts.n), walk_far(nrays), st};
     const bool aonly = (flags & GLM_ALPHA_ONLY) != 0;
     // counts requested: the product walk with counters; else the product or the plain-FP32 walk
     if (counts) launch_walk_counts(a, aonly);
@@ -439,7 +450,7 @@ glm_status potential_device(const TreeStorage& ts, const double* rx, const doubl
     WalkOut out{a1, a2, nullptr, nullptr, nullptr, nullptr};
     out.psi = psi;
     out.td = td;
-    launch_walk_potential(WalkArgs{ts.dev, sr.xs, sr.ys, sr.perm, nrays, out, walk_waves(nrays), walk_far(nrays), st});
+    launch_walk_potential(WalkArgs{ts.dev, sr.xs, sr.ys, sr.perm, nrays, out, walk_shape(nrays, ts.n), walk_far(nrays), st});
     GLM_HIP(hipGetLastError());
     return GLM_OK;
 }

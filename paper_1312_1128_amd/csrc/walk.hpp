@@ -102,22 +102,38 @@ struct StagedRays {
     const uint32_t* perm; // sorted -> input position, or null when unsorted
 };
 
-// Morton-sort the rays (8 to 16 bits per axis in their bounding square) so that
+// Sort the rays along a Hilbert curve (8 to 16 bits per axis in their bounding square) so that
 // each 64-ray group is spatially compact.
 glm_status stage_rays(const double* rx, const double* ry, int64_t nrays, void* ws, const RayLayout& L,
                       StagedRays* out, hipStream_t st);
 // The staged rays that stage_rays left in the workspace (no launch).
 StagedRays staged_rays_view(int64_t nrays, void* ws, const RayLayout& L);
 
-// Wavefronts that share one 64-ray group of a forward walk: a power of two, 1
-// to 16, so that about kGroupWaves wavefronts keep the chip busy.
-constexpr int64_t kGroupWaves = 8192;
-inline int walk_waves(int64_t nrays)
+// Rays per group (64 down to 4) and wavefronts that share a group (1 to 16, a
+// power of two) of a forward walk.
+//  - Few rays: a group of 64 scattered rays covers much of the lens and needs
+//    nearly everything that any of them needs, while most of the chip idles;
+//    groups of fewer rays (the other lanes idle) need less each.  1,024 rays on
+//    1e6 particles: 3.65 ms in 16 groups of 64, 0.39 ms in 256 of 4.  With 256
+//    groups the halving stops paying for small trees (4,096 rays on 1e4
+//    particles: 0.18 ms, with 512 groups 0.23), with 512 for large ones (1e6
+//    particles: 0.97 and 0.76).
+//  - Wavefronts: about 8,192 fill the chip.  Groups over a large tree differ more in
+//    cost, so it takes twice as many (262,144 rays on 1e6 particles: 2.45 ms
+//    with 8,192, 1.83 with 16,384; on 1e4 particles 0.47 and 0.51).
+constexpr int kMaxGroupRays = 64;
+struct WalkShape {
+    int rays, waves;
+};
+inline WalkShape walk_shape(int64_t nrays, int64_t n)
 {
-    const int64_t groups = (nrays + 63) / 64;
-    int w = 1;
-    while (w < 16 && w * groups < kGroupWaves) w *= 2;
-    return w;
+    const bool large = n >= 65536;
+    const int64_t min_groups = large ? 512 : 256, fill = large ? 16384 : 8192;
+    WalkShape s{kMaxGroupRays, 1};
+    while (s.rays > 4 && nrays < min_groups * s.rays) s.rays /= 2;
+    const int64_t groups = (nrays + s.rays - 1) / s.rays;
+    while (s.waves < 16 && s.waves * groups < fill) s.waves *= 2;
+    return s;
 }
 
 // Whether a forward walk expands far boxes over its ray groups (farfield.hpp).

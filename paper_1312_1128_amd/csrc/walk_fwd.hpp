@@ -171,13 +171,13 @@ constexpr size_t walk_coop_lds(int W)
     return coop_lds_bytes(W) > sums ? coop_lds_bytes(W) : sums;
 }
 
-// W = blockDim.x / 64 wavefronts per ray group; their sums meet in wavefront
+// W = blockDim.x / 64 wavefronts per group of `rays` (up to 64) rays; their sums meet in wavefront
 // order in LDS.
 template <int P, bool AONLY, int MODE, bool PSI, int KIND>
 __global__ __launch_bounds__(kWave* kMaxGroupWaves) void k_walk_coop(TreeDev T, const double* __restrict__ rxs,
                                                                     const double* __restrict__ rys,
                                                                     const uint32_t* __restrict__ rperm, int64_t nrays,
-                                                                    WalkOut out, int far)
+                                                                    WalkOut out, int rays, int far)
 {
     extern __shared__ __align__(16) char lds[];
     constexpr bool STATS = MODE == 1;
@@ -185,9 +185,9 @@ __global__ __launch_bounds__(kWave* kMaxGroupWaves) void k_walk_coop(TreeDev T, 
     const int lane = threadIdx.x & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), W = blockDim.x / kWave;
     int64_t grp;
-    if (!group_task(blockIdx.x, (nrays + kWave - 1) / kWave, &grp)) return; // (whole workgroups)
-    const int64_t r = grp * kWave + lane;
-    const bool valid = r < nrays;
+    if (!group_task(blockIdx.x, (nrays + rays - 1) / rays, &grp)) return; // (whole workgroups)
+    const int64_t r = grp * rays + lane;
+    const bool valid = lane < rays && r < nrays;
     const double X = valid ? rxs[r] : 0.0, Y = valid ? rys[r] : 0.0;
     const RayGroup g = ray_group(X, Y, valid, far != 0 && MODE != 2);
     FwdVisitor<P, AONLY, MODE, PSI, KIND> v(T, g, X, Y, lane, valid);
@@ -236,7 +236,7 @@ struct WalkArgs {
     const uint32_t* rperm;
     int64_t nrays;
     WalkOut out;
-    int waves; // wavefronts per ray group (1: k_walk)
+    WalkShape shape;
     bool far;  // expand far boxes over the groups
     hipStream_t st;
 };
@@ -244,17 +244,17 @@ struct WalkArgs {
 template <int P, bool AONLY, int MODE, bool PSI, int KIND>
 void launch_walk_kind(const WalkArgs& a)
 {
-    const dim3 g((unsigned)group_grid((a.nrays + kWave - 1) / kWave));
+    const dim3 g((unsigned)group_grid((a.nrays + a.shape.rays - 1) / a.shape.rays));
     if constexpr (MODE == 0) {
-        if (a.waves == 1) {
+        if (a.shape.waves == 1) {
             hipLaunchKernelGGL((k_walk<P, AONLY, PSI, KIND>), g, dim3(kWave), 0, a.st, a.T, a.rxs, a.rys, a.rperm,
                                a.nrays, a.out);
             return;
         }
     }
-    hipLaunchKernelGGL((k_walk_coop<P, AONLY, MODE, PSI, KIND>), g, dim3(kWave * a.waves),
-                       (walk_coop_lds<AONLY, PSI, MODE == 1>(a.waves)), a.st, a.T, a.rxs, a.rys, a.rperm, a.nrays,
-                       a.out, a.far ? 1 : 0);
+    hipLaunchKernelGGL((k_walk_coop<P, AONLY, MODE, PSI, KIND>), g, dim3(kWave * a.shape.waves),
+                       (walk_coop_lds<AONLY, PSI, MODE == 1>(a.shape.waves)), a.st, a.T, a.rxs, a.rys, a.rperm, a.nrays,
+                       a.out, a.shape.rays, a.far ? 1 : 0);
 }
 
 template <bool AONLY, int MODE, bool PSI>

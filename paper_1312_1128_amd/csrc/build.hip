@@ -18,6 +18,7 @@
 
 #include "build.hpp"
 #include "eval.hpp"
+#include "lanesum.hpp"
 
 namespace glm {
 

@@ -632,17 +632,4 @@ __device__ inline bool group_task(int b, int64_t groups, int64_t* group)
     return *group < groups;
 }
 
-__device__ inline double wave_min(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-__device__ inline double wave_max(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
 } // namespace glm

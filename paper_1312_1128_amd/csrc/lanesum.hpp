@@ -182,4 +182,33 @@ __device__ inline double word_totals64(const float* a)
     return c[0];
 }
 
+// Smallest, largest value and sum over the wavefront, in every lane (butterfly
+// exchanges in registers: pairs 32, 16, 8, 4, 2, 1 lanes apart).
+template <class Op>
+__device__ inline double wave_all(double v, Op op)
+{
+    auto l = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(v), (uint32_t)__double2loint(v), false, false);
+    auto h = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(v), (uint32_t)__double2hiint(v), false, false);
+    v = op(lane_pair(l[0], h[0]), lane_pair(l[1], h[1]));
+    l = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(v), (uint32_t)__double2loint(v), false, false);
+    h = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(v), (uint32_t)__double2hiint(v), false, false);
+    v = op(lane_pair(l[0], h[0]), lane_pair(l[1], h[1]));
+    v = op(v, row_peer64<kRowStep[0]>(v));
+    v = op(v, row_peer64<kRowStep[1]>(v));
+    v = op(v, row_peer64<kRowStep[2]>(v));
+    return op(v, row_peer64<kRowStep[3]>(v));
+}
+__device__ inline double wave_min(double v)
+{
+    return wave_all(v, [](double a, double b) { return fmin(a, b); });
+}
+__device__ inline double wave_max(double v)
+{
+    return wave_all(v, [](double a, double b) { return fmax(a, b); });
+}
+__device__ inline double wave_sum(double v)
+{
+    return wave_all(v, [](double a, double b) { return a + b; });
+}
+
 } // namespace glm

@@ -55,8 +55,8 @@ struct TravLds {
     uint64_t* qm;   // three queues of `qcap` masks: accepted boxes, open leaves, lists
     int* stkb;
     int* qb;        // the queues' boxes
-    int* cnt;       // 4 x kMaxGroupWaves item counts of a round
-    int* fq;        // this wavefront's far boxes
+    int* cnt;       // 3 x kMaxGroupWaves item counts of a round
+    int* fq;        // far boxes
     int cap, qcap;
 };
 
@@ -69,7 +69,7 @@ __host__ __device__ constexpr int coop_queue(int W)
 __host__ __device__ constexpr size_t solo_lds_bytes() { return 12ull * kSoloStack + 4ull * kFarQueue; }
 __host__ __device__ constexpr size_t coop_lds_bytes(int W)
 {
-    return 12ull * coop_stack(W) + 36ull * coop_queue(W) + 16ull * kMaxGroupWaves + 4ull * kFarQueue * W;
+    return 12ull * coop_stack(W) + 40ull * coop_queue(W) + 16ull * kMaxGroupWaves + 4ull * kWave;
 }
 
 __device__ inline TravLds solo_lds(char* base)
@@ -82,7 +82,7 @@ __device__ inline TravLds solo_lds(char* base)
     return L;
 }
 
-__device__ inline TravLds coop_lds(char* base, int w, int W)
+__device__ inline TravLds coop_lds(char* base, int W)
 {
     TravLds L;
     L.cap = coop_stack(W);
@@ -92,7 +92,7 @@ __device__ inline TravLds coop_lds(char* base, int w, int W)
     L.stkb = reinterpret_cast<int*>(L.qm + 3 * L.qcap);
     L.qb = L.stkb + L.cap;
     L.cnt = L.qb + 3 * L.qcap;
-    L.fq = L.cnt + 4 * kMaxGroupWaves + w * kFarQueue;
+    L.fq = L.cnt + 4 * kMaxGroupWaves; // one round's boxes after fewer than 64 left over
     return L;
 }
 
@@ -144,7 +144,7 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
     int rot = 0; // which wavefront takes the next queue item
     int nf = 0;  // far boxes queued
     while (top > 0) {
-        if constexpr (V::farfield)
+        if constexpr (V::farfield && !COOP)
             if (nf >= kWave) {
                 nf -= kWave;
                 v.far(L.fq[nf + lane], true);
@@ -170,8 +170,10 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
         if constexpr (V::farfield) {
             fa = all && m == g.full && is_far(g, h, T.theta);
             const uint64_t fb = __ballot(fa);
-            if (fa) L.fq[nf + rank_in(fb)] = c;
-            nf += __popcll(fb);
+            if constexpr (!COOP) {
+                if (fa) L.fq[nf + rank_in(fb)] = c;
+                nf += __popcll(fb);
+            }
             if constexpr (V::stats) v.accepted(__popcll(fb));
         }
         if constexpr (V::stats) v.visited(__popcll(__ballot(has && m == g.full)));
@@ -238,15 +240,18 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
         }
         int at = top; // where this wavefront's children go
         if constexpr (COOP) {
-            const uint64_t qa[3] = {__ballot(am != 0 && !fa), __ballot(opl), __ballot(lr)};
+            const uint64_t qa[4] = {__ballot(am != 0 && !fa), __ballot(opl), __ballot(lr), __ballot(fa)};
+            // counts of this wavefront, two to a word (a round's are below 2^16)
+            const int pk[2] = {(int)(__popcll(qa[0]) | (__popcll(qa[1]) << 16)),
+                               (int)(__popcll(qa[2]) | (__popcll(qa[3]) << 16))};
             if (lane == 0) {
                 L.cnt[w] = nk;
-#pragma unroll
-                for (int q = 0; q < 3; ++q) L.cnt[(q + 1) * kMaxGroupWaves + w] = __popcll(qa[q]);
+                L.cnt[kMaxGroupWaves + w] = pk[0];
+                L.cnt[2 * kMaxGroupWaves + w] = pk[1];
             }
             __syncthreads();
-            // lane 16 q + u: count q of wavefront u; inclusive sums along each row of 16
-            int cv = (lane & 15) < W ? L.cnt[lane] : 0;
+            // lane 16 q + u: word q of wavefront u; inclusive sums along each row of 16
+            int cv = (lane & 15) < W && lane < 3 * kMaxGroupWaves ? L.cnt[lane] : 0;
 #pragma unroll
             for (int o = 1; o < kMaxGroupWaves; o <<= 1) {
                 const int t = __shfl_up(cv, o, kMaxGroupWaves);
@@ -254,16 +259,20 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
             }
             at += __builtin_amdgcn_readlane(cv, w) - nk;
             top += __builtin_amdgcn_readlane(cv, 15);
-            int qn[3];
+            int qn[4];
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int me = __popcll(qa[q]);
-                const int off = __builtin_amdgcn_readlane(cv, 16 * (q + 1) + w) - me;
-                qn[q] = __builtin_amdgcn_readlane(cv, 16 * (q + 1) + 15);
+            for (int q = 0; q < 4; ++q) {
+                const int word = q >> 1, sh = 16 * (q & 1);
+                const int off = ((__builtin_amdgcn_readlane(cv, 16 * (word + 1) + w) - pk[word]) >> sh) & 0xffff;
+                qn[q] = (__builtin_amdgcn_readlane(cv, 16 * (word + 1) + 15) >> sh) & 0xffff;
                 if (lane_bit(qa[q])) {
-                    const int p = q * L.qcap + off + rank_in(qa[q]);
-                    L.qb[p] = c;
-                    L.qm[p] = q == 0 ? am : (q == 1 ? om : m);
+                    if (q == 3) {
+                        L.fq[nf + off + rank_in(qa[q])] = c;
+                    } else {
+                        const int p = q * L.qcap + off + rank_in(qa[q]);
+                        L.qb[p] = c;
+                        L.qm[p] = q == 0 ? am : (q == 1 ? om : m);
+                    }
                 }
             }
 #pragma unroll
@@ -276,7 +285,15 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
                 at += __popcll(kb[u]);
             }
             __syncthreads();
-            // the round's work, dealt item by item (W is a power of two)
+            // the round's work, dealt item by item (W is a power of two); far
+            // boxes 64 at a time, the rest wait for the next round
+            if constexpr (V::farfield) {
+                nf += qn[3];
+                while (nf >= kWave) {
+                    nf -= kWave;
+                    if (((w - rot++) & (W - 1)) == 0) v.far(L.fq[nf + lane], true);
+                }
+            }
             for (int i = (w - rot) & (W - 1); i < qn[0]; i += W) {
                 const int ck = __builtin_amdgcn_readfirstlane(L.qb[i]);
                 const bool acc = lane_bit(uniform64(L.qm[i]));
@@ -311,12 +328,14 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
             top = at;
         }
     }
-    if constexpr (V::farfield)
-        while (nf > 0) { // at most two passes are left
+    if constexpr (V::farfield) {
+        if (COOP && ((w - rot) & (W - 1)) != 0) return; // (fewer than 64 left: one wavefront's pass)
+        while (nf > 0) {
             const int n = nf < kWave ? nf : kWave;
             nf -= n;
             v.far(lane < n ? L.fq[nf + lane] : 0, lane < n);
         }
+    }
 }
 
 } // namespace glm

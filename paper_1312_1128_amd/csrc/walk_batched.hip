@@ -38,8 +38,13 @@ __global__ __launch_bounds__(kBlock) void k_walk_batched(const BatchLens* __rest
         const RayGroup g = ray_group(X, Y, valid, MODE != 2);
         FwdVisitor<P, AONLY, MODE, false, KIND> v(B.tree, g, X, Y, lane, valid);
         traverse<false>(B.tree, v, g, X, Y, lane, 0, 1, L);
-        v.finish(reinterpret_cast<double*>(L.stkm));
-        wave_lds_sync(); // the next item's stack overwrites the words
+        if (g.far) {
+            double* words = reinterpret_cast<double*>(L.stkm);
+            v.put_words(words);
+            wave_lds_sync();
+            v.finish(words);
+            wave_lds_sync(); // the next item's stack overwrites the words
+        }
         if (valid) write_out<AONLY, false>(v.A, v.cnt, (int64_t)perm[gi] - B.ray_off, B.out);
     }
 }

@@ -49,22 +49,18 @@ struct FwdVisitor {
         if constexpr (PSI) fpsi += (double)p0;
     }
 
-    // The local expansion at the rays; `words`: kFarWords doubles of LDS of
-    // this wavefront, free after the traversal.
-    __device__ void finish(double* words)
+    // This lane's word of the local expansion into `words` (kFarWords doubles of LDS).
+    __device__ void put_words(double* words) const
     {
-        if constexpr (farfield) {
-            if (!g.far) return;
-            const int slot = word_slot<kFarWords>(lane);
-            if (slot >= 0) words[slot] = fsum;
-            wave_lds_sync();
-            far_eval<AONLY, PSI>(g, words, X, Y, A);
-            if constexpr (PSI) {
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) fpsi += __shfl_xor(fpsi, o, kWave);
-                A.ps += fpsi;
-            }
-        }
+        const int slot = word_slot<kFarWords>(lane);
+        if (slot >= 0) words[slot] = fsum;
+    }
+
+    // The local expansion at the rays.
+    __device__ void finish(const double* words)
+    {
+        far_eval<AONLY, PSI>(g, words, X, Y, A);
+        if constexpr (PSI) A.ps += wave_sum(fpsi);
     }
 
     __device__ void box(int c, bool acc, double w1, double w2)
@@ -155,7 +151,12 @@ __global__ __launch_bounds__(kWave) void k_walk(TreeDev T, const double* __restr
     const RayGroup g = ray_group(X, Y, valid, true);
     FwdVisitor<P, AONLY, 0, PSI, KIND> v(T, g, X, Y, lane, valid);
     traverse<false>(T, v, g, X, Y, lane, 0, 1, solo_lds(lds));
-    v.finish(reinterpret_cast<double*>(lds));
+    if (g.far) {
+        double* words = reinterpret_cast<double*>(lds);
+        v.put_words(words);
+        wave_lds_sync();
+        v.finish(words);
+    }
     if (valid) write_out<AONLY, false, PSI>(v.A, v.cnt, rperm ? (int64_t)rperm[r] : r, out);
 }
 
@@ -191,12 +192,26 @@ __global__ __launch_bounds__(kWave* kMaxGroupWaves) void k_walk_coop(TreeDev T, 
     const double X = valid ? rxs[r] : 0.0, Y = valid ? rys[r] : 0.0;
     const RayGroup g = ray_group(X, Y, valid, far != 0 && MODE != 2);
     FwdVisitor<P, AONLY, MODE, PSI, KIND> v(T, g, X, Y, lane, valid);
-    const TravLds L = coop_lds(lds, w, W);
-    traverse<true>(T, v, g, X, Y, lane, w, W, L);
-    v.finish(reinterpret_cast<double*>(L.fq));
+    traverse<true>(T, v, g, X, Y, lane, w, W, coop_lds(lds, W));
     Acc& A = v.A;
     __syncthreads(); // the traversal's LDS is free
     double* sums = reinterpret_cast<double*>(lds);
+    if (MODE != 2 && g.far) { // the wavefronts' local expansions, summed into one
+        v.put_words(sums + w * kFarWords);
+        __syncthreads();
+        if (w == 0) {
+            double t = 0.0;
+            if (lane < kFarWords)
+                for (int u = 0; u < W; ++u) t += sums[u * kFarWords + lane];
+            wave_lds_sync();
+            if (lane < kFarWords) sums[lane] = t;
+            wave_lds_sync();
+            v.finish(sums);
+        } else if constexpr (PSI) {
+            A.ps += wave_sum(v.fpsi);
+        }
+        __syncthreads();
+    }
     int* csum = reinterpret_cast<int*>(sums + (size_t)(W - 1) * NW * kWave);
     if (w > 0) {
         double* p = sums + (size_t)(w - 1) * NW * kWave + lane;

@@ -109,6 +109,24 @@ __device__ __forceinline__ E uniform_ld(const E* p, int64_t i)
     return __builtin_bit_cast(E, v);
 }
 
+// Waits for wave-uniform data that uniform_ld loads started, and only then
+// lets the load that `next` indexes start (the address passes through after
+// the data).  Scalar loads return in any order, so waiting for one waits for
+// all in flight: a loop that settles an item, starts the next one's loads and
+// then works on the item keeps one item's loads in flight behind the work.
+template <class E>
+__device__ __forceinline__ void settle(E& v, int& next)
+{
+    static_assert(sizeof(E) % 4 == 0, "whole 32-bit words");
+    struct Words {
+        uint32_t w[sizeof(E) / 4];
+    } q = __builtin_bit_cast(Words, v);
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(E) / 4); ++k) asm volatile("" : "+s"(q.w[k]));
+    v = __builtin_bit_cast(E, q);
+    asm volatile("" : "+s"(next));
+}
+
 // ---------------------------------------------------------------------------
 // host-side error plumbing
 // ---------------------------------------------------------------------------

@@ -453,10 +453,17 @@ __device__ inline void list_particle(const PRec& pr, double X, double Y, Acc& A,
 //   alpha1 - i alpha2 = v B(t),  gamma1 - i gamma2 = -v^2 (B(t) + t B'(t)),
 // v = 1/w, t = r_cm v, B(t) = M P(t) = M + sum_{k>=2} (M Qn_k) t^k with
 // Qn_k = Q_k / (M r_cm^k); the record holds M, r_cm and M Qn_k = Q_k / r_cm^k.
+// A box's moment record, wave-uniform.
+template <int P>
+struct BoxMoments {
+    float v[mom_stride(P)];
+};
+
 template <int P, bool AONLY, bool F64A, bool PSI = false>
-__device__ inline void eval_box(const float* __restrict__ mo, double w1, double w2, Acc& A)
+__device__ inline void eval_box(const BoxMoments<P>& mom, double w1, double w2, Acc& A)
 {
-    const float M = uniform_ld(mo, 0), rcm = uniform_ld(mo, 1);
+    const float* mo = mom.v;
+    const float M = mo[0], rcm = mo[1];
     const float f1 = (float)w1, f2 = (float)w2;
     const float inv = __builtin_amdgcn_rcpf(fmaf(f1, f1, f2 * f2));
     const float v1 = f1 * inv, v2 = -f2 * inv;
@@ -465,14 +472,14 @@ __device__ inline void eval_box(const float* __restrict__ mo, double w1, double 
     // each complex multiply-add as two FMAs per component
     float b1 = M, b2 = 0.0f, c1 = 0.0f, c2 = 0.0f;
     if constexpr (P >= 2) {
-        b1 = uniform_ld(mo, 2 + 2 * (P - 2));
-        b2 = uniform_ld(mo, 3 + 2 * (P - 2));
+        b1 = mo[2 + 2 * (P - 2)];
+        b2 = mo[3 + 2 * (P - 2)];
         c1 = b1; // first step: c = 0 * t + b
         c2 = b2;
 #pragma unroll
         for (int k = P - 1; k >= 0; --k) {
-            const float q1 = k >= 2 ? uniform_ld(mo, 2 + 2 * (k - 2)) : (k == 0 ? M : 0.0f);
-            const float q2 = k >= 2 ? uniform_ld(mo, 3 + 2 * (k - 2)) : 0.0f;
+            const float q1 = k >= 2 ? mo[2 + 2 * (k - 2)] : (k == 0 ? M : 0.0f);
+            const float q2 = k >= 2 ? mo[3 + 2 * (k - 2)] : 0.0f;
             const float n1 = fmaf(b1, t1, fmaf(-b2, t2, q1));
             const float n2 = fmaf(b1, t2, fmaf(b2, t1, q2));
             b1 = n1;
@@ -505,8 +512,8 @@ __device__ inline void eval_box(const float* __restrict__ mo, double w1, double 
             float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
             for (int k = P; k >= 2; --k) {
-                const float q1 = uniform_ld(mo, 2 + 2 * (k - 2)) * (1.0f / (float)k);
-                const float q2 = uniform_ld(mo, 3 + 2 * (k - 2)) * (1.0f / (float)k);
+                const float q1 = mo[2 + 2 * (k - 2)] * (1.0f / (float)k);
+                const float q2 = mo[3 + 2 * (k - 2)] * (1.0f / (float)k);
                 const float n1 = fmaf(s1, t1, fmaf(-s2, t2, q1)), n2 = fmaf(s1, t2, fmaf(s2, t1, q2));
                 s1 = n1;
                 s2 = n2;

@@ -90,60 +90,76 @@ __device__ inline FarOffset far_offset(const TreeDev& T, const RayGroup& g, int 
     return o;
 }
 
-// The words L_0 .. L_kFarOrder (Re, Im) of the lane's box, and with PSI the
-// real part of its complex potential at the group's centre,
-// M ln|w0| - Re sum_{k>=2} u_k / k.
-template <int P, bool PSI>
-__device__ inline void far_words(const TreeDev& T, const RayGroup& g, int c, bool active, float* L, float* psi0)
-{
-    const FarOffset o = far_offset(T, g, c, active);
-    constexpr int ST = mom_stride(P);
-    float mo[ST];
-    const float4* mp = reinterpret_cast<const float4*>(T.mom + (size_t)c * ST);
+// One far box per lane: u_k and the running factor v e^j of its words.
+template <int P>
+struct FarBox {
+    float M, r2;
+    float u1[P + 1], u2[P + 1]; // u_k, k = 2 .. P
+    float p1, p2;               // v e^j, j the next word
+    float e1, e2;
+
+    __device__ void load(const TreeDev& T, const RayGroup& g, int c, bool active)
+    {
+        const FarOffset o = far_offset(T, g, c, active);
+        constexpr int ST = mom_stride(P);
+        float mo[ST];
+        const float4* mp = reinterpret_cast<const float4*>(T.mom + (size_t)c * ST);
 #pragma unroll
-    for (int i = 0; i < ST / 4; ++i) {
-        const float4 q = mp[i];
-        mo[4 * i] = q.x;
-        mo[4 * i + 1] = q.y;
-        mo[4 * i + 2] = q.z;
-        mo[4 * i + 3] = q.w;
-    }
-    const float M = mo[0], t1 = mo[1] * o.v1, t2 = mo[1] * o.v2;
-    float u1[P + 1], u2[P + 1];
-    float p1 = t1, p2 = t2;
+        for (int i = 0; i < ST / 4; ++i) {
+            const float4 q = mp[i];
+            mo[4 * i] = q.x;
+            mo[4 * i + 1] = q.y;
+            mo[4 * i + 2] = q.z;
+            mo[4 * i + 3] = q.w;
+        }
+        M = mo[0];
+        r2 = o.r2;
+        const float t1 = mo[1] * o.v1, t2 = mo[1] * o.v2;
+        float q1 = t1, q2 = t2;
 #pragma unroll
-    for (int k = 2; k <= P; ++k) {
-        const float n1 = fmaf(p1, t1, -p2 * t2), n2 = fmaf(p1, t2, p2 * t1);
-        p1 = n1;
-        p2 = n2;
-        const float q1 = mo[2 + 2 * (k - 2)], q2 = mo[3 + 2 * (k - 2)];
-        u1[k] = fmaf(q1, p1, -q2 * p2);
-        u2[k] = fmaf(q1, p2, q2 * p1);
+        for (int k = 2; k <= P; ++k) {
+            const float n1 = fmaf(q1, t1, -q2 * t2), n2 = fmaf(q1, t2, q2 * t1);
+            q1 = n1;
+            q2 = n2;
+            const float a1 = mo[2 + 2 * (k - 2)], a2 = mo[3 + 2 * (k - 2)];
+            u1[k] = fmaf(a1, q1, -a2 * q2);
+            u2[k] = fmaf(a1, q2, a2 * q1);
+        }
+        p1 = o.v1;
+        p2 = o.v2;
+        e1 = -g.a * o.v1;
+        e2 = -g.a * o.v2;
     }
-    if constexpr (PSI) {
+
+    // Real part of the box's complex potential at the group's centre.
+    __device__ float psi0(bool active) const
+    {
         float re = 0.0f;
 #pragma unroll
         for (int k = P; k >= 2; --k) re = fmaf(u1[k], 1.0f / (float)k, re);
-        *psi0 = active ? fmaf(0.5f * M, __logf(o.r2), -re) : 0.0f;
+        return active ? fmaf(0.5f * M, __logf(r2), -re) : 0.0f;
     }
-    const float e1 = -g.a * o.v1, e2 = -g.a * o.v2;
-    p1 = o.v1;
-    p2 = o.v2;
+
+    // The words L_J0 .. L_(J0 + kFarOrder / 2) (Re, Im); J0 = 0 first, then the other half.
+    template <int J0>
+    __device__ void words(float* L)
+    {
 #pragma unroll
-    for (int j = 0; j <= kFarOrder; ++j) {
-        float s1 = M, s2 = 0.0f;
+        for (int j = J0; j <= J0 + kFarOrder / 2; ++j) {
+            float s1 = M, s2 = 0.0f;
 #pragma unroll
-        for (int k = 2; k <= P; ++k) {
-            s1 = fmaf(far_binomial(k, j), u1[k], s1);
-            s2 = fmaf(far_binomial(k, j), u2[k], s2);
+            for (int k = 2; k <= P; ++k) {
+                s1 = fmaf(far_binomial(k, j), u1[k], s1);
+                s2 = fmaf(far_binomial(k, j), u2[k], s2);
+            }
+            L[2 * (j - J0)] = fmaf(p1, s1, -p2 * s2);
+            L[2 * (j - J0) + 1] = fmaf(p1, s2, p2 * s1);
+            const float n1 = fmaf(p1, e1, -p2 * e2), n2 = fmaf(p1, e2, p2 * e1);
+            p1 = n1;
+            p2 = n2;
         }
-        L[2 * j] = fmaf(p1, s1, -p2 * s2);
-        L[2 * j + 1] = fmaf(p1, s2, p2 * s1);
-        const float n1 = fmaf(p1, e1, -p2 * e2), n2 = fmaf(p1, e2, p2 * e1);
-        p1 = n1;
-        p2 = n2;
     }
-}
+};
 
 // The group's local expansion at this lane's ray (L: the FP64 words in LDS),
 // added to its sums.  L_0 and L_1, the field and its derivative at the centre,

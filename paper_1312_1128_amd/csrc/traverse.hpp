@@ -9,7 +9,7 @@
 // rays.  The bounding-box distances round monotonically (the same FP64
 // operations as the per-ray test, no contraction), so the decisions are
 // exactly those of a per-ray walk.  The boxes' work then goes to a visitor:
-//   box(c, acc, w1, w2)      rays `acc` accept box c (offset w per ray)
+//   box(b, c, acc, w1, w2)   rays `acc` accept box c (b = load(c), offset w per ray)
 //   leaf(pbeg, pend, opn)    rays `opn` sum these particles
 //   list(lbeg, lend, act)    rays `act` check these big-particle list entries
 // with wave-uniform arguments and lanes as rays.  A box that every ray of the
@@ -54,7 +54,8 @@ struct TravLds {
     uint64_t* stkm;
     uint64_t* qm;   // three queues of `qcap` masks: accepted boxes, open leaves, lists
     int* stkb;
-    int* qb;        // the queues' boxes
+    int* qb;        // the queues' boxes, or first particles or entries
+    int* qe;        // the last two queues' ends of those
     int* cnt;       // 3 x kMaxGroupWaves item counts of a round
     int* fq;        // far boxes
     int cap, qcap;
@@ -69,7 +70,7 @@ __host__ __device__ constexpr int coop_queue(int W)
 __host__ __device__ constexpr size_t solo_lds_bytes() { return 12ull * kSoloStack + 4ull * kFarQueue; }
 __host__ __device__ constexpr size_t coop_lds_bytes(int W)
 {
-    return 12ull * coop_stack(W) + 40ull * coop_queue(W) + 16ull * kMaxGroupWaves + 4ull * kWave;
+    return 12ull * coop_stack(W) + 48ull * coop_queue(W) + 16ull * kMaxGroupWaves + 4ull * kWave;
 }
 
 __device__ inline TravLds solo_lds(char* base)
@@ -91,7 +92,8 @@ __device__ inline TravLds coop_lds(char* base, int W)
     L.qm = L.stkm + L.cap;
     L.stkb = reinterpret_cast<int*>(L.qm + 3 * L.qcap);
     L.qb = L.stkb + L.cap;
-    L.cnt = L.qb + 3 * L.qcap;
+    L.qe = L.qb + 3 * L.qcap;
+    L.cnt = L.qe + 2 * L.qcap;
     L.fq = L.cnt + 4 * kMaxGroupWaves; // one round's boxes after fewer than 64 left over
     return L;
 }
@@ -101,6 +103,11 @@ __device__ inline uint64_t readlane64(uint64_t v, int k)
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, k);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), k);
     return ((uint64_t)hi << 32) | lo;
+}
+__device__ inline double readlane_f64(double v, int k)
+{
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), k), hi = __builtin_amdgcn_readlane(__double2hiint(v), k);
+    return __hiloint2double(hi, lo);
 }
 __device__ inline uint64_t uniform64(uint64_t v)
 {
@@ -115,6 +122,13 @@ __device__ inline int rank_in(uint64_t m)
 }
 // this lane's bit of a wave-uniform mask
 __device__ inline bool lane_bit(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// A box's header and what its visitor needs of it, loaded together.
+template <class B>
+struct HdrBox {
+    CellHdr h;
+    B box;
+};
 
 // Smallest and largest FP64 squared distance of a point to the group's
 // bounding box; both round like the per-ray sqdist, so they bound its value for
@@ -180,19 +194,37 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
         // the boxes that only some rays accept, and (SOLO) all the work of the accepted ones
         uint64_t am = all ? m : 0ull;
         uint64_t todo = COOP ? __ballot(mixed) : __ballot(mixed || (all && !fa));
-        while (todo) {
-            const int k = __ffsll((unsigned long long)todo) - 1;
-            todo &= todo - 1;
-            const int ck = __builtin_amdgcn_readlane(c, k);
-            const bool act = lane_bit(readlane64(m, k));
-            const CellHdr hk = uniform_ld(T.hdr, ck);
-            double w1, w2;
-            const double d2 = sqdist(X, Y, hk.cx, hk.cy, &w1, &w2);
-            const bool acc = act && d2 > hk.rcut2;
-            const uint64_t ak = __ballot(acc);
-            if constexpr (!COOP)
-                if (ak) v.box(ck, acc, w1, w2);
-            if (lane == k) am = ak;
+        if constexpr (COOP) {
+            while (todo) {
+                const int k = __ffsll((unsigned long long)todo) - 1;
+                todo &= todo - 1;
+                const bool act = lane_bit(readlane64(m, k));
+                double w1, w2;
+                const double d2 = sqdist(X, Y, readlane_f64(h.cx, k), readlane_f64(h.cy, k), &w1, &w2);
+                const uint64_t ak = __ballot(act && d2 > readlane_f64(h.rcut2, k));
+                if (lane == k) am = ak;
+            }
+        } else if (todo) {
+            int k = __ffsll((unsigned long long)todo) - 1, ck = __builtin_amdgcn_readlane(c, k);
+            typename V::Box bx = v.load(ck);
+            do {
+                todo &= todo - 1;
+                const int kn = todo ? __ffsll((unsigned long long)todo) - 1 : k;
+                int cn = __builtin_amdgcn_readlane(c, kn);
+                settle(bx, cn);
+                const typename V::Box bn = v.load(cn);
+                const bool act = lane_bit(readlane64(m, k));
+                double w1, w2;
+                const double d2 = sqdist(X, Y, readlane_f64(h.cx, k), readlane_f64(h.cy, k), &w1, &w2);
+                const bool acc = act && d2 > readlane_f64(h.rcut2, k);
+                const uint64_t ak = __ballot(acc);
+                if (ak) v.box(bx, ck, acc, w1, w2);
+                if (lane == k) am = ak;
+                if (kn == k) break;
+                k = kn;
+                ck = cn;
+                bx = bn;
+            } while (true);
         }
         if constexpr (V::stats) {
             uint64_t part = __ballot(has && m != g.full);
@@ -209,9 +241,9 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
             lr = (g.gx1 >= q[0]) & (g.gx0 <= q[1]) & (g.gy1 >= q[2]) & (g.gy0 <= q[3]);
         }
         const bool opl = has && leaf && om != 0;
+        CellExt e{};
+        if (lr || opl) e = T.ext[c];
         if constexpr (!COOP) {
-            CellExt e{};
-            if (lr || opl) e = T.ext[c];
             uint64_t lt = __ballot(lr);
             while (lt) {
                 const int k = __ffsll((unsigned long long)lt) - 1;
@@ -270,7 +302,8 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
                         L.fq[nf + off + rank_in(qa[q])] = c;
                     } else {
                         const int p = q * L.qcap + off + rank_in(qa[q]);
-                        L.qb[p] = c;
+                        L.qb[p] = q == 0 ? c : (q == 1 ? e.pbeg : e.lbeg);
+                        if (q > 0) L.qe[p - L.qcap] = q == 1 ? e.pend : e.lend;
                         L.qm[p] = q == 0 ? am : (q == 1 ? om : m);
                     }
                 }
@@ -294,26 +327,39 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
                     if (((w - rot++) & (W - 1)) == 0) v.far(L.fq[nf + lane], true);
                 }
             }
-            for (int i = (w - rot) & (W - 1); i < qn[0]; i += W) {
-                const int ck = __builtin_amdgcn_readfirstlane(L.qb[i]);
-                const bool acc = lane_bit(uniform64(L.qm[i]));
-                const CellHdr hk = uniform_ld(T.hdr, ck);
-                v.box(ck, acc, X - hk.cx, Y - hk.cy);
+            int i = (w - rot) & (W - 1);
+            if (i < qn[0]) {
+                int ck = __builtin_amdgcn_readfirstlane(L.qb[i]);
+                uint64_t mk = uniform64(L.qm[i]);
+                HdrBox<typename V::Box> bx{uniform_ld(T.hdr, ck), v.load(ck)};
+                do {
+                    i += W;
+                    const int in = i < qn[0] ? i : i - W;
+                    int cn = __builtin_amdgcn_readfirstlane(L.qb[in]);
+                    const uint64_t mn = uniform64(L.qm[in]);
+                    settle(bx, cn);
+                    const HdrBox<typename V::Box> bn{uniform_ld(T.hdr, cn), v.load(cn)};
+                    v.box(bx.box, ck, lane_bit(mk), X - bx.h.cx, Y - bx.h.cy);
+                    ck = cn;
+                    mk = mn;
+                    bx = bn;
+                } while (i < qn[0]);
             }
             rot += qn[0];
-            for (int i = (w - rot) & (W - 1); i < qn[1]; i += W) {
-                const CellExt e = uniform_ld(T.ext, __builtin_amdgcn_readfirstlane(L.qb[L.qcap + i]));
-                v.leaf(e.pbeg, e.pend, uniform64(L.qm[L.qcap + i]));
+            for (i = (w - rot) & (W - 1); i < qn[1]; i += W) {
+                const int p = L.qcap + i;
+                v.leaf(__builtin_amdgcn_readfirstlane(L.qb[p]), __builtin_amdgcn_readfirstlane(L.qe[i]),
+                       uniform64(L.qm[p]));
             }
             rot += qn[1];
-            // short lists go to one wavefront each, the chunks of a long one to all in turn
-            for (int i = 0; i < qn[2]; ++i) {
+            // the 64-entry chunks of all lists in turn
+            for (i = 0; i < qn[2]; ++i) {
                 const int p = 2 * L.qcap + i;
-                const CellExt e = uniform_ld(T.ext, __builtin_amdgcn_readfirstlane(L.qb[p]));
-                const int my = (w - rot) & (W - 1);
-                const int chunks = (e.lend - e.lbeg + kWave - 1) / kWave;
+                const int lb = __builtin_amdgcn_readfirstlane(L.qb[p]);
+                const int le = __builtin_amdgcn_readfirstlane(L.qe[L.qcap + i]);
+                const int my = (w - rot) & (W - 1), chunks = (le - lb + kWave - 1) / kWave;
                 rot += chunks;
-                if (my < chunks) v.list(e.lbeg + my * kWave, e.lend, kWave * W, uniform64(L.qm[p]));
+                if (my < chunks) v.list(lb + my * kWave, le, kWave * W, uniform64(L.qm[p]));
             }
         } else {
 #pragma unroll

@@ -114,25 +114,28 @@ StagedRays staged_rays_view(int64_t nrays, void* ws, const RayLayout& L);
 //  - Few rays: a group of 64 scattered rays covers much of the lens and needs
 //    nearly everything that any of them needs, while most of the chip idles;
 //    groups of fewer rays (the other lanes idle) need less each.  1,024 rays on
-//    1e6 particles: 3.65 ms in 16 groups of 64, 0.39 ms in 256 of 4.  With 256
-//    groups the halving stops paying for small trees (4,096 rays on 1e4
-//    particles: 0.18 ms, with 512 groups 0.23), with 512 for large ones (1e6
-//    particles: 0.97 and 0.76).
-//  - Wavefronts: about 8,192 fill the chip.  Groups over a large tree differ more in
-//    cost, so it takes twice as many (262,144 rays on 1e6 particles: 2.45 ms
-//    with 8,192, 1.83 with 16,384; on 1e4 particles 0.47 and 0.51).
+//    1e6 particles: 3.65 ms in 16 groups of 64, 0.45 ms in 256 of 4.  The
+//    halving pays up to more groups on larger trees (4,096 rays on 1e4
+//    particles: 185 us in 256 groups, 229 in 512; on 1e6 particles 1,168 us in
+//    256, 696 in 1,024).
+//  - Wavefronts: the most that keep the launch under `fill`.  On a small tree
+//    the groups cost alike and more wavefronts only wait for one another; over a
+//    large one the groups of the dense core cost many times the others.
+//    262,144 rays (4,096 groups) with 1, 2, 4, 8 wavefronts each, in us: on 1e4
+//    particles 520, 464, 480, 666; on 6e4 863, 684, 610, 787; on 1e6 -, 2405,
+//    1682, 1617.
 constexpr int kMaxGroupRays = 64;
 struct WalkShape {
     int rays, waves;
 };
 inline WalkShape walk_shape(int64_t nrays, int64_t n)
 {
-    const bool large = n >= 65536;
-    const int64_t min_groups = large ? 512 : 256, fill = large ? 16384 : 8192;
+    const int64_t min_groups = n < 131072 ? 256 : (n < 524288 ? 512 : 1024);
+    const int64_t fill = n < 32768 ? 8192 : (n < 524288 ? 20480 : 40960);
     WalkShape s{kMaxGroupRays, 1};
     while (s.rays > 4 && nrays < min_groups * s.rays) s.rays /= 2;
     const int64_t groups = (nrays + s.rays - 1) / s.rays;
-    while (s.waves < 16 && s.waves * groups < fill) s.waves *= 2;
+    while (s.waves < 16 && 2 * s.waves * groups <= fill) s.waves *= 2;
     return s;
 }
 

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kBlock) void k_walk_batched(const BatchLens* __rest
         const int64_t gi = B.ray_off + (valid ? rl : 0);
         const double X = valid ? xs[gi] : 0.0, Y = valid ? ys[gi] : 0.0;
         const RayGroup g = ray_group(X, Y, valid, MODE != 2);
-        FwdVisitor<P, AONLY, MODE, false, KIND> v(B.tree, g, X, Y, lane, valid);
+        FwdVisitor<P, AONLY, MODE, false, KIND, MODE != 2> v(B.tree, g, X, Y, lane, valid);
         traverse<false>(B.tree, v, g, X, Y, lane, 0, 1, L);
         if (g.far) {
             double* words = reinterpret_cast<double*>(L.stkm);

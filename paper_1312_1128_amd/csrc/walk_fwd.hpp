@@ -4,17 +4,20 @@
 // by M r_cm^k; the terms are summed in FP64.
 #pragma once
 
+#include <type_traits>
+
 #include "traverse.hpp"
 
 namespace glm {
 
 // MODE: 0 = the product walk, 1 = the same plus interaction counts, 2 = plain
 // FP32 sum of the alpha terms (debug).
-template <int P, bool AONLY, int MODE, bool PSI, int KIND>
+template <int P, bool AONLY, int MODE, bool PSI, int KIND, bool FAR>
 struct FwdVisitor {
+    using Box = BoxMoments<P>;
     static constexpr bool f64a = MODE != 2;
     static constexpr bool stats = MODE == 1;
-    static constexpr bool farfield = MODE != 2;
+    static constexpr bool farfield = FAR;
     const TreeDev& T;
     const RayGroup& g;
     const double X, Y;
@@ -22,7 +25,7 @@ struct FwdVisitor {
     const bool valid;
     Acc A{};
     int cnt[stats ? kCounts : 1] = {};
-    double fsum = 0.0; // this lane's word of the group's local expansion (see word_slot)
+    double flo = 0.0, fhi = 0.0; // this lane's words of the two halves of the group's local expansion (see word_slot)
     double fpsi = 0.0; // this lane's boxes' potential at the group's centre
 
     __device__ FwdVisitor(const TreeDev& T_, const RayGroup& g_, double X_, double Y_, int lane_, bool valid_)
@@ -43,17 +46,25 @@ struct FwdVisitor {
 
     __device__ void far(int c, bool active)
     {
-        float L[kFarWords], p0 = 0.0f;
-        far_words<P, PSI>(T, g, c, active, L, &p0);
-        fsum += word_totals64<kFarWords>(L);
-        if constexpr (PSI) fpsi += (double)p0;
+        FarBox<P> b;
+        b.load(T, g, c, active);
+        if constexpr (PSI) fpsi += (double)b.psi0(active);
+        // half of the words at a time: fewer registers
+        float L[kFarWords / 2];
+        b.template words<0>(L);
+        flo += word_totals64<kFarWords / 2>(L);
+        b.template words<kFarOrder / 2 + 1>(L);
+        fhi += word_totals64<kFarWords / 2>(L);
     }
 
-    // This lane's word of the local expansion into `words` (kFarWords doubles of LDS).
+    // This lane's words of the local expansion into `words` (kFarWords doubles of LDS).
     __device__ void put_words(double* words) const
     {
-        const int slot = word_slot<kFarWords>(lane);
-        if (slot >= 0) words[slot] = fsum;
+        const int slot = word_slot<kFarWords / 2>(lane);
+        if (slot >= 0) {
+            words[slot] = flo;
+            words[kFarWords / 2 + slot] = fhi;
+        }
     }
 
     // The local expansion at the rays.
@@ -63,13 +74,15 @@ struct FwdVisitor {
         if constexpr (PSI) A.ps += wave_sum(fpsi);
     }
 
-    __device__ void box(int c, bool acc, double w1, double w2)
+    __device__ Box load(int c) const { return uniform_ld(reinterpret_cast<const Box*>(T.mom), c); }
+
+    __device__ void box(const Box& mo, int, bool acc, double w1, double w2)
     {
         if constexpr (stats) {
             cnt[1] += acc;
             ++cnt[5];
         }
-        if (acc) eval_box<P, AONLY, f64a, PSI>(T.mom + (size_t)c * mom_stride(P), w1, w2, A);
+        if (acc) eval_box<P, AONLY, f64a, PSI>(mo, w1, w2, A);
     }
 
     __device__ void leaf(int pbeg, int pend, uint64_t opn)
@@ -79,9 +92,13 @@ struct FwdVisitor {
             if (act) cnt[2] += pend - pbeg;
             cnt[6] += pend - pbeg;
         }
+        PRec pr = uniform_ld(T.prt, pbeg);
         for (int j = pbeg; j < pend; ++j) {
-            const PRec pr = uniform_ld(T.prt, j);
+            int next = j + 1 < pend ? j + 1 : j;
+            settle(pr, next);
+            const PRec nx = uniform_ld(T.prt, next);
             if (act) leaf_particle<AONLY, f64a, PSI, KIND>(pr, X, Y, A, T.psiK, T.einTerms, T.invC);
+            pr = nx;
         }
     }
 
@@ -93,9 +110,8 @@ struct FwdVisitor {
         for (int base = lbeg; base < lend; base += stride) {
             const int j = base + lane;
             bool cand = false;
-            PRec me{};
             if (j < lend) {
-                me = T.lst[j];
+                const PRec me = T.lst[j];
                 const double dx = fmax(fmax(g.gx0 - me.x, me.x - g.gx1), 0.0);
                 const double dy = fmax(fmax(g.gy0 - me.y, me.y - g.gy1), 0.0);
                 cand = dx * dx + dy * dy < me.qs2 * (1.0 + 1e-9);
@@ -105,11 +121,16 @@ struct FwdVisitor {
                 cnt[4] += base + kWave < lend ? kWave : lend - base;
                 cnt[7] += __popcll(cm);
             }
+            if (!cm) continue;
+            PRec pr = uniform_ld(T.lst, base + __ffsll((unsigned long long)cm) - 1);
             while (cm) {
-                const int k = __ffsll((unsigned long long)cm) - 1;
-                cm &= cm - 1;
-                const PRec pr = uniform_ld(T.lst, base + k);
+                const uint64_t rest = cm & (cm - 1);
+                int next = base + __ffsll((unsigned long long)(rest ? rest : cm)) - 1;
+                settle(pr, next);
+                const PRec nx = uniform_ld(T.lst, next);
                 if (act) list_particle<AONLY, f64a, PSI, KIND>(pr, X, Y, A, hits, T.psiK, T.einTerms, T.invC);
+                pr = nx;
+                cm = rest;
             }
         }
         if constexpr (stats) cnt[3] += hits;
@@ -137,7 +158,7 @@ __device__ inline void write_out(const Acc& A, const int* cnt, int64_t o, const 
 
 // One wavefront (and workgroup) per ray group.
 template <int P, bool AONLY, bool PSI, int KIND>
-__global__ __launch_bounds__(kWave) void k_walk(TreeDev T, const double* __restrict__ rxs,
+__global__ __launch_bounds__(kWave, 6) void k_walk(TreeDev T, const double* __restrict__ rxs,
                                                const double* __restrict__ rys, const uint32_t* __restrict__ rperm,
                                                int64_t nrays, WalkOut out)
 {
@@ -149,7 +170,7 @@ __global__ __launch_bounds__(kWave) void k_walk(TreeDev T, const double* __restr
     const bool valid = r < nrays;
     const double X = valid ? rxs[r] : 0.0, Y = valid ? rys[r] : 0.0;
     const RayGroup g = ray_group(X, Y, valid, true);
-    FwdVisitor<P, AONLY, 0, PSI, KIND> v(T, g, X, Y, lane, valid);
+    FwdVisitor<P, AONLY, 0, PSI, KIND, true> v(T, g, X, Y, lane, valid);
     traverse<false>(T, v, g, X, Y, lane, 0, 1, solo_lds(lds));
     if (g.far) {
         double* words = reinterpret_cast<double*>(lds);
@@ -174,11 +195,11 @@ constexpr size_t walk_coop_lds(int W)
 
 // W = blockDim.x / 64 wavefronts per group of `rays` (up to 64) rays; their sums meet in wavefront
 // order in LDS.
-template <int P, bool AONLY, int MODE, bool PSI, int KIND>
-__global__ __launch_bounds__(kWave* kMaxGroupWaves) void k_walk_coop(TreeDev T, const double* __restrict__ rxs,
+template <int P, bool AONLY, int MODE, bool PSI, int KIND, bool FAR>
+__global__ __launch_bounds__(kWave* kMaxGroupWaves, 5) void k_walk_coop(TreeDev T, const double* __restrict__ rxs,
                                                                     const double* __restrict__ rys,
                                                                     const uint32_t* __restrict__ rperm, int64_t nrays,
-                                                                    WalkOut out, int rays, int far)
+                                                                    WalkOut out, int rays)
 {
     extern __shared__ __align__(16) char lds[];
     constexpr bool STATS = MODE == 1;
@@ -190,13 +211,13 @@ __global__ __launch_bounds__(kWave* kMaxGroupWaves) void k_walk_coop(TreeDev T, 
     const int64_t r = grp * rays + lane;
     const bool valid = lane < rays && r < nrays;
     const double X = valid ? rxs[r] : 0.0, Y = valid ? rys[r] : 0.0;
-    const RayGroup g = ray_group(X, Y, valid, far != 0 && MODE != 2);
-    FwdVisitor<P, AONLY, MODE, PSI, KIND> v(T, g, X, Y, lane, valid);
+    const RayGroup g = ray_group(X, Y, valid, FAR);
+    FwdVisitor<P, AONLY, MODE, PSI, KIND, FAR> v(T, g, X, Y, lane, valid);
     traverse<true>(T, v, g, X, Y, lane, w, W, coop_lds(lds, W));
     Acc& A = v.A;
     __syncthreads(); // the traversal's LDS is free
     double* sums = reinterpret_cast<double*>(lds);
-    if (MODE != 2 && g.far) { // the wavefronts' local expansions, summed into one
+    if (FAR && g.far) { // the wavefronts' local expansions, summed into one
         v.put_words(sums + w * kFarWords);
         __syncthreads();
         if (w == 0) {
@@ -267,9 +288,15 @@ void launch_walk_kind(const WalkArgs& a)
             return;
         }
     }
-    hipLaunchKernelGGL((k_walk_coop<P, AONLY, MODE, PSI, KIND>), g, dim3(kWave * a.shape.waves),
-                       (walk_coop_lds<AONLY, PSI, MODE == 1>(a.shape.waves)), a.st, a.T, a.rxs, a.rys, a.rperm, a.nrays,
-                       a.out, a.shape.rays, a.far ? 1 : 0);
+    const auto coop = [&](auto far) {
+        hipLaunchKernelGGL((k_walk_coop<P, AONLY, MODE, PSI, KIND, decltype(far)::value>), g, dim3(kWave * a.shape.waves),
+                           (walk_coop_lds<AONLY, PSI, MODE == 1>(a.shape.waves)), a.st, a.T, a.rxs, a.rys, a.rperm,
+                           a.nrays, a.out, a.shape.rays);
+    };
+    if constexpr (MODE != 2) {
+        if (a.far) return coop(std::true_type{});
+    }
+    coop(std::false_type{});
 }
 
 template <bool AONLY, int MODE, bool PSI>

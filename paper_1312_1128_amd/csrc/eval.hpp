@@ -525,74 +525,7 @@ __device__ inline void eval_box(const BoxMoments<P>& mom, double w1, double w2, 
     }
 }
 
-// Whether some ray of the group (bounding box [gx0, gx1] x [gy0, gy1]) can
-// lie inside a particle of box c's big-particle list (see the list reach).
-__device__ inline bool list_reaches(const TreeDev& T, int c, double gx0, double gx1, double gy0, double gy1)
-{
-    // the four bounds load together and the tests combine without branches
-    const int64_t i = 4 * (int64_t)c;
-    const double r0 = uniform_ld(T.lreach, i), r1 = uniform_ld(T.lreach, i + 1);
-    const double r2 = uniform_ld(T.lreach, i + 2), r3 = uniform_ld(T.lreach, i + 3);
-    return (gx1 >= r0) & (gx0 <= r1) & (gy1 >= r2) & (gy0 <= r3);
-}
-
-// The walk of a preorder range [c0, c1) of boxes: every ancestor of a box in
-// the range is either in the range or an ancestor of c0.  A lane that accepts
-// an ancestor of c0 skips that ancestor's whole subtree; returns the preorder
-// index at which the lane becomes active (its current skip if none).  c0 must
-// be a box (c0 < ncells): an empty range at the end of the array has no
-// ancestors to replay, and its walk is not made.
-__device__ inline int ancestor_skip(const TreeDev& T, double X, double Y, int c0, int skip)
-{
-    const int nc = T.ncells;
-    int a = 0;
-    while (a < c0 && a < nc) {
-        a = __builtin_amdgcn_readfirstlane(a);
-        const CellHdr ha = T.hdr[a];
-        double w1, w2;
-        const double d2 = sqdist(X, Y, ha.cx, ha.cy, &w1, &w2);
-        if (skip == 0 && d2 > ha.rcut2) skip = ha.next;
-        int ch = a + 1; // the child of a whose subtree holds c0
-        for (int guard = 0; guard < 4 && ch < nc; ++guard) {
-            const int nx = T.hdr[ch].next;
-            if (c0 < nx) break;
-            ch = nx;
-        }
-        a = ch > a ? ch : a + 1;
-    }
-    return skip;
-}
-
-// Box range [c0, c1) of split k of K: everything before box B, K-2 equal
-// slices of B's subtree [B, NB), everything after it (B = the deepest box
-// holding all rays of the launch, so that the slices share the work).
-__device__ inline void split_range(int k, int K, int B, int NB, int nc, int* c0, int* c1)
-{
-    if (K == 1) {
-        *c0 = 0;
-        *c1 = nc;
-        return;
-    }
-    if (k == 0) {
-        *c0 = 0;
-        *c1 = B;
-        return;
-    }
-    if (k == K - 1) {
-        *c0 = NB;
-        *c1 = nc;
-        return;
-    }
-    const int64_t w = NB - B;
-    *c0 = B + (int)((int64_t)(k - 1) * w / (K - 2));
-    *c1 = B + (int)((int64_t)k * w / (K - 2));
-}
-
-// Work of one wavefront in a walk launch over `groups` ray groups, each walked
-// by K wavefronts (one per box range).  Workgroups are dispatched round-robin
-// over the 8 XCDs; inside an XCD the waves run range-major, so that the first
-// range of every group is dispatched first.
-constexpr int kXcds = 8;
+constexpr int kXcds = 8; // workgroups are dispatched to them in turn
 
 // Groups go to the XCDs in chunks of C consecutive groups (C = groups / 512,
 // 1 to 128), round robin, so that every XCD gets a share of each part of the
@@ -609,24 +542,6 @@ __host__ __device__ inline int64_t walk_slots(int64_t groups) // group slots per
     const int64_t c = walk_chunk(groups);
     const int64_t chunks = (groups + c - 1) / c;
     return (chunks + kXcds - 1) / kXcds * c;
-}
-
-__host__ __device__ inline int64_t walk_grid_blocks(int64_t groups, int K)
-{
-    const int64_t gx = walk_slots(groups);
-    return kXcds * ((K * gx + kBlock / kWave - 1) / (kBlock / kWave));
-}
-
-// b: workgroup index, w: wave in the workgroup (both wave-uniform).  Returns
-// false for the waves of the padded grid that have no work.
-__device__ inline bool walk_task(int b, int w, int64_t groups, int K, int* k, int64_t* group)
-{
-    const int64_t gx = walk_slots(groups), c = walk_chunk(groups);
-    const int64_t wj = (int64_t)(b / kXcds) * (kBlock / kWave) + w;
-    *k = (int)(wj / gx);
-    const int64_t slot = wj % gx;
-    *group = ((slot / c) * kXcds + b % kXcds) * c + slot % c;
-    return *k < K && *group < groups;
 }
 
 // One workgroup per group: the grid, and the group of workgroup b (false for

@@ -182,6 +182,30 @@ __device__ inline double word_totals64(const float* a)
     return c[0];
 }
 
+// Totals over the wavefront of four FP64 words: row R (lanes 16 R .. 16 R + 15)
+// ends with word R's.
+__device__ inline double row_word4(const double* a)
+{
+    double b[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) { // half h of the wavefront keeps words 2 h, 2 h + 1
+        const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(a[k]), (uint32_t)__double2loint(a[2 + k]),
+                                                        false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(a[k]), (uint32_t)__double2hiint(a[2 + k]),
+                                                        false, false);
+        b[k] = lane_pair(l[0], h[0]) + lane_pair(l[1], h[1]);
+    }
+    const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(b[0]), (uint32_t)__double2loint(b[1]), false,
+                                                    false);
+    const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(b[0]), (uint32_t)__double2hiint(b[1]), false,
+                                                    false);
+    double v = lane_pair(l[0], h[0]) + lane_pair(l[1], h[1]);
+    v += row_peer64<kRowStep[0]>(v);
+    v += row_peer64<kRowStep[1]>(v);
+    v += row_peer64<kRowStep[2]>(v);
+    return v + row_peer64<kRowStep[3]>(v);
+}
+
 // Smallest, largest value and sum over the wavefront, in every lane (butterfly
 // exchanges in registers: pairs 32, 16, 8, 4, 2, 1 lanes apart).
 template <class Op>

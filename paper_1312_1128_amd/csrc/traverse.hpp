@@ -61,7 +61,7 @@ struct TravLds {
     int cap, qcap;
 };
 
-__host__ __device__ constexpr int coop_stack(int W) { return W <= 2 ? 512 : (W <= 8 ? 256 * W - 256 : 2048); }
+__host__ __device__ constexpr int coop_stack(int W) { return W <= 2 ? 512 : (W == 4 ? 768 : (W == 8 ? 1280 : 2048)); }
 __host__ __device__ constexpr int coop_queue(int W)
 {
     const int by_stack = (coop_stack(W) - kStackReserve) / 3;

@@ -121,35 +121,6 @@ __global__ __launch_bounds__(kBlock) void k_ray_gather(const uint32_t* __restric
     ys[k] = y[perm[k]];
 }
 
-// The deepest box whose square holds the rays' bounding box (one thread);
-// -1 when the rays cover under 5% of the root square: their work then sits in
-// a small part of the tree and splitting by box ranges would not spread it.
-__global__ void k_split_box(BoxArrays b, const int32_t* __restrict__ next, double x0, double y0, double S,
-                            const double* __restrict__ bb, int ncells, int* __restrict__ out)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    if ((bb[1] - bb[0]) * (bb[3] - bb[2]) < 0.05 * S * S) {
-        *out = -1;
-        return;
-    }
-    int c = 0;
-    for (int guard = 0; guard <= kMaxLevel; ++guard) {
-        if (b.leaf[c]) break;
-        int found = -1;
-        for (int ch = c + 1, n = 0; ch < next[c] && n < 4; ch = next[ch] > ch ? next[ch] : ch + 1, ++n) {
-            const double side = ldexp(S, -b.level[ch]);
-            const double bx0 = x0 + (double)b.ix[ch] * side, by0 = y0 + (double)b.iy[ch] * side;
-            if (bb[0] >= bx0 && bb[1] < bx0 + side && bb[2] >= by0 && bb[3] < by0 + side) {
-                found = ch;
-                break;
-            }
-        }
-        if (found < 0) break;
-        c = found;
-    }
-    *out = c < ncells ? c : 0;
-}
-
 } // namespace
 
 RayLayout ray_layout(int64_t nrays)
@@ -164,8 +135,6 @@ RayLayout ray_layout(int64_t nrays)
     L.ys = a.take(8ull * nrays);
     L.hist = a.take(4ull * radix_hist_words(nrays));
     L.part = a.take(sizeof(double) * 4 * (kRayBboxBlocks + 1));
-    L.sbox = a.take(64);
-    L.split = walk_split(nrays);
     L.bytes = a.size;
     return L;
 }
@@ -392,24 +361,6 @@ glm_status shoot_batched_device(const BatchLens* host_table, int nlens, int orde
     launch_walk_batched(BatchArgs{dtab, nlens, dgpre, counter, xs, ys, perm, items, order, host_table[0].tree.kind,
                                   (flags & GLM_ALPHA_ONLY) != 0, (flags & GLM_FP32_ALPHA) != 0, st});
     GLM_HIP(hipGetLastError());
-    return GLM_OK;
-}
-
-glm_status split_box_device(const TreeStorage& ts, const double* rx, const double* ry, int64_t nrays, void* ws,
-                            const RayLayout& L, bool have_bbox, int** out, hipStream_t st)
-{
-    char* W = static_cast<char*>(ws);
-    double* part = reinterpret_cast<double*>(W + L.part);
-    const int nbb = kRayBboxBlocks;
-    if (!have_bbox) {
-        hipLaunchKernelGGL(k_ray_bbox, dim3(nbb), dim3(kBlock), 0, st, rx, ry, nrays, part);
-        hipLaunchKernelGGL(k_ray_root, dim3(1), dim3(kBlock), 0, st, part, nbb, part + 4 * nbb);
-    }
-    int* sb = reinterpret_cast<int*>(W + L.sbox);
-    hipLaunchKernelGGL(k_split_box, dim3(1), dim3(1), 0, st, ts.b, ts.b.next, ts.x0, ts.y0, ts.side, part + 4 * nbb,
-                       ts.ncells, sb);
-    GLM_HIP(hipGetLastError());
-    *out = sb;
     return GLM_OK;
 }
 

@@ -61,26 +61,6 @@ glm_status interp_estimate_device(const double* cx, const double* cy, const floa
                                   int64_t nbase, int64_t capacity, const void* state, hipStream_t st);
 size_t shoot_indexed_workspace_bytes(int64_t count);
 
-// Wavefronts per 64-ray group.  A small launch (few groups) splits the
-// preorder box array into K ranges walked by separate wavefronts, so that
-// about kSplitWaves wavefronts keep the chip busy; their partial sums are
-// merged per ray in range order.  A split has a range before, K - 2 slices
-// of, and a range after one box: below kMinSplit ranges it rarely spreads the
-// work, so there is none.
-constexpr int64_t kSplitWaves = 16384;
-constexpr int64_t kMinSplit = 4;
-constexpr int64_t kMaxSplit = 32;
-
-inline int walk_split(int64_t nrays)
-{
-    const int64_t groups = (nrays + 63) / 64;
-    if (groups <= 0) return 1;
-    int64_t k = (kSplitWaves + groups - 1) / groups;
-    if (k > kMaxSplit) k = kMaxSplit;
-    if (k < kMinSplit) k = 1;
-    return (int)k;
-}
-
 // Per-ray counts of a walk: boxes visited (opening tests), boxes accepted,
 // leaf particles summed, list particles the ray falls inside; then counts of
 // its wavefront (the same for the 64 rays of a group): list entries tested
@@ -91,8 +71,7 @@ constexpr int kCounts = 8;
 
 // Byte offsets of the ray workspace pieces.
 struct RayLayout {
-    size_t k0, k1, v0, v1, xs, ys, hist, part, sbox, bytes;
-    int split;
+    size_t k0, k1, v0, v1, xs, ys, hist, part, bytes;
 };
 RayLayout ray_layout(int64_t nrays);
 
@@ -139,16 +118,20 @@ inline WalkShape walk_shape(int64_t nrays, int64_t n)
     return s;
 }
 
+// The same for the adjoint walk: at most 8 wavefronts, whose LDS (a ray table
+// each) still fits twice on a CU.
+inline WalkShape adjoint_shape(int64_t nrays, int64_t n)
+{
+    WalkShape s = walk_shape(nrays, n);
+    if (s.waves > 8) s.waves = 8;
+    return s;
+}
+
 // Whether a forward walk expands far boxes over its ray groups (farfield.hpp).
 // With fewer rays than this the groups of scattered rays are too wide to have
 // many far boxes, and a ray's result keeps not depending on its group.
 constexpr int64_t kFarRays = 65536;
 inline bool walk_far(int64_t nrays) { return nrays >= kFarRays; }
-
-// Index of the deepest box holding the rays' bounding box, written to the
-// workspace (computes the box unless stage_rays did).
-glm_status split_box_device(const TreeStorage& ts, const double* rx, const double* ry, int64_t nrays, void* ws,
-                            const RayLayout& L, bool have_bbox, int** out, hipStream_t st);
 
 glm_status shoot_device(const TreeStorage& ts, const double* rx, const double* ry, int64_t nrays, float* a1,
                         float* a2, float* k, float* g1, float* g2, int32_t* counts, uint32_t flags, void* ws,

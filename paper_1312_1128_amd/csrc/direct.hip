@@ -1,8 +1,13 @@
 // Plain direct summation over every particle (the theta = 0 limit of the
-// tree, Sec. 5.1), FP32 terms summed in FP64 for alpha and shear, or FP64 throughout, for truncated
-// Gaussians or truncated NFW halos (and point masses with either).  One thread per ray;
-// particles stream through LDS in tiles of 256 and every lane reads the same
-// record (LDS broadcast).
+// tree, Sec. 5.1), FP32 terms summed in FP64, or FP64 throughout, for truncated
+// Gaussians or truncated NFW halos (and point masses with either).
+//
+// A workgroup of 16 (or 4) wavefronts serves RB rays.  Particles stream through LDS in
+// tiles; lane (ray, sub) of wavefront w takes every kth particle of a tile,
+// k = (wavefronts) * 64 / RB, and the partial sums meet at the end (lanes of a ray by
+// shuffles, wavefronts in LDS, in wavefront order).  One thread per ray left the
+// chip mostly idle below about 500,000 rays: 20,480 validation rays made 80 workgroups
+// for 256 compute units.
 #include <math.h>
 
 #include "eval.hpp"
@@ -27,113 +32,181 @@ __device__ inline void make_rec(PRec& r, double x, double y, double m, double s,
     r.meta = idx; // not listed: the profile inside the support, a point outside
 }
 
-template <bool AONLY, int KIND>
-__global__ __launch_bounds__(kBlock) void k_direct32(const double* __restrict__ x, const double* __restrict__ y,
-                                                    const double* __restrict__ m, const double* __restrict__ s, int n,
-                                                    double q, double norm, const double* __restrict__ rx,
-                                                    const double* __restrict__ ry, int64_t nr, float* __restrict__ a1,
-                                                    float* __restrict__ a2, float* __restrict__ ka,
-                                                    float* __restrict__ g1, float* __restrict__ g2)
+// Wavefronts of a workgroup (a tile is one particle per thread): 16 where few
+// rays share a workgroup; 4 with 64 rays, where there are workgroups enough and
+// fewer wavefronts wait for one another at the tiles' barriers (halos, whose
+// lanes diverge: 2.62e5 rays and 30,000 halos 23.2 ms with 16 wavefronts).
+__host__ __device__ constexpr int dir_waves(int rb) { return rb == kWave ? 4 : 16; }
+
+// Partial sums v[0 .. NV) of the lanes and wavefronts that share the
+// workgroup's RB rays, summed into the lanes of wavefront 0 below RB (true there).
+template <int RB, int NV>
+__device__ inline bool direct_sum(double* v, double* lds)
 {
-    __shared__ PRec tile[kBlock];
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool valid = r < nr;
-    const double X = valid ? rx[r] : 0.0, Y = valid ? ry[r] : 0.0;
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+#pragma unroll
+    for (int o = kWave / 2; o >= RB; o >>= 1)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v[i] += __shfl_xor(v[i], o, kWave);
+    __syncthreads(); // the tile is free
+    if (w > 0 && lane < RB)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) lds[((w - 1) * NV + i) * RB + lane] = v[i];
+    __syncthreads();
+    if (w > 0 || lane >= RB) return false;
+    for (int u = 0; u < dir_waves(RB) - 1; ++u)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v[i] += lds[(u * NV + i) * RB + lane];
+    return true;
+}
+
+template <bool AONLY, int KIND, int RB>
+__global__ __launch_bounds__(kWave* dir_waves(RB)) void k_direct32(const double* __restrict__ x, const double* __restrict__ y,
+                                                         const double* __restrict__ m, const double* __restrict__ s,
+                                                         int n, double q, double norm, const double* __restrict__ rx,
+                                                         const double* __restrict__ ry, int64_t nr,
+                                                         float* __restrict__ a1, float* __restrict__ a2,
+                                                         float* __restrict__ ka, float* __restrict__ g1,
+                                                         float* __restrict__ g2)
+{
+    constexpr int SUB = kWave / RB, NV = AONLY ? 2 : 5, kDirWaves = dir_waves(RB), kDirTile = kWave * kDirWaves;
+    __shared__ __align__(16) char lds[sizeof(PRec) * kDirTile];
+    static_assert(sizeof(lds) >= sizeof(double) * (kDirWaves - 1) * NV * RB, "the sums fit the tile");
+    PRec* tile = reinterpret_cast<PRec*>(lds);
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int64_t r = (int64_t)blockIdx.x * RB + lane % RB;
+    const double X = r < nr ? rx[r] : 0.0, Y = r < nr ? ry[r] : 0.0;
     Acc A = {};
-    for (int base = 0; base < n; base += kBlock) {
-        const int j = base + threadIdx.x;
+    for (int64_t base = 0; base < n; base += kDirTile) {
+        const int64_t j = base + threadIdx.x;
         PRec t;
         if (j < n) make_rec<KIND>(t, x[j], y[j], m[j], s ? s[j] : 0.0, q, norm, (uint32_t)j);
-        else make_rec<KIND>(t, 0.0, 0.0, 0.0, 0.0, q, norm, 0u);
+        else make_rec<KIND>(t, 0.0, 0.0, 0.0, 0.0, q, norm, 0u); // no mass: adds nothing
+        __syncthreads(); // the previous tile is done
         tile[threadIdx.x] = t;
         __syncthreads();
-        const int cnt = min(kBlock, n - base);
-        for (int k = 0; k < cnt; ++k) leaf_particle<AONLY, true, false, KIND>(tile[k], X, Y, A);
-        __syncthreads();
+        const int cnt = (int)(n - base < kDirTile ? n - base : kDirTile);
+        for (int k = w * SUB; k < cnt; k += kDirWaves * SUB)
+            leaf_particle<AONLY, true, false, KIND>(tile[k + lane / RB], X, Y, A);
     }
-    if (!valid) return;
-    a1[r] = (float)alpha1(A);
-    a2[r] = (float)alpha2(A);
+    double v[5] = {alpha1(A), alpha2(A), A.k, A.g1, A.g2};
+    if (!direct_sum<RB, NV>(v, reinterpret_cast<double*>(lds)) || r >= nr) return;
+    a1[r] = (float)v[0];
+    a2[r] = (float)v[1];
     if (!AONLY) {
-        ka[r] = (float)A.k;
-        g1[r] = (float)A.g1;
-        g2[r] = (float)A.g2;
+        ka[r] = (float)v[2];
+        g1[r] = (float)v[3];
+        g2[r] = (float)v[4];
     }
+}
+
+// 1 / v to FP64 rounding (about 1 ulp): the hardware estimate and two Newton
+// steps, 5 instructions for a division's dozen; outside the range where the
+// steps cannot over- or underflow, the division.
+__device__ inline double recip64(double v)
+{
+    double r = __builtin_amdgcn_rcp(v);
+    double e = fma(-v, r, 1.0);
+    r = fma(r, e, r);
+    e = fma(-v, r, 1.0);
+    r = fma(r, e, r);
+    if (__any(!(v >= 0x1p-900 && v <= 0x1p900))) r = v >= 0x1p-900 && v <= 0x1p900 ? r : 1.0 / v;
+    return r;
 }
 
 // FP64: the brute-force sum term by term (Sec. 3.1 kernel or the NFW halo of
 // Sec. 3.2 inside the support, Sec. 3.5 point mass outside).  C: the Gaussian
-// normalisation 1 - exp(-q^2/2), or g(c) for halos.
-template <bool AONLY, int KIND>
-__global__ __launch_bounds__(kBlock) void k_direct64(const double* __restrict__ x, const double* __restrict__ y,
-                                                    const double* __restrict__ m, const double* __restrict__ s, int n,
-                                                    double q, double C, const double* __restrict__ rx,
-                                                    const double* __restrict__ ry, int64_t nr, double* __restrict__ a1,
-                                                    double* __restrict__ a2, double* __restrict__ ka,
-                                                    double* __restrict__ g1, double* __restrict__ g2)
+// normalisation 1 - exp(-q^2/2), or g(c) for halos.  FP64 VALU bound: a point
+// pair takes one reciprocal of r^2 and about 25 FP64 operations (it took four
+// divisions); the profile is evaluated where some lane is inside a support.
+// 20,480 rays on 2e5 smoothed particles: 49.3 ms with one thread per ray, 6.5 ms now.
+template <bool AONLY, int KIND, int RB>
+__global__ __launch_bounds__(kWave* dir_waves(RB)) void k_direct64(const double* __restrict__ x, const double* __restrict__ y,
+                                                         const double* __restrict__ m, const double* __restrict__ s,
+                                                         int n, double q, double C, const double* __restrict__ rx,
+                                                         const double* __restrict__ ry, int64_t nr,
+                                                         double* __restrict__ a1, double* __restrict__ a2,
+                                                         double* __restrict__ ka, double* __restrict__ g1,
+                                                         double* __restrict__ g2)
 {
-    __shared__ double tx[kBlock], ty[kBlock], tm[kBlock], ts[kBlock];
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool valid = r < nr;
-    const double X = valid ? rx[r] : 0.0, Y = valid ? ry[r] : 0.0;
+    constexpr int SUB = kWave / RB, NV = AONLY ? 2 : 5, kDirWaves = dir_waves(RB), kDirTile = kWave * kDirWaves;
+    __shared__ __align__(16) double sums[5 * kDirTile]; // the tile, then the sums
+    double2* txy = reinterpret_cast<double2*>(sums);    // position
+    double2* tmq = txy + kDirTile;                      // mass and squared support
+    double* ts = sums + 4 * kDirTile;
+    static_assert(5 * kDirTile >= (kDirWaves - 1) * NV * RB, "the sums fit the tile");
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int64_t r = (int64_t)blockIdx.x * RB + lane % RB;
+    const double X = r < nr ? rx[r] : 0.0, Y = r < nr ? ry[r] : 0.0;
     double sa1 = 0, sa2 = 0, sk = 0, sg1 = 0, sg2 = 0;
-    for (int base = 0; base < n; base += kBlock) {
-        const int j = base + threadIdx.x;
-        tx[threadIdx.x] = j < n ? x[j] : 0.0;
-        ty[threadIdx.x] = j < n ? y[j] : 0.0;
-        tm[threadIdx.x] = j < n ? m[j] : 0.0;
-        ts[threadIdx.x] = (j < n && s) ? s[j] : 0.0;
-        __syncthreads();
-        const int cnt = min(kBlock, n - base);
-        for (int k = 0; k < cnt; ++k) {
-            double d1, d2;
-            const double r2 = sqdist(X, Y, tx[k], ty[k], &d1, &d2);
-            const double sj = ts[k], mj = tm[k];
-            double qs2;
-            {
+    for (int64_t base = 0; base < n; base += kDirTile) {
+        const int64_t j = base + threadIdx.x;
+        const double sj = (j < n && s) ? s[j] : 0.0;
+        double2 xy = make_double2(0.0, 0.0), mq = make_double2(0.0, 0.0); // no mass: adds nothing
+        if (j < n) {
 #pragma clang fp contract(off)
-                const double qs = KIND == kKindNfw ? sj : q * sj;
-                qs2 = qs * qs;
-            }
-            const bool inside = sj > 0.0 && r2 < qs2;
-            if (r2 == 0.0) { // a Gaussian's centre has finite kappa; a halo's gives nothing
-                if (KIND == kKindGauss && inside) sk += mj / (2.0 * sj * sj * C);
-                continue;
-            }
-            double hh = mj / r2, K = 0.0; // alpha = hh d
+            const double qs = KIND == kKindNfw ? sj : q * sj;
+            xy = make_double2(x[j], y[j]);
+            mq = make_double2(m[j], sj > 0.0 ? qs * qs : 0.0);
+        }
+        __syncthreads(); // the previous tile is done
+        txy[threadIdx.x] = xy;
+        tmq[threadIdx.x] = mq;
+        ts[threadIdx.x] = sj;
+        __syncthreads();
+        const int cnt = (int)(n - base < kDirTile ? n - base : kDirTile);
+#pragma unroll(KIND == kKindNfw ? 1 : 2)
+        for (int k0 = w * SUB; k0 < cnt; k0 += kDirWaves * SUB) {
+            const int k = k0 + lane / RB;
+            const double2 p = txy[k], mm = tmq[k];
+            double d1, d2;
+            const double r2 = sqdist(X, Y, p.x, p.y, &d1, &d2);
+            const bool inside = r2 < mm.y;
+            const double ir2 = r2 > 0.0 ? recip64(r2) : 0.0; // (a particle exactly at the ray has no deflection)
+            double hh = mm.x * ir2, tt = hh * ir2; // alpha = hh d, gamma = -tt (d1^2 - d2^2, 2 d1 d2)
             if (inside) {
+                const double sp = ts[k];
+                double K;
                 if constexpr (KIND == kKindNfw) {
-                    const double hs = q / sj, x2 = r2 * (hs * hs);
+                    const double hs = q / sp, x2 = r2 * (hs * hs);
                     double gx2, f;
                     nfw_shape<double, 17>(x2, x2 - 1.0, 0.1, &gx2, &f);
-                    const double mh2 = mj / C * (hs * hs);
+                    const double mh2 = mm.x / C * (hs * hs);
                     hh = mh2 * gx2;
-                    K = 0.5 * mh2 * f;
+                    K = r2 > 0.0 ? 0.5 * mh2 * f : 0.0; // a halo's centre gives nothing
                 } else {
-                    const double u = r2 / (2.0 * sj * sj);
-                    hh = mj * (-expm1(-u) / C) / r2;
-                    K = mj * exp(-u) / (2.0 * sj * sj * C);
+                    const double u = r2 / (2.0 * sp * sp);
+                    hh = mm.x * (-expm1(-u) / C) * ir2;
+                    K = mm.x * exp(-u) / (2.0 * sp * sp * C);
                 }
-            }
-            sa1 += hh * d1;
-            sa2 += hh * d2;
-            if (!AONLY) {
-                const double Gam = hh - K;
+                tt = (hh - K) * ir2;
                 sk += K;
-                sg1 -= Gam * (d1 * d1 - d2 * d2) / r2;
-                sg2 -= Gam * 2.0 * d1 * d2 / r2;
+            }
+            sa1 = fma(hh, d1, sa1);
+            sa2 = fma(hh, d2, sa2);
+            if (!AONLY) {
+                sg1 = fma(-tt, d1 * d1 - d2 * d2, sg1);
+                sg2 = fma(-tt, 2.0 * d1 * d2, sg2);
             }
         }
-        __syncthreads();
     }
-    if (!valid) return;
-    a1[r] = sa1;
-    a2[r] = sa2;
+    double v[5] = {sa1, sa2, sk, sg1, sg2};
+    if (!direct_sum<RB, NV>(v, sums) || r >= nr) return;
+    a1[r] = v[0];
+    a2[r] = v[1];
     if (!AONLY) {
-        ka[r] = sk;
-        g1[r] = sg1;
-        g2[r] = sg2;
+        ka[r] = v[2];
+        g1[r] = v[3];
+        g2[r] = v[4];
     }
+}
+
+// Rays per workgroup: the most that still leave a few workgroups for every
+// compute unit (2e5 particles: 4,096 rays 1.8 ms in 1,024 workgroups of 4 rays;
+// 262,144 rays on 3e4 particles 17.4 ms in 4,096 of 64, 20.4 in 16,384 of 16).
+inline int direct_rays(int64_t nrays)
+{
+    return nrays >= 64 * 2048 ? 64 : (nrays >= 16 * 512 ? 16 : 4);
 }
 
 } // namespace
@@ -145,35 +218,41 @@ glm_status direct_device(const double* x, const double* y, const double* m, cons
     if (nrays == 0) return GLM_OK;
     const double C = kind == kKindNfw ? nfw_g_at(q) : -expm1(-0.5 * q * q);
     const bool aonly = !out5[2] || !out5[3] || !out5[4];
-    const dim3 g(ceil_div(nrays, kBlock)), b(kBlock);
+    const int rb = direct_rays(nrays);
+    const dim3 g(ceil_div(nrays, rb)), b(kWave * dir_waves(rb));
+#define GLM_DIRECT(KERNEL, AO, KD, NORM)                                                                                \
+    do {                                                                                                                \
+        if (rb == 64)                                                                                                   \
+            hipLaunchKernelGGL((KERNEL<AO, KD, 64>), g, b, 0, st, x, y, m, s, (int)n, q, NORM, rx, ry, nrays, o[0], o[1], \
+                               o[2], o[3], o[4]);                                                                       \
+        else if (rb == 16)                                                                                              \
+            hipLaunchKernelGGL((KERNEL<AO, KD, 16>), g, b, 0, st, x, y, m, s, (int)n, q, NORM, rx, ry, nrays, o[0], o[1], \
+                               o[2], o[3], o[4]);                                                                       \
+        else                                                                                                            \
+            hipLaunchKernelGGL((KERNEL<AO, KD, 4>), g, b, 0, st, x, y, m, s, (int)n, q, NORM, rx, ry, nrays, o[0], o[1], \
+                               o[2], o[3], o[4]);                                                                       \
+    } while (0)
+#define GLM_KINDS(KERNEL, NORM)                              \
+    do {                                                     \
+        if (kind == kKindNfw) {                              \
+            if (aonly) GLM_DIRECT(KERNEL, true, kKindNfw, NORM);   \
+            else GLM_DIRECT(KERNEL, false, kKindNfw, NORM);        \
+        } else {                                             \
+            if (aonly) GLM_DIRECT(KERNEL, true, kKindGauss, NORM); \
+            else GLM_DIRECT(KERNEL, false, kKindGauss, NORM);      \
+        }                                                    \
+    } while (0)
     if (fp64) {
         double* o[5];
         for (int k = 0; k < 5; ++k) o[k] = static_cast<double*>(out5[k]);
-#define GLM_D64(AO, KD) \
-    hipLaunchKernelGGL((k_direct64<AO, KD>), g, b, 0, st, x, y, m, s, (int)n, q, C, rx, ry, nrays, o[0], o[1], o[2], o[3], o[4])
-        if (kind == kKindNfw) {
-            if (aonly) GLM_D64(true, kKindNfw);
-            else GLM_D64(false, kKindNfw);
-        } else {
-            if (aonly) GLM_D64(true, kKindGauss);
-            else GLM_D64(false, kKindGauss);
-        }
-#undef GLM_D64
+        GLM_KINDS(k_direct64, C);
     } else {
         float* o[5];
         for (int k = 0; k < 5; ++k) o[k] = static_cast<float*>(out5[k]);
-#define GLM_D32(AO, KD)                                                                                                 \
-    hipLaunchKernelGGL((k_direct32<AO, KD>), g, b, 0, st, x, y, m, s, (int)n, q, 1.0 / C, rx, ry, nrays, o[0], o[1], o[2], \
-                       o[3], o[4])
-        if (kind == kKindNfw) {
-            if (aonly) GLM_D32(true, kKindNfw);
-            else GLM_D32(false, kKindNfw);
-        } else {
-            if (aonly) GLM_D32(true, kKindGauss);
-            else GLM_D32(false, kKindGauss);
-        }
-#undef GLM_D32
+        GLM_KINDS(k_direct32, 1.0 / C);
     }
+#undef GLM_KINDS
+#undef GLM_DIRECT
     GLM_HIP(hipGetLastError());
     return GLM_OK;
 }

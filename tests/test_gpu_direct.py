@@ -54,3 +54,33 @@ def test_direct_matches_oracle(ora, which):
     # the sum of the terms' magnitudes, which exceeds |gamma| where terms cancel
     assert ea.max() <= FP32_MAX["alpha"] and eg.max() <= FP32_MAX["gamma"]
     assert np.all(ek[~zero] <= FP32_MAX["kappa"])
+
+
+@pytest.mark.parametrize("n,nr", [(1, 1), (63, 15), (64, 17), (255, 4097), (256, 8191), (1023, 8192), (1024, 8193),
+                                  (1025, 16), (300, 131_071), (257, 131_073)])
+@pytest.mark.parametrize("nfw", [False, True])
+def test_direct_at_tile_and_workgroup_edges(ora, n, nr, nfw):
+    """Particle counts around a tile, ray counts around the sizes where a
+    workgroup takes 4, 16 or 64 rays; rays exactly on particles included."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    if nfw:
+        lens, c = synth.nfw_halo_field(n, 71)
+    else:
+        lens, c = synth.gaussian_blobs(n, 71, s_lo=0.01, s_hi=0.2), 3.0
+        lens.s[::5] = 0.0
+    rx, ry = synth.uniform_points(nr, 72, -0.7, 0.7)
+    k = min(n, nr) // 2
+    rx[:k], ry[:k] = lens.x[:k], lens.y[:k]
+    idx = np.union1d(synth.sample_rays(rx, ry, 4000, 73), [0, nr - 1])
+    say(f"[gpu] direct edges n={n} rays={nr} nfw={nfw}")
+    ref = (ora.direct_nfw if nfw else ora.direct)(lens.x, lens.y, lens.m, lens.s, c, rx[idx], ry[idx])
+    for fp64, tol in ((True, 1e-10), (False, 1e-5)):
+        o = g.shoot_direct(dev(lens.x), dev(lens.y), dev(lens.m), dev(lens.s), c, dev(rx), dev(ry), fp64=fp64, nfw=nfw)
+        torch.cuda.synchronize()
+        got = np.stack([o[q].double().cpu().numpy()[idx] for q in ["a1", "a2", "kappa", "g1", "g2"]], axis=1)
+        for cols in (slice(0, 2), slice(2, 3), slice(3, 5)):
+            mag = np.linalg.norm(ref[:, cols], axis=1)
+            err = np.linalg.norm(got[:, cols] - ref[:, cols], axis=1)
+            assert np.all(err <= tol * (mag + 1e-2 * mag.max() + 1e-300)), (fp64, cols)

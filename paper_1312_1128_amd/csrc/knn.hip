@@ -4,31 +4,23 @@
 //
 // One wavefront serves 64 particles that are neighbours in Morton order (one
 // per lane).  Each lane keeps the k smallest squared distances found so far
-// in an ascending register list of fixed capacity KC >= k whose first KC - k
-// slots hold -inf, so the k-th smallest always sits in the last slot.  The
-// list starts from the group's own 64 particles (a tight first bound), then
-// the wave walks the preorder box array: it enters a box if some lane's
-// distance to the box square is below that lane's current k-th distance, and
-// scans the particles of the leaves it reaches.  Every distance is FP64 and
-// formed exactly as in the definition, so the result is the k-th smallest
-// FP64 distance.
+// (knn_list.hpp), starting from its own k neighbours on either side along the
+// Morton order.  (Started from the group's 64 particles, the few lanes on the far
+// side of one of the curve's jumps had no bound but the distance across it, and
+// their wavefront scanned a good part of the lens: at 1e6 particles, k = 32, half
+// a wavefront per SIMD was running on average over 11 ms.)  Then the wave walks
+// the tree: it enters a box if some lane's distance to the box square is below
+// that lane's current k-th distance, and scans the particles of the leaves it
+// reaches.  Every distance is FP64 and formed exactly as in the definition, so
+// the result is the k-th smallest FP64 distance.
 #include <math.h>
 
 #include "build.hpp"
+#include "knn_list.hpp"
 
 namespace glm {
 
 namespace {
-
-// Insert v into the ascending list h (the largest entry drops out):
-// h[i] <- max(h[i-1], min(v, h[i])), no branches.
-template <int KC>
-__device__ inline void knn_insert(double (&h)[KC], double v)
-{
-#pragma unroll
-    for (int i = KC - 1; i > 0; --i) h[i] = fmax(h[i - 1], fmin(v, h[i]));
-    h[0] = fmin(v, h[0]);
-}
 
 __device__ inline double knn_d2(double X, double Y, double px, double py)
 {
@@ -36,6 +28,8 @@ __device__ inline double knn_d2(double X, double Y, double px, double py)
     const double dx = X - px, dy = Y - py;
     return dx * dx + dy * dy;
 }
+
+constexpr int kKnnStack = 384;
 
 template <int KC>
 __global__ __launch_bounds__(kBlock) void k_knn(TreeDev T, BoxArrays b, double x0, double y0, double S,
@@ -46,50 +40,92 @@ __global__ __launch_bounds__(kBlock) void k_knn(TreeDev T, BoxArrays b, double x
     const int n = T.n;
     const int g0 = (blockIdx.x * (kBlock / kWave) + w) * kWave; // first particle of the group
     if (g0 >= n) return;
-    const int g1 = min(n, g0 + kWave);
     const int j = g0 + lane;
     const bool valid = j < n;
     const PRec me = T.prt[valid ? j : g0];
     const double X = me.x, Y = me.y;
-    double h[KC];
-#pragma unroll
-    for (int i = 0; i < KC; ++i) h[i] = i < KC - k ? -INFINITY : INFINITY;
+    __shared__ double lds[kBlock / kWave][kKnnQueue * kWave];
+    __shared__ int stack[kBlock / kWave][kKnnStack];
+    KnnList<KC> L(k, lds[w], lane);
 
-    // the group's own particles first
-    for (int c = g0; c < g1; ++c) {
-        const PRec pr = T.prt[c];
-        knn_insert<KC>(h, c == j ? INFINITY : knn_d2(X, Y, pr.x, pr.y));
+    // each lane's k neighbours along the Morton order on either side first
+    for (int o = 1; o <= k; ++o) {
+        const int a = j - o, b2 = j + o;
+        const PRec& pa = T.prt[a >= 0 ? a : 0];
+        const PRec& pb = T.prt[b2 < n ? b2 : 0];
+        const double da = knn_d2(X, Y, pa.x, pa.y), db = knn_d2(X, Y, pb.x, pb.y);
+        L.insert(a >= 0 ? da : INFINITY);
+        L.insert(b2 < n ? db : INFINITY);
     }
 
-    // then every box that some lane still needs, in preorder
-    const int nc = T.ncells;
-    int cur = 0;
-    while (cur < nc) {
-        cur = __builtin_amdgcn_readfirstlane(cur);
-        const int lev = b.level[cur], nx = b.next[cur];
-        const double side = ldexp(S, -lev);
-        const double bx0 = x0 + (double)b.ix[cur] * side - margin;
-        const double bx1 = x0 + ((double)b.ix[cur] + 1.0) * side + margin;
-        const double by0 = y0 + (double)b.iy[cur] * side - margin;
-        const double by1 = y0 + ((double)b.iy[cur] + 1.0) * side + margin;
-        const double dx = fmax(fmax(bx0 - X, X - bx1), 0.0), dy = fmax(fmax(by0 - Y, Y - by1), 0.0);
-        const bool need = valid && dx * dx + dy * dy < h[KC - 1];
-        if (!__any(need)) {
-            cur = nx > cur ? nx : cur + 1; // skip the subtree
-            continue;
+    // then every box that some lane still needs
+    const double gx0 = wave_min(X), gx1 = wave_max(X), gy0 = wave_min(Y), gy1 = wave_max(Y); // (idle lanes: particle g0)
+    int* stk = stack[w];
+    int top = 1;
+    if (lane == 0) stk[0] = 0;
+    wave_lds_sync();
+    while (top > 0) {
+        top = __builtin_amdgcn_readfirstlane(top);
+        const int m = knn_take(top, kKnnStack, 4, kMaxLevel);
+        top -= m;
+        const bool has = lane < m;
+        const int c = has ? stk[top + lane] : 0;
+        const double side = ldexp(S, -b.level[c]);
+        const double cx = x0 + ((double)b.ix[c] + 0.5) * side, cy = y0 + ((double)b.iy[c] + 0.5) * side;
+        const double hs = 0.5 * side + margin;
+        const int leaf = b.leaf[c], beg = b.beg[c], end = b.end[c];
+        const int4 kc = *reinterpret_cast<const int4*>(T.kids + 4 * (size_t)c);
+        const double far = wave_max(valid ? L.bound() : 0.0);
+        bool keep = has;
+        {
+            const double dx = fmax(fmax(gx0 - cx, cx - gx1) - hs, 0.0), dy = fmax(fmax(gy0 - cy, cy - gy1) - hs, 0.0);
+            keep = keep && dx * dx + dy * dy < far;
         }
-        if (b.leaf[cur]) {
-            const int pe = b.end[cur];
-            for (int c = b.beg[cur]; c < pe; ++c) {
-                if (c >= g0 && c < g1) continue; // already in the lists
-                const PRec pr = T.prt[c];
-                const double d2 = knn_d2(X, Y, pr.x, pr.y);
-                if (__any(d2 < h[KC - 1])) knn_insert<KC>(h, d2);
+        bool push = false;
+        uint64_t todo = __ballot(keep);
+        while (todo) {
+            const int u = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            const double h = knn_bcast(hs, u);
+            const double dx = fmax(fabs(X - knn_bcast(cx, u)) - h, 0.0), dy = fmax(fabs(Y - knn_bcast(cy, u)) - h, 0.0);
+            if (!__any(valid && dx * dx + dy * dy < L.bound())) continue;
+            if (!__builtin_amdgcn_readlane(leaf, u)) {
+                push = push || lane == u;
+                continue;
+            }
+            const int lb = __builtin_amdgcn_readlane(beg, u), le = __builtin_amdgcn_readlane(end, u);
+            for (int base = lb; base < le; base += kWave) { // (a leaf at the depth cap may exceed 64)
+                const int p = base + lane;
+                const bool in = p < le;
+                double px = 0.0, py = 0.0;
+                if (in) {
+                    px = T.prt[p].x;
+                    py = T.prt[p].y;
+                }
+                const double ex = fmax(fmax(gx0 - px, px - gx1), 0.0), ey = fmax(fmax(gy0 - py, py - gy1), 0.0);
+                uint64_t near = __ballot(in && (ex * ex + ey * ey) * (1.0 - 1e-12) < far);
+                while (near) {
+                    const int v = __ffsll((unsigned long long)near) - 1;
+                    near &= near - 1;
+                    const int q = base + v;
+                    const bool seen = q - j <= k && j - q <= k; // already in this lane's list, or itself
+                    const double d2 = knn_d2(X, Y, knn_bcast(px, v), knn_bcast(py, v));
+                    L.offer(seen ? INFINITY : d2);
+                }
             }
         }
-        cur = cur + 1;
+        const int kid[4] = {kc.x, kc.y, kc.z, kc.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool on = push && kid[u] >= 0;
+            const uint64_t kb = __ballot(on);
+            if (on) stk[top + knn_rank(kb)] = kid[u];
+            top += __popcll(kb);
+        }
+        wave_lds_sync();
     }
-    if (valid) s_out[T.perm[j]] = sqrt(h[KC - 1]);
+    L.flush();
+    if (valid) s_out[T.perm[j]] = sqrt(L.bound());
 }
 
 } // namespace

@@ -12,11 +12,12 @@
 // node (level, j) covers particles [j B F^level, (j + 1) B F^level).
 //
 // One wavefront serves 64 consecutive particles of a segment (one per lane):
-// each lane keeps the k smallest squared distances in an ascending register
-// list of capacity KC >= k padded with -inf, seeded with the group's own
-// particles; the wave then walks the hierarchy depth first (stackless, the
-// next node follows from (level, j) arithmetically), entering a node if some
-// lane's distance to its box is below that lane's current k-th distance.
+// each lane keeps the k smallest squared distances (knn_list.hpp), seeded with
+// its k neighbours on either side along the sorted order (with only the group's
+// own particles, lanes beyond a jump of the curve had no useful bound); the wave
+// then walks the hierarchy (the children of node (level, j) follow
+// arithmetically), entering a node if some lane's distance to its box is below
+// that lane's current k-th distance.
 // Squared distances are FP64, (dx^2 + dy^2) + dz^2 without contraction, so
 // the result is the k-th smallest FP64 squared distance of the definition.
 #include <math.h>
@@ -25,6 +26,7 @@
 #include <vector>
 
 #include "build.hpp"
+#include "knn_list.hpp"
 
 namespace glm {
 
@@ -248,15 +250,6 @@ __global__ __launch_bounds__(kBlock) void k_bvh_level(Bvh B, int l)
     }
 }
 
-// Insert v into the ascending list h (the largest entry drops out).
-template <int KC>
-__device__ inline void knn3_insert(double (&h)[KC], double v)
-{
-#pragma unroll
-    for (int i = KC - 1; i > 0; --i) h[i] = fmax(h[i - 1], fmin(v, h[i]));
-    h[0] = fmin(v, h[0]);
-}
-
 template <bool D3>
 __device__ inline double knn3_d2(double X, double Y, double Z, double px, double py, double pz)
 {
@@ -270,6 +263,9 @@ __device__ inline double knn3_d2(double X, double Y, double Z, double px, double
     return r2;
 }
 
+constexpr int kBvhStack = 576;
+constexpr int kNodeBits = 27; // 2^31 particles make 2^26 buckets
+
 // One segment: particles [0, ns) of the sorted arrays (already offset to the
 // segment); perm maps them to their original index.
 template <int KC, bool D3>
@@ -281,64 +277,108 @@ __global__ __launch_bounds__(kBlock) void k_knn_bvh(const double* __restrict__ x
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int g0 = (blockIdx.x * (kBlock / kWave) + w) * kWave;
     if (g0 >= ns) return;
-    const int g1 = min(ns, g0 + kWave);
     const int j = g0 + lane;
     const bool valid = j < ns;
     const int jj = valid ? j : g0;
     const double X = xs[jj], Y = ys[jj], Z = D3 ? zs[jj] : 0.0;
-    double h[KC];
-#pragma unroll
-    for (int i = 0; i < KC; ++i) h[i] = i < KC - k ? -INFINITY : INFINITY;
+    __shared__ double lds[kBlock / kWave][kKnnQueue * kWave];
+    __shared__ int stack[kBlock / kWave][kBvhStack];
+    constexpr int NA = D3 ? 3 : 2;
+    KnnList<KC> L(k, lds[w], lane);
 
-    for (int c = g0; c < g1; ++c) {
-        const double d2 = knn3_d2<D3>(X, Y, Z, xs[c], ys[c], D3 ? zs[c] : 0.0);
-        knn3_insert<KC>(h, c == j ? INFINITY : d2);
+    // each lane's k neighbours along the sorted order on either side first
+    for (int o = 1; o <= k; ++o) {
+        const int a = jj - o, b = jj + o;
+        const int ca = a >= 0 ? a : 0, cb = b < ns ? b : 0;
+        const double da = knn3_d2<D3>(X, Y, Z, xs[ca], ys[ca], D3 ? zs[ca] : 0.0);
+        const double db = knn3_d2<D3>(X, Y, Z, xs[cb], ys[cb], D3 ? zs[cb] : 0.0);
+        L.insert(a >= 0 ? da : INFINITY);
+        L.insert(b < ns ? db : INFINITY);
     }
 
-    const int top = B.top;
-    int l = top, nj = 0;
-    for (;;) {
-        l = __builtin_amdgcn_readfirstlane(l);
-        nj = __builtin_amdgcn_readfirstlane(nj);
+    // bounding box of the wavefront's particles (idle lanes: particle g0)
+    double g0c[3], g1c[3];
+    const double me[3] = {X, Y, Z};
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+        g0c[a] = wave_min(me[a]);
+        g1c[a] = wave_max(me[a]);
+    }
+    int* stk = stack[w];
+    int top = 1;
+    if (lane == 0) stk[0] = B.top << kNodeBits; // the root: node 0 of the top level
+    wave_lds_sync();
+    while (top > 0) {
+        top = __builtin_amdgcn_readfirstlane(top);
+        const int m = knn_take(top, kBvhStack, kFan, kMaxLevels);
+        top -= m;
+        const bool has = lane < m;
+        const int it = has ? stk[top + lane] : 0;
+        const int l = it >> kNodeBits, nj = it & ((1 << kNodeBits) - 1);
         const int o = B.off[l] + nj;
-        double dx = fmax(fmax(B.lo[0][o] - X, X - B.hi[0][o]), 0.0);
-        double dy = fmax(fmax(B.lo[1][o] - Y, Y - B.hi[1][o]), 0.0);
-        double bd = dx * dx + dy * dy;
-        if (D3) {
-            const double dz = fmax(fmax(B.lo[2][o] - Z, Z - B.hi[2][o]), 0.0);
-            bd += dz * dz;
+        double lo[3], hi[3];
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+            lo[a] = B.lo[a][o];
+            hi[a] = B.hi[a][o];
         }
-        const bool need = valid && bd < h[KC - 1];
-        if (__any(need)) {
-            if (l > 0) { // first child
-                --l;
-                nj *= kFan;
+        const double far = wave_max(valid ? L.bound() : 0.0);
+        double gd = 0.0;
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+            const double d = fmax(fmax(lo[a] - g1c[a], g0c[a] - hi[a]), 0.0);
+            gd += d * d;
+        }
+        bool push = false;
+        uint64_t todo = __ballot(has && gd < far);
+        while (todo) {
+            const int u = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            double bd = 0.0;
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+                const double d = fmax(fmax(knn_bcast(lo[a], u) - me[a], me[a] - knn_bcast(hi[a], u)), 0.0);
+                bd += d * d;
+            }
+            if (!__any(valid && bd < L.bound())) continue;
+            if (__builtin_amdgcn_readlane(l, u) > 0) {
+                push = push || lane == u;
                 continue;
             }
-            const int c0 = nj * kBucket, c1 = min(ns, c0 + kBucket);
-            for (int c = c0; c < c1; ++c) {
-                if (c >= g0 && c < g1) continue; // already in the lists
-                const double d2 = knn3_d2<D3>(X, Y, Z, xs[c], ys[c], D3 ? zs[c] : 0.0);
-                if (__any(d2 < h[KC - 1])) knn3_insert<KC>(h, d2);
+            // the bucket's particles, one per lane
+            const int c0 = __builtin_amdgcn_readlane(nj, u) * kBucket;
+            const int c = c0 + lane;
+            const bool in = lane < kBucket && c < ns;
+            const double p[3] = {in ? xs[c] : 0.0, in ? ys[c] : 0.0, D3 && in ? zs[c] : 0.0};
+            double pd = 0.0;
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+                const double d = fmax(fmax(g0c[a] - p[a], p[a] - g1c[a]), 0.0);
+                pd += d * d;
+            }
+            uint64_t near = __ballot(in && pd * (1.0 - 1e-12) < far);
+            while (near) {
+                const int v = __ffsll((unsigned long long)near) - 1;
+                near &= near - 1;
+                const int q = c0 + v;
+                const bool seen = q - jj <= k && jj - q <= k; // already in this lane's list, or itself
+                const double d2 = knn3_d2<D3>(X, Y, Z, knn_bcast(p[0], v), knn_bcast(p[1], v), D3 ? knn_bcast(p[2], v) : 0.0);
+                L.offer(seen ? INFINITY : d2);
             }
         }
-        // next node in depth-first order: the next sibling, else up
-        bool done = false;
-        for (;;) {
-            if (l == top) {
-                done = true;
-                break;
-            }
-            if ((nj % kFan) != kFan - 1 && nj + 1 < B.cnt[l]) {
-                ++nj;
-                break;
-            }
-            nj /= kFan;
-            ++l;
+        // children, kFan at most: (l - 1, kFan nj ..)
+        const int first = nj * kFan;
+        const int nkid = push ? min(kFan, B.cnt[l > 0 ? l - 1 : 0] - first) : 0;
+#pragma unroll
+        for (int u = 0; u < kFan; ++u) {
+            const uint64_t kb = __ballot(u < nkid);
+            if (u < nkid) stk[top + knn_rank(kb)] = ((l - 1) << kNodeBits) | (first + u);
+            top += __popcll(kb);
         }
-        if (done) break;
+        wave_lds_sync();
     }
-    if (valid) s_out[perm[j]] = sqrt(h[KC - 1]);
+    L.flush();
+    if (valid) s_out[perm[j]] = sqrt(L.bound());
 }
 
 struct KnnLayout {

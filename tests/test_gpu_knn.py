@@ -158,3 +158,34 @@ def test_knn_positions_invalid():
     z2[17] = np.nan
     with pytest.raises(g.GlamerError, match="NaN"):
         gpu_knn_pos(x, y, 4, z=z2)
+
+
+@pytest.mark.parametrize("n,k", [(2, 1), (33, 32), (64, 16), (65, 17), (66, 64), (129, 33), (1000, 1), (1000, 64),
+                                 (4097, 32)])
+def test_smoothing_lengths_at_list_and_wavefront_edges(n, k):
+    """Particle counts around a wavefront, k around the list capacities (16, 32,
+    64), with tight clumps, a hundred coincident particles (a leaf at the depth
+    cap) and a few far outliers: the k-th neighbour distance exactly, in 2D on
+    the quad-tree and in 2D and 3D on the bounding-box hierarchy."""
+    gen = synth.rng(900 + n + k)
+    p = gen.uniform(-0.5, 0.5, (n, 3))
+    if n > 500:
+        p[: n // 3] = 1e-3 * gen.normal(size=(n // 3, 3)) + 0.25
+        p[n // 3: n // 3 + 100] = p[0]
+        p[-3:] = 40.0 * p[-3:]
+    say(f"[gpu] knn edges n={n} k={k}")
+
+    def brute(q):
+        out = np.empty(n)
+        for i in range(n):
+            d = q - q[i]
+            r2 = d[:, 0] * d[:, 0] + d[:, 1] * d[:, 1]
+            if q.shape[1] == 3:
+                r2 = r2 + d[:, 2] * d[:, 2]
+            out[i] = np.sqrt(np.sort(np.delete(r2, i))[k - 1])
+        return out
+
+    ref2, ref3 = brute(p[:, :2]), brute(p)
+    np.testing.assert_array_equal(gpu_knn(p[:, 0], p[:, 1], k), ref2)
+    np.testing.assert_array_equal(gpu_knn_pos(p[:, 0], p[:, 1], k), ref2)
+    np.testing.assert_array_equal(gpu_knn_pos(p[:, 0], p[:, 1], k, z=p[:, 2]), ref3)

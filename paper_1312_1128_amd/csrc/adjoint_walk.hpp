@@ -67,6 +67,19 @@ __device__ inline void kg_grad(const Cot& cg, float f1, float f2, float ir2, flo
     *e2 = 2.0f * (cg.k * dk * f2 + cg.h1 * f2 * fmaf(b, c, -a) + cg.h2 * f1 * fmaf(b, 1.0f - c, a));
 }
 
+// Point-mass terms of one particle (Sec. 3.5): alpha = m d / r^2 and
+// gamma = -(m / r^2) (cos 2phi, sin 2phi).
+__device__ inline void point_terms(float m, float f1, float f2, float ir2, float* P)
+{
+#pragma clang fp contract(off)
+    const float pm = m * ir2;
+    const float c2 = (f1 * f1 - f2 * f2) * ir2, s2 = (2.0f * f1 * f2) * ir2;
+    P[0] = pm * f1;
+    P[1] = pm * f2;
+    P[2] = -(pm * c2);
+    P[3] = -(pm * s2);
+}
+
 // Gradient terms of one particle for this lane, per the same cases as the
 // forward's leaf_particle and list_particle.  Returns FP64 (m, x, y, s) contributions in G.
 // mode 0: leaf sum; mode 1: big-particle correction (Gaussian - point).

@@ -89,6 +89,7 @@ __global__ __launch_bounds__(kWave* dir_waves(RB)) void k_direct32(const double*
         for (int k = w * SUB; k < cnt; k += kDirWaves * SUB)
             leaf_particle<AONLY, true, false, KIND>(tile[k + lane / RB], X, Y, A);
     }
+    if constexpr (!AONLY) join_shear(A);
     double v[5] = {alpha1(A), alpha2(A), A.k, A.g1, A.g2};
     if (!direct_sum<RB, NV>(v, reinterpret_cast<double*>(lds)) || r >= nr) return;
     a1[r] = (float)v[0];

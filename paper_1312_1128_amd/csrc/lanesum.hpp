@@ -23,27 +23,30 @@ __device__ inline float row_peer(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
 
-// One halving step inside the rows: the M words of each lane become ceil(M / 2).
-// Partner lanes (as DPP control CTRL pairs them) keep opposite words of each
-// pair (hi: the second) and add the partner's copy; an odd last word is summed
-// over both partners, who then hold the same total.
-template <int M, int CTRL>
-__device__ inline void row_halve(float* v, bool hi)
-{
-    constexpr int NP = M / 2;
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        const float keep = hi ? v[2 * p + 1] : v[2 * p];
-        const float send = hi ? v[2 * p] : v[2 * p + 1];
-        v[p] = keep + row_peer<CTRL>(send);
-    }
-    if constexpr ((M & 1) != 0) v[NP] = v[M - 1] + row_peer<CTRL>(v[M - 1]);
-}
-
 // The halving steps inside a row pair lane j with j ^ 8 (row_ror:8), with
 // 7 - j inside its 8-lane half (row_half_mirror), then with j ^ 2 and j ^ 1
 // (quad_perm); lane bit 3, 2, 1, 0 in turn picks the word kept.
 constexpr int kRowStep[4] = {0x128, 0x141, 0x04E, 0x0B1};
+constexpr uint64_t kRowHigh[4] = {0xFF00FF00FF00FF00ull, 0xF0F0F0F0F0F0F0F0ull, 0xCCCCCCCCCCCCCCCCull,
+                                  0xAAAAAAAAAAAAAAAAull}; // lanes with that bit set
+
+// One halving step inside the rows: the M words of each lane become ceil(M / 2).
+// Partner lanes (as step STEP pairs them) keep opposite words of each
+// pair (those with the lane bit set: the second) and add the partner's copy; an odd last word is summed
+// over both partners, who then hold the same total.
+template <int M, int STEP>
+__device__ inline void row_halve(float* v)
+{
+    constexpr int CTRL = kRowStep[STEP];
+    constexpr int NP = M / 2;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        float keep, send;
+        pick_pair(kRowHigh[STEP], v[2 * p], v[2 * p + 1], keep, send);
+        v[p] = keep + row_peer<CTRL>(send);
+    }
+    if constexpr ((M & 1) != 0) v[NP] = v[M - 1] + row_peer<CTRL>(v[M - 1]);
+}
 
 // Totals over the wavefront of NA per-lane words (NA even), by recursive
 // halving across the lanes, in registers.  The 32-lane halves swap the half of
@@ -78,11 +81,10 @@ __device__ inline float word_totals(const float* a)
         const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[k]), __float_as_uint(hi), false, false);
         c[k] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
-    const int j = (int)__lane_id() & 15;
-    row_halve<Q, kRowStep[0]>(c, (j >> 3) & 1);
-    row_halve<M2, kRowStep[1]>(c, (j >> 2) & 1);
-    row_halve<M3, kRowStep[2]>(c, (j >> 1) & 1);
-    row_halve<M4, kRowStep[3]>(c, j & 1);
+    row_halve<Q, 0>(c);
+    row_halve<M2, 1>(c);
+    row_halve<M3, 2>(c);
+    row_halve<M4, 3>(c);
     return c[0];
 }
 
@@ -136,14 +138,15 @@ __device__ inline double row_peer64(double v)
     return __hiloint2double(hi, lo);
 }
 
-template <int M, int CTRL>
-__device__ inline void row_halve64(double* v, bool hi)
+template <int M, int STEP>
+__device__ inline void row_halve64(double* v)
 {
+    constexpr int CTRL = kRowStep[STEP];
     constexpr int NP = M / 2;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        const double keep = hi ? v[2 * p + 1] : v[2 * p];
-        const double send = hi ? v[2 * p] : v[2 * p + 1];
+        double keep, send;
+        pick_pair(kRowHigh[STEP], v[2 * p], v[2 * p + 1], keep, send);
         v[p] = keep + row_peer64<CTRL>(send);
     }
     if constexpr ((M & 1) != 0) v[NP] = v[M - 1] + row_peer64<CTRL>(v[M - 1]);
@@ -174,11 +177,10 @@ __device__ inline double word_totals64(const float* a)
                                                         false, false);
         c[k] = lane_pair(l[0], h[0]) + lane_pair(l[1], h[1]);
     }
-    const int j = (int)__lane_id() & 15;
-    row_halve64<Q, kRowStep[0]>(c, (j >> 3) & 1);
-    row_halve64<M2, kRowStep[1]>(c, (j >> 2) & 1);
-    row_halve64<M3, kRowStep[2]>(c, (j >> 1) & 1);
-    row_halve64<M4, kRowStep[3]>(c, j & 1);
+    row_halve64<Q, 0>(c);
+    row_halve64<M2, 1>(c);
+    row_halve64<M3, 2>(c);
+    row_halve64<M4, 3>(c);
     return c[0];
 }
 

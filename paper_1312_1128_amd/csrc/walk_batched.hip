@@ -45,6 +45,7 @@ __global__ __launch_bounds__(kBlock) void k_walk_batched(const BatchLens* __rest
             v.finish(words);
             wave_lds_sync(); // the next item's stack overwrites the words
         }
+        if constexpr (!AONLY) join_shear(v.A);
         if (valid) write_out<AONLY, false>(v.A, v.cnt, (int64_t)perm[gi] - B.ray_off, B.out);
     }
 }

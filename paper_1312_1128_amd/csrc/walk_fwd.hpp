@@ -178,6 +178,7 @@ __global__ __launch_bounds__(kWave, 6) void k_walk(TreeDev T, const double* __re
         wave_lds_sync();
         v.finish(words);
     }
+    if constexpr (!AONLY) join_shear(v.A);
     if (valid) write_out<AONLY, false, PSI>(v.A, v.cnt, rperm ? (int64_t)rperm[r] : r, out);
 }
 
@@ -215,6 +216,7 @@ __global__ __launch_bounds__(kWave* kMaxGroupWaves, 5) void k_walk_coop(TreeDev 
     FwdVisitor<P, AONLY, MODE, PSI, KIND, FAR> v(T, g, X, Y, lane, valid);
     traverse<true>(T, v, g, X, Y, lane, w, W, coop_lds(lds, W));
     Acc& A = v.A;
+    if constexpr (!AONLY) join_shear(A);
     __syncthreads(); // the traversal's LDS is free
     double* sums = reinterpret_cast<double*>(lds);
     if (FAR && g.far) { // the wavefronts' local expansions, summed into one

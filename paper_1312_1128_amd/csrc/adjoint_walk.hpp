@@ -22,14 +22,13 @@
 //   d kappa / d d_j = 2 (dkappa/du) d_j,
 //   d gamma1/d d1 = 2 d1 (b c + a), d gamma1/d d2 = 2 d2 (b c - a),
 //   d gamma2/d d1 = 2 d2 (b (1 + c) + a), d gamma2/d d2 = 2 d1 (b (1 - c) + a),  c = cos 2phi;
-// for the Gaussian a = -m h^2 (Gam-series / x) (no cancellation at small x = h u),
-// dkappa/du = -h kappa, d kappa/ds - dA/ds = m e^-x x / (C s^3).
+// dkappa/du = -h kappa and d kappa/ds - dA/ds = m e^-x x / (C s^3) for the Gaussian (x = h u).
 // A push-down pass gives every particle its share through
 //   dQ_k/dm_i = d^k - k Q_{k-1} d / M,  dQ_k/dz_i = k m_i d^(k-1) - k Q_{k-1} m_i / M,
 //   dz_cm/dm_i = d / M,  dz_cm/dz_i = m_i / M  (d = z_i - z_cm; all holomorphic).
 // Per-lane terms are reduced across the wavefront before one FP64 atomic per
-// quantity; the point-mass parts of big-particle pairs are reduced in FP64 so
-// that they cancel like the forward's balance.
+// quantity; the particles' terms are formed and reduced in FP64, so that the
+// point-mass parts of big-particle pairs cancel like the forward's balance.
 #pragma once
 
 #include <type_traits>
@@ -52,159 +51,105 @@ struct Cot {
     float g1, g2, k, h1, h2;
 };
 
-// kappa and gamma part of a term's gradient, per unit mass (m, then d/d d1,
-// d/d d2 of L, the s part separately): kap = kappa, Am = A = alpha / d,
-// dk = dkappa/du, a = (kappa - A) / u.
-__device__ inline void kg_grad(const Cot& cg, float f1, float f2, float ir2, float kap, float a, float dk, float* em,
-                               float* e1, float* e2)
+// Gradient words of one particle for this lane, from its profile in unit mass: A, G = A - kappa, K =
+// kappa and R = u dkappa/du (u = r^2), ird = 1 / u, offset d, w1 = d1^2 - d2^2, w2 = d1 d2.  With
+// J = h1 cos 2phi + h2 sin 2phi,
+//   W0 = A (g . d) + k K - G J                                            dL/dm,
+//   W1 = [G (g1 w1 + 2 g2 w2) - 2 (d1 V - G (h1 d1 + h2 d2))] / u - K g1  dL/dx / m,
+//   W2 = [G (2 g1 w2 - g2 w1) - 2 (d2 V - G (h2 d1 - h1 d2))] / u - K g2  dL/dy / m,
+//   W3 = K (g . d) + k (K + R) + J R,     V = k R + (R + 2 G) J           dL/ds / (-m c),
+// c as in word_factor: the a, b and dkappa/du of the file's head times u, so that nothing divides by
+// u twice.  All of it is linear in (A, G, K, R): a big-particle
+// correction takes the point mass off A and G, and its words then cancel those of the leaf to FP64
+// rounding.  FP64 throughout: an FP64 FMA issues like an FP32 one here, and the widened cotangents
+// and squares are shared by the four words; the factors that a particle's rays have in common
+// (m, -m c) are left to after the sum over the rays.
+template <bool KG>
+__device__ inline void grad_words(const Cot& cg, double d1, double d2, double w1, double w2, double ird, double A,
+                                  double G, double K, double R, double* W)
 {
-    const float c = (f1 * f1 - f2 * f2) * ir2, sn = 2.0f * f1 * f2 * ir2;
-    const float b = dk - 2.0f * a;
-    const float u = (f1 * f1 + f2 * f2);
-    // gamma1 = a (d1^2 - d2^2) = a u c, gamma2 = a u sn
-    *em = cg.k * kap + (cg.h1 * c + cg.h2 * sn) * (a * u);
-    *e1 = 2.0f * (cg.k * dk * f1 + cg.h1 * f1 * fmaf(b, c, a) + cg.h2 * f2 * fmaf(b, 1.0f + c, a));
-    *e2 = 2.0f * (cg.k * dk * f2 + cg.h1 * f2 * fmaf(b, c, -a) + cg.h2 * f1 * fmaf(b, 1.0f - c, a));
-}
-
-// Point-mass terms of one particle (Sec. 3.5): alpha = m d / r^2 and
-// gamma = -(m / r^2) (cos 2phi, sin 2phi).
-__device__ inline void point_terms(float m, float f1, float f2, float ir2, float* P)
-{
-#pragma clang fp contract(off)
-    const float pm = m * ir2;
-    const float c2 = (f1 * f1 - f2 * f2) * ir2, s2 = (2.0f * f1 * f2) * ir2;
-    P[0] = pm * f1;
-    P[1] = pm * f2;
-    P[2] = -(pm * c2);
-    P[3] = -(pm * s2);
-}
-
-// Gradient terms of one particle for this lane, per the same cases as the
-// forward's leaf_particle and list_particle.  Returns FP64 (m, x, y, s) contributions in G.
-// mode 0: leaf sum; mode 1: big-particle correction (Gaussian - point).
-template <bool KG, int KIND>
-__device__ inline bool particle_grad(const PRec& pr, double X, double Y, int mode, bool act, const Cot& cg,
-                                     float invC, double G[4])
-{
-    G[0] = G[1] = G[2] = G[3] = 0.0;
-    if (!act) return false;
-    const float g1 = cg.g1, g2 = cg.g2;
-    double d1, d2;
-    const double r2 = sqdist(X, Y, pr.x, pr.y, &d1, &d2);
-    const bool inside = r2 < pr.qs2;
-    const bool listed = (pr.meta >> 31) != 0;
-    if (mode == 1 && !inside) return false;
-    const float f1 = (float)d1, f2 = (float)d2, r2f = (float)r2;
-    const float ir2 = r2f > 0.0f ? __builtin_amdgcn_rcpf(r2f) : 0.0f;
-    const float gd = g1 * f1 + g2 * f2;
-    // point mass, per unit mass: alpha = d / r^2, gamma = -(cos 2phi, sin 2phi) / r^2, kappa = 0
-    float P[4];
-    point_terms(1.0f, f1, f2, ir2, P);
-    float pm_m = g1 * P[0] + g2 * P[1];
-    float pm_x = -(g1 * P[2] + g2 * P[3]) * pr.m;
-    float pm_y = -(g1 * P[3] - g2 * P[2]) * pr.m;
+    const double g1 = (double)cg.g1, g2 = (double)cg.g2, t2 = w2 + w2;
+    const double gd = fma(g1, d1, g2 * d2);
+    double n1 = fma(g1, w1, g2 * t2), n2 = fma(g1, t2, -g2 * w1);
+    W[0] = A * gd;
+    W[3] = K * gd;
     if constexpr (KG) {
-        // point mass: kappa = 0, A = 1/u, a = -1/u^2, dkappa/du = 0
-        float km, k1, k2;
-        kg_grad(cg, f1, f2, ir2, 0.0f, -(ir2 * ir2), 0.0f, &km, &k1, &k2);
-        pm_m += km;
-        pm_x -= k1 * pr.m;
-        pm_y -= k2 * pr.m;
+        const double k = (double)cg.k, h1 = (double)cg.h1, h2 = (double)cg.h2;
+        const double J = fma(h1, w1, h2 * t2) * ird;
+        const double V = -2.0 * fma(k, R, fma(2.0, G, R) * J);
+        W[0] += fma(k, K, -G * J);
+        W[3] += fma(k, K + R, J * R);
+        n1 = fma(2.0, fma(h1, d1, h2 * d2), n1);
+        n2 = fma(2.0, fma(h2, d1, -h1 * d2), n2);
+        W[1] = fma(fma(G, n1, d1 * V), ird, -K * g1);
+        W[2] = fma(fma(G, n2, d2 * V), ird, -K * g2);
+    } else {
+        const double t = G * ird;
+        W[1] = fma(t, n1, -K * g1);
+        W[2] = fma(t, n2, -K * g2);
     }
-    const bool gauss = inside && !(mode == 0 && listed);
-    if (!gauss) { // point mass (a listed+inside point pairs with the list box's -point)
-        G[0] = (double)pm_m;
-        G[1] = (double)pm_x;
-        G[2] = (double)pm_y;
-        return true;
+}
+
+// Words of one particle, by the same cases as the forward's leaf_particle (mode 0) and
+// list_particle (mode 1: Gaussian - point inside the support, nothing outside).
+template <bool KG, int KIND>
+__device__ inline void particle_grad(const PRec& pr, double X, double Y, int mode, const Cot& cg, float invC, double* W)
+{
+    double d1, d2, w1, w2;
+    const double r2 = sqdist_angles(X, Y, pr.x, pr.y, &d1, &d2, &w1, &w2);
+    const float r2f = (float)r2;
+    // 1 / r^2, finite: at r = 0 every word it enters has a factor 0
+    const float ir2 = fminf(__builtin_amdgcn_rcpf(r2f), 3.402823466e38f);
+    const double ird = (double)ir2;
+    const bool inside = r2 < pr.qs2;
+    if (mode == 0) {
+        if ((pr.meta >> 31) != 0 || !__any(inside)) { // a listed particle is a point mass here
+            grad_words<KG>(cg, d1, d2, w1, w2, ird, ird, ird, 0.0, 0.0, W);
+            return;
+        }
+    } else {
+        W[0] = W[1] = W[2] = W[3] = 0.0;
+        if (!inside) return;
     }
-    const float c2 = (f1 * f1 - f2 * f2) * ir2, s2 = 2.0f * f1 * f2 * ir2;
+    // per unit mass (invC = 1 / C, or 1 / g(c)): the factors of profile_terms without m
+    float A, G, K, R;
     if constexpr (KIND == kKindNfw) {
-        // truncated NFW halo per unit mass (invC = 1/g(c), h = c/R): A = h^2 g/x^2 / g(c),
-        // kappa = h^2 f / (2 g(c)); size derivatives of a scale family: d alpha/dR = -(2 kappa/R) d,
-        // d kappa/dR = -2 (kappa + u dkappa/du)/R, d(kappa - A)/dR = -2 u dkappa/du / R
         const double x2 = r2 * ((double)pr.h * (double)pr.h);
         float gx2, f, dfde;
         nfw_shape32((float)x2, (float)(x2 - 1.0), &gx2, &f, &dfde);
         const float hh2 = (invC * pr.h) * pr.h;
-        const float Au = hh2 * gx2;
-        const float Ku = r2 > 0.0 ? 0.5f * hh2 * f : 0.0f;
-        const float Gu = Au - Ku;
-        const float iR = __builtin_amdgcn_rsqf((float)pr.qs2);
-        const float ga1 = -Gu * c2, ga2 = -Gu * s2;
-        float em = Au * gd;
-        float ex = -(g1 * (Ku + ga1) + g2 * ga2) * pr.m;
-        float ey = -(g1 * ga2 + g2 * (Ku - ga1)) * pr.m;
-        float es = -pr.m * 2.0f * Ku * iR * gd;
-        if constexpr (KG) {
-            const float a = (Ku - Au) * ir2;
-            const float dk = r2 > 0.0 ? 0.5f * hh2 * (pr.h * pr.h) * dfde : 0.0f;
-            float km, k1, k2;
-            kg_grad(cg, f1, f2, ir2, Ku, a, dk, &km, &k1, &k2);
-            em += km;
-            ex -= k1 * pr.m;
-            ey -= k2 * pr.m;
-            const float ks = -2.0f * (Ku + r2f * dk) * iR, gs = -2.0f * r2f * dk * iR;
-            es += pr.m * (cg.k * ks + (cg.h1 * c2 + cg.h2 * s2) * gs);
-        }
-        if (mode == 1) {
-            G[0] = (double)em - (double)pm_m;
-            G[1] = (double)ex - (double)pm_x;
-            G[2] = (double)ey - (double)pm_y;
-        } else {
-            G[0] = (double)em;
-            G[1] = (double)ex;
-            G[2] = (double)ey;
-        }
-        G[3] = (double)es;
-        return true;
-    }
-    const float u = r2f * pr.h;
-    const float e = __expf(-u);
-    const float hu = invC * pr.h; // per unit mass m/C/(2 s^2)
-    float Au, Gu;
-    gauss_terms(u, e, ir2, invC, hu, &Au, &Gu);
-    const float Ku = hu * e;
-    const float ga1 = -Gu * c2, ga2 = -Gu * s2; // gamma per unit mass
-    float em = Au * gd;
-    float ex = -(g1 * (Ku + ga1) + g2 * ga2) * pr.m;
-    float ey = -(g1 * ga2 + g2 * (Ku - ga1)) * pr.m;
-    // d alpha / d s = -m d e^-u / (s^3 C), 1/s^3 = 2h sqrt(2h)
-    float es = -pr.m * hu * e * 2.0f * __builtin_sqrtf(2.0f * pr.h) * gd;
-    if constexpr (KG) {
-        // a = -Gam / u with Gam = hu * sd(x), x = u_gauss: a = -hu * h * sd(x) / x
-        float sdx;
-        if (u < 0.5f) {
-            sdx = 1.0f / 2 + u * (-1.0f / 3 + u * (1.0f / 8 + u * (-1.0f / 30 + u * (1.0f / 144 + u * (-1.0f / 840 + u * (1.0f / 5760 + u * (-1.0f / 45360 + u * (1.0f / 403200))))))));
-        } else {
-            const float iu = __builtin_amdgcn_rcpf(u);
-            sdx = ((1.0f - e) * iu - e) * iu;
-        }
-        const float a = -hu * pr.h * sdx;
-        const float dk = -pr.h * Ku;
-        float km, k1, k2;
-        kg_grad(cg, f1, f2, ir2, Ku, a, dk, &km, &k1, &k2);
-        em += km;
-        ex -= k1 * pr.m;
-        ey -= k2 * pr.m;
-        // d/ds: kappa_s and (kappa_s - A_s) = invC e x / s^3 (per unit mass)
-        const float is3 = 2.0f * pr.h * __builtin_sqrtf(2.0f * pr.h);
-        const float ks = invC * e * (u - 1.0f) * is3;
-        const float gs = invC * e * u * is3;
-        es += pr.m * (cg.k * ks + (cg.h1 * c2 + cg.h2 * s2) * gs);
-    }
-    if (mode == 1) {
-        G[0] = (double)em - (double)pm_m;
-        G[1] = (double)ex - (double)pm_x;
-        G[2] = (double)ey - (double)pm_y;
+        A = hh2 * gx2;
+        K = r2 > 0.0 ? 0.5f * hh2 * f : 0.0f;
+        G = A - K;
+        R = r2 > 0.0 ? r2f * (0.5f * hh2 * (pr.h * pr.h) * dfde) : 0.0f;
     } else {
-        G[0] = (double)em;
-        G[1] = (double)ex;
-        G[2] = (double)ey;
+        const float u = r2f * pr.h;
+        const float e = __expf(-u);
+        const float hu = invC * pr.h;
+        gauss_terms(u, e, ir2, invC, hu, &A, &G);
+        K = hu * e;
+        R = -u * K;
     }
-    G[3] = (double)es;
-    return true;
+    if (mode == 0) {
+        A = inside ? A : ir2;
+        G = inside ? G : ir2;
+        K = inside ? K : 0.0f;
+        R = inside ? R : 0.0f;
+        grad_words<KG>(cg, d1, d2, w1, w2, ird, (double)A, (double)G, (double)K, (double)R, W);
+    } else {
+        grad_words<KG>(cg, d1, d2, w1, w2, ird, (double)A - ird, (double)G - ird, (double)K, (double)R, W);
+    }
+}
+
+// What word w of a particle is multiplied by: dkappa/ds and d(kappa - A)/ds are -c (kappa + R) and
+// -c R of a profile that scales with its size, c = 2 / s (Gaussian: 2 sqrt(2 h)) or 2 / size.
+template <int KIND>
+__device__ inline double word_factor(const PRec& pr, int w)
+{
+    if (w == 0) return 1.0;
+    if (w < 3) return (double)pr.m;
+    const float c = KIND == kKindNfw ? 2.0f * __builtin_amdgcn_rsqf((float)pr.qs2) : 2.0f * __builtin_sqrtf(2.0f * pr.h);
+    return -(double)pr.m * (double)c;
 }
 
 // Position of the c-th set bit (from 0) of m, for c < popcount(m).
@@ -285,26 +230,21 @@ __device__ inline void particles_grad(const PRec* __restrict__ rec, uint64_t sel
         double A[4] = {0.0, 0.0, 0.0, 0.0};
         for (int t = 0; t < its; ++t) {
             const int s = g + G * t;
-            const bool act = g < G && s < nr;
-            const int ss = act ? s : 0;
-            Cot cr;
-            const float2 gg = tab.g[ss];
+            if (g >= G || s >= nr) continue;
+            Cot cr{};
+            const float2 gg = tab.g[s];
             cr.g1 = gg.x;
             cr.g2 = gg.y;
             if constexpr (KG) {
-                cr.k = tab.k[ss];
-                const float2 hh = tab.h[ss];
+                cr.k = tab.k[s];
+                const float2 hh = tab.h[s];
                 cr.h1 = hh.x;
                 cr.h2 = hh.y;
-            } else {
-                cr.k = cr.h1 = cr.h2 = 0.0f;
             }
-            double Gt[4];
-            particle_grad<KG, KIND>(pr, tab.x[ss], tab.y[ss], mode, act, cr, invC, Gt);
-            A[0] += Gt[0];
-            A[1] += Gt[1];
-            A[2] += Gt[2];
-            A[3] += Gt[3];
+            double Wt[4];
+            particle_grad<KG, KIND>(pr, tab.x[s], tab.y[s], mode, cr, invC, Wt);
+#pragma unroll
+            for (int w = 0; w < 4; ++w) A[w] += Wt[w];
         }
         // the G ray groups' sums meet in group 0 pairwise, in ceil(log2 G) rounds
         for (int st = 1; st < G; st <<= 1) {
@@ -320,7 +260,7 @@ __device__ inline void particles_grad(const PRec* __restrict__ rec, uint64_t sel
             double* dst = pg + 4 * (size_t)(pr.meta & 0x7fffffffu);
 #pragma unroll
             for (int w = 0; w < 4; ++w)
-                if (A[w] != 0.0) unsafeAtomicAdd(dst + w, A[w]);
+                if (A[w] != 0.0) unsafeAtomicAdd(dst + w, A[w] * word_factor<KIND>(pr, w));
         }
         for (int q = 0; q < C; ++q) sel &= sel - 1; // drop this pass's particles
     }
@@ -498,17 +438,23 @@ struct AdjVisitor {
         far_add<(P + 2) / 2, P + 2>(c, boxes, H, t1, t2, s1, s2);
     }
 
-    // One particle's gradient (m, x, y, s) over the rays `act`: per-ray terms in
+    // One particle's gradient (m, x, y, s) over the rays that `c` has cotangents of: per-ray words in
     // FP64, summed over the wavefront in registers (each 16-lane row ends with one of the
     // four words), one atomic instruction over the four adjacent words.
-    __device__ void particle(const PRec& pr, int mode, bool act)
+    __device__ void particle(const PRec& pr, int mode, const Cot& c)
     {
-        double G[4];
-        const bool some = particle_grad<KG, KIND>(pr, X, Y, mode, act, cg, T.invC, G);
-        if (!__any(some)) return;
-        const double t = row_word4(G);
+        double W[4];
+        particle_grad<KG, KIND>(pr, X, Y, mode, c, T.invC, W);
+        const double t = row_word4(W);
         if ((lane & 15) == 0 && t != 0.0)
-            unsafeAtomicAdd(pg + 4 * (size_t)(pr.meta & 0x7fffffffu) + (lane >> 4), t);
+            unsafeAtomicAdd(pg + 4 * (size_t)(pr.meta & 0x7fffffffu) + (lane >> 4), t * word_factor<KIND>(pr, lane >> 4));
+    }
+
+    // The cotangents of the rays in m (the other lanes' are zero).
+    __device__ Cot cot_of(uint64_t m) const
+    {
+        const bool on = lane_bit(m);
+        return Cot{on ? cg.g1 : 0.0f, on ? cg.g2 : 0.0f, on ? cg.k : 0.0f, on ? cg.h1 : 0.0f, on ? cg.h2 : 0.0f};
     }
 
     __device__ void leaf(int pbeg, int pend, uint64_t opn)
@@ -520,13 +466,13 @@ struct AdjVisitor {
                 particles_grad<KG, KIND>(T.prt + j, sel, 0, opn, X, Y, cg, T.invC, pg, lane, lds);
             }
         } else {
-            const bool act = lane_bit(opn);
+            const Cot c = cot_of(opn);
             PRec pr = uniform_ld(T.prt, pbeg);
             for (int j = pbeg; j < pend; ++j) {
                 int next = j + 1 < pend ? j + 1 : j;
                 settle(pr, next);
                 const PRec nx = uniform_ld(T.prt, next);
-                particle(pr, 0, act);
+                particle(pr, 0, c);
                 pr = nx;
             }
         }
@@ -534,7 +480,7 @@ struct AdjVisitor {
 
     __device__ void list(int lbeg, int lend, int stride, uint64_t actm)
     {
-        const bool act = lane_bit(actm);
+        const Cot c = PAIRS ? cg : cot_of(actm);
         for (int base = lbeg; base < lend; base += stride) {
             const int j = base + lane;
             bool cand = false;
@@ -555,7 +501,7 @@ struct AdjVisitor {
                     int next = base + __ffsll((unsigned long long)(rest ? rest : cm)) - 1;
                     settle(pr, next);
                     const PRec nx = uniform_ld(T.lst, next);
-                    particle(pr, 1, act);
+                    particle(pr, 1, c);
                     pr = nx;
                     cm = rest;
                 }

@@ -62,31 +62,41 @@ struct Cot {
 // u twice.  All of it is linear in (A, G, K, R): a big-particle
 // correction takes the point mass off A and G, and its words then cancel those of the leaf to FP64
 // rounding.  FP64 throughout: an FP64 FMA issues like an FP32 one here, and the widened cotangents
-// and squares are shared by the four words; the factors that a particle's rays have in common
+// and squares are shared by the four words (POINT: K = R = 0); the factors that a particle's rays have in common
 // (m, -m c) are left to after the sum over the rays.
-template <bool KG>
+template <bool KG, bool POINT>
 __device__ inline void grad_words(const Cot& cg, double d1, double d2, double w1, double w2, double ird, double A,
                                   double G, double K, double R, double* W)
 {
     const double g1 = (double)cg.g1, g2 = (double)cg.g2, t2 = w2 + w2;
     const double gd = fma(g1, d1, g2 * d2);
-    double n1 = fma(g1, w1, g2 * t2), n2 = fma(g1, t2, -g2 * w1);
+    double n1 = fma(g1, w1, g2 * t2), n2 = fma(g1, t2, -g2 * w1), t = G * ird;
     W[0] = A * gd;
-    W[3] = K * gd;
+    W[3] = POINT ? 0.0 : K * gd;
     if constexpr (KG) {
         const double k = (double)cg.k, h1 = (double)cg.h1, h2 = (double)cg.h2;
         const double J = fma(h1, w1, h2 * t2) * ird;
-        const double V = -2.0 * fma(k, R, fma(2.0, G, R) * J);
-        W[0] += fma(k, K, -G * J);
-        W[3] += fma(k, K + R, J * R);
+        double V;
+        if constexpr (POINT) {
+            W[0] = fma(-G, J, W[0]);
+            V = 2.0 * G * J;
+        } else {
+            W[0] += fma(k, K, -G * J);
+            W[3] += fma(k, K + R, J * R);
+            V = fma(k, R, fma(2.0, G, R) * J);
+        }
         n1 = fma(2.0, fma(h1, d1, h2 * d2), n1);
         n2 = fma(2.0, fma(h2, d1, -h1 * d2), n2);
-        W[1] = fma(fma(G, n1, d1 * V), ird, -K * g1);
-        W[2] = fma(fma(G, n2, d2 * V), ird, -K * g2);
+        V *= -2.0 * ird;
+        W[1] = fma(t, n1, d1 * V);
+        W[2] = fma(t, n2, d2 * V);
     } else {
-        const double t = G * ird;
-        W[1] = fma(t, n1, -K * g1);
-        W[2] = fma(t, n2, -K * g2);
+        W[1] = t * n1;
+        W[2] = t * n2;
+    }
+    if constexpr (!POINT) {
+        W[1] = fma(-K, g1, W[1]);
+        W[2] = fma(-K, g2, W[2]);
     }
 }
 
@@ -104,7 +114,7 @@ __device__ inline void particle_grad(const PRec& pr, double X, double Y, int mod
     const bool inside = r2 < pr.qs2;
     if (mode == 0) {
         if ((pr.meta >> 31) != 0 || !__any(inside)) { // a listed particle is a point mass here
-            grad_words<KG>(cg, d1, d2, w1, w2, ird, ird, ird, 0.0, 0.0, W);
+            grad_words<KG, true>(cg, d1, d2, w1, w2, ird, ird, ird, 0.0, 0.0, W);
             return;
         }
     } else {
@@ -135,9 +145,9 @@ __device__ inline void particle_grad(const PRec& pr, double X, double Y, int mod
         G = inside ? G : ir2;
         K = inside ? K : 0.0f;
         R = inside ? R : 0.0f;
-        grad_words<KG>(cg, d1, d2, w1, w2, ird, (double)A, (double)G, (double)K, (double)R, W);
+        grad_words<KG, false>(cg, d1, d2, w1, w2, ird, (double)A, (double)G, (double)K, (double)R, W);
     } else {
-        grad_words<KG>(cg, d1, d2, w1, w2, ird, (double)A - ird, (double)G - ird, (double)K, (double)R, W);
+        grad_words<KG, false>(cg, d1, d2, w1, w2, ird, (double)A - ird, (double)G - ird, (double)K, (double)R, W);
     }
 }
 

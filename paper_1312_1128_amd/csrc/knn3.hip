@@ -105,16 +105,19 @@ __global__ __launch_bounds__(kBlock) void k_knn_bbox(const double* __restrict__ 
 }
 
 // Cube over the bounding box; quantisation to `bits` bits per axis.
-__global__ __launch_bounds__(kBlock) void k_knn_root(const double* __restrict__ part, int nb, int bits,
+__global__ __launch_bounds__(kWave) void k_knn_root(const double* __restrict__ part, int nb, int bits,
                                                     KnnSync* __restrict__ sync)
 {
 #pragma clang fp contract(off)
-    if (threadIdx.x != 0) return;
+    // one wavefront over the partials (one thread alone took 60 us: a load latency each)
     double v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
-    for (int b = 0; b < nb; ++b) {
+    for (int b = threadIdx.x; b < nb; b += kWave) {
         for (int a = 0; a < 3; ++a) v[a] = fmin(v[a], part[b * 7 + a]);
         for (int a = 3; a < 7; ++a) v[a] = fmax(v[a], part[b * 7 + a]);
     }
+    for (int a = 0; a < 3; ++a) v[a] = wave_min(v[a]);
+    for (int a = 3; a < 7; ++a) v[a] = wave_max(v[a]);
+    if (threadIdx.x != 0) return;
     double ext = 0.0;
     for (int a = 0; a < 3; ++a) ext = fmax(ext, v[3 + a] - v[a]);
     double S = ext * (1.0 + 0x1p-40);
@@ -457,7 +460,7 @@ glm_status knn_positions_device(const double* x, const double* y, const double* 
     const int g = ceil_div(n, kBlock);
 
     hipLaunchKernelGGL(k_knn_bbox, dim3(kBboxBlocks), dim3(kBlock), 0, st, x, y, z, n, part);
-    hipLaunchKernelGGL(k_knn_root, dim3(1), dim3(64), 0, st, part, kBboxBlocks, d3 ? 21 : 31, sync);
+    hipLaunchKernelGGL(k_knn_root, dim3(1), dim3(kWave), 0, st, part, kBboxBlocks, d3 ? 21 : 31, sync);
     hipLaunchKernelGGL(k_knn_keys, dim3(g), dim3(kBlock), 0, st, x, y, z, n, sync, k0, v0);
     const int w = radix_sort_u64(k0, v0, k1, v1, n, 8, hist, st);
     const uint32_t* perm = w ? v1 : v0;

@@ -29,6 +29,8 @@ Printed as one JSON line, with:
 rocprofv3 counter summary (FETCH_SIZE + WRITE_SIZE, scaled by the counters'
 reading for a plain 1 GiB device copy, which every run performs last); it is
 null when the walk's sources differ from those the counters were taken on.
+The algorithmic FLOPs count an accepted box once per ray, also where the walk
+takes it once per ray group (far boxes through the group's local expansion).
 """
 from __future__ import annotations
 
@@ -63,7 +65,8 @@ def adjoint_flops_per_ray(counts: np.ndarray, p: int) -> np.ndarray:
     return 5.0 * counts[:, 0] + (23.0 + 8.0 * p) * counts[:, 1] + 38.0 * counts[:, 2] + 90.0 * counts[:, 3]
 
 
-WALK_SOURCES = ["walk.hip", "walk.hpp", "eval.hpp", "common.hpp"]
+WALK_SOURCES = ["walk.hip", "walk.hpp", "walk_fwd.hpp", "walk_full.hip", "traverse.hpp", "farfield.hpp", "lanesum.hpp",
+                "eval.hpp", "common.hpp"]
 HBM_PROFILE = os.path.join(ROOT, "profiles", "k_walk_nfw1e6_grid2048_hbm.txt")
 
 

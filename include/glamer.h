@@ -233,18 +233,20 @@ GLM_API glm_status glm_shoot_workspace_bytes(int64_t nrays, size_t* bytes);
  * `flags` carries it.  counts (device int32, GLM_COUNTS = 8 per ray, nullable)
  * receives per ray: boxes visited (opening tests), boxes accepted, leaf
  * particles summed, list particles the ray falls inside; then four counts of
- * the wavefront that walked the ray's 64-ray group (summed over the box
- * ranges of a split walk): big-particle list entries tested against the
+ * the wavefronts that walked the ray's group (up to 64 rays, one or several
+ * wavefronts): big-particle list entries tested against the
  * group's bounding box (the list search), boxes some ray of the group
  * accepted, leaf particles evaluated, list candidates evaluated.  The per-ray
  * counts over the wavefront counts give each phase's lane use.  A box's list
  * is tested 64 entries at a time, and not at all when the bounding box of its
  * particles' supports misses the group.  The walk evaluates its terms in FP32
- * and sums alpha and gamma in FP64; ray-particle and ray-box offsets and every
- * accept/inside decision are taken in FP64.
+ * and sums them in FP64; ray-particle and ray-box offsets and every
+ * accept/inside decision are taken in FP64.  Boxes that every ray of a group
+ * accepts from far enough are summed into one local expansion about the group
+ * (single-wavefront groups and launches of 65,536 rays or more), so there a ray's result
+ * depends on its group by rounding.
  *   workspace: device buffer of at least glm_shoot_workspace_bytes(nrays)
- *   (ray sort, and for small ray counts the partial sums of several
- *   wavefronts per ray group, each walking one range of the box array).
+ *   (the ray sort and the sorted rays).
  *   flags: GLM_ALPHA_ONLY, GLM_FP32_ALPHA, GLM_RAYS_ORDERED or GLM_RAYS_STAGED
  *   (not both; see glm_stage_rays), or-ed with the tree's.
  * nrays may be 0 (nothing is launched).
@@ -255,7 +257,7 @@ GLM_API glm_status glm_shoot(const glm_tree* t, const double* rx, const double* 
 
 /*
  * The ray staging of glm_shoot (Sec. 3.3: rays are independent; here they are
- * sorted along a Morton curve of their bounding square into spatially compact
+ * sorted along a Hilbert curve of their bounding square into spatially compact
  * 64-ray groups, and copied in that order) on its own, so that it can run on
  * another stream than the tree build, which it does not depend on.  It writes
  * the staged rays into `workspace` (at least glm_shoot_workspace_bytes(nrays)
@@ -300,7 +302,6 @@ GLM_API glm_status glm_shoot_noalloc(const glm_tree* t, const double* rx, const 
  *   a1, a2, psi: device FP32 outputs (nrays, input order);
  *   tdelay: device FP32 |alpha|^2 / 2 - psi, or NULL;
  *   flags: GLM_RAYS_ORDERED or 0; workspace as for glm_shoot.
- * One wavefront per 64-ray group (small launches are not split).
  */
 GLM_API glm_status glm_shoot_potential(const glm_tree* t, const double* rx, const double* ry, int64_t nrays,
                                        float* a1, float* a2, float* psi, float* tdelay, uint32_t flags,
@@ -378,7 +379,7 @@ GLM_API glm_status glm_shoot_batched_workspace_bytes(const int64_t* nrays, int n
 /*
  * Walk many independent lenses in ONE persistent launch (Sec. 3.3: the solver
  * parallelises over points, and bigger batches are more efficient): the rays
- * of every lens are Morton-sorted within their lens, cut into 64-ray groups,
+ * of every lens are sorted along a Hilbert curve, cut into 64-ray groups,
  * and the wavefronts of one launch take (lens, group) items from a device
  * counter, lenses with the most expected work (rays x log2 particles) first.
  * Results equal glm_shoot per lens.  `lenses` is a HOST array of nlens

@@ -430,9 +430,9 @@ struct AdjVisitor {
     {
         const FarOffset o = far_offset(T, g, c, active);
         const float rcm = T.mom[(size_t)c * mom_stride(P) + 1];
-        const float t1 = rcm * o.v1, t2 = rcm * o.v2, e1 = -g.a * o.v1, e2 = -g.a * o.v2;
+        float p1 = (float)o.v1, p2 = (float)o.v2;
+        const float t1 = rcm * p1, t2 = rcm * p2, e1 = -g.a * p1, e2 = -g.a * p2;
         float H[kFarWords]; // v e^j Lam_j
-        float p1 = o.v1, p2 = o.v2;
 #pragma unroll
         for (int j = 0; j <= kFarOrder; ++j) {
             const float l1 = lam[2 * j], l2 = lam[2 * j + 1];

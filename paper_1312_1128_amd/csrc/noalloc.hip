@@ -1,5 +1,5 @@
 // glm_shoot for callers that cannot allocate device memory: the ray workspace
-// (ray sort keys and values, sorted ray copies, partial sums of split walks)
+// (ray sort keys and values, sorted ray copies)
 // is a file-scope device array instead of a caller buffer.  Each GPU the
 // library runs on holds one copy of the array until the process ends; every
 // call on that GPU shares it, so calls that overlap on one GPU (on different

@@ -63,7 +63,7 @@ size_t shoot_indexed_workspace_bytes(int64_t count);
 
 // Per-ray counts of a walk: boxes visited (opening tests), boxes accepted,
 // leaf particles summed, list particles the ray falls inside; then counts of
-// its wavefront (the same for the 64 rays of a group): list entries tested
+// its group's wavefronts (the same for all rays of a group): list entries tested
 // against the ray group (the search overhead), boxes some lane accepted, leaf
 // particles evaluated, list candidates evaluated.  The per-lane counts over the
 // wavefront's give the lane use of each phase.
@@ -142,7 +142,7 @@ glm_status shoot_indexed_device(const TreeStorage& ts, const double* cx, const d
                                 void* ws, hipStream_t st);
 
 // alpha and the potential psi (and the time delay when td is not NULL) of
-// the rays; one wavefront per 64-ray group (no split).
+// the rays.
 glm_status potential_device(const TreeStorage& ts, const double* rx, const double* ry, int64_t nrays, float* a1,
                             float* a2, float* psi, float* td, uint32_t flags, void* ws, hipStream_t st);
 

@@ -51,9 +51,12 @@ struct FwdVisitor {
         if constexpr (PSI) fpsi += (double)b.psi0(active);
         // half of the words at a time: fewer registers
         float L[kFarWords / 2];
-        b.template words<0>(L);
+        double r1 = 0.0, r2 = 0.0;
+        b.template words<0>(L, r1, r2);
+        A.a1 += wave_sum(r1);
+        A.a2 -= wave_sum(r2);
         flo += word_totals64<kFarWords / 2>(L);
-        b.template words<kFarOrder / 2 + 1>(L);
+        b.template words<kFarOrder / 2 + 1>(L, r1, r2);
         fhi += word_totals64<kFarWords / 2>(L);
     }
 

@@ -1,8 +1,8 @@
 """The forward walk at the launch sizes where it changes shape: the number of
 wavefronts that share a ray group (16 down to 1 as the launch grows), far
 boxes through the groups' local expansions (65,536 rays and more), ragged last
-groups, groups whose rays all sit at one point, and lists so long and ray groups
-so wide that a list pass takes its candidates ray by ray.  Against the FP64
+groups, groups whose rays all sit at one point, and long lists under wide ray
+groups.  Against the FP64
 oracle tree: decision counts exactly, values to FP32 rounding (the bound of
 every tree test)."""
 import numpy as np

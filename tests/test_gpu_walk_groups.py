@@ -88,3 +88,37 @@ def test_wide_groups_over_a_dense_core(ora):
     got, cnt = shoot(tree, rx, ry, counts=True)
     np.testing.assert_array_equal(cnt, rc[:, [0, 1, 2, 4]])
     assert_matches_oracle_tree(got, ref)
+
+
+@pytest.mark.parametrize("nfw", [False, True])
+@pytest.mark.parametrize("lensing", [False, True])
+def test_adjoint_of_one_wavefront_per_group_is_the_sum_over_parts(nfw, lensing):
+    """300,001 rays on 3,000 particles take one wavefront per ray group, parts
+    of 50,000 several, with other far boxes and another particle pass; the
+    gradient is linear in the rays, so the parts add up to it (FP32 words of
+    boxes and profiles, summed in FP64: 2e-6 of the largest, as against the oracle)."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    gen = synth.rng(771)
+    n, nr = 3000, 300_001
+    x, y, m = gen.uniform(-1, 1, n), gen.uniform(-1, 1, n), gen.uniform(0.1, 1.0, n)
+    s = gen.uniform(0.002, 0.2, n)
+    s[gen.random(n) < 0.2] = 0.0
+    say(f"[gpu] adjoint parts nfw={nfw} lensing={lensing}")
+    tree = g.Tree().build(dev(x), dev(y), dev(m), dev(s), theta=0.4, q=5.0 if nfw else 3.0, leaf_size=8, order=6, nfw=nfw)
+    rx, ry = dev(gen.uniform(-1, 1, nr)), dev(gen.uniform(-1, 1, nr))
+    cot = torch.as_tensor(gen.normal(size=(5, nr)).astype(np.float32), device="cuda")
+
+    def grad(parts):
+        out = [torch.zeros(n, dtype=torch.float64, device="cuda") for _ in range(4)]
+        for a in range(0, nr, parts):
+            c = [v[a:a + parts].contiguous() for v in cot]
+            kw = dict(gk=c[2], gg1=c[3], gg2=c[4]) if lensing else {}
+            g.shoot_adjoint(tree, rx[a:a + parts].contiguous(), ry[a:a + parts].contiguous(), c[0], c[1], *out, **kw)
+        torch.cuda.synchronize()
+        return [o.cpu().numpy() for o in out]
+
+    for name, whole, parts in zip("mxys", grad(nr), grad(50_000)):
+        assert np.abs(whole).max() > 0
+        assert np.abs(whole - parts).max() <= 2e-6 * np.abs(parts).max(), name

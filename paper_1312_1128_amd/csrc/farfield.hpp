@@ -16,6 +16,8 @@
 // boxes, 64 at a time cost about 600, so a box costs about 10.
 #pragma once
 
+#include <float.h>
+
 #include "eval.hpp"
 #include "lanesum.hpp"
 
@@ -50,14 +52,16 @@ __device__ inline RayGroup ray_group(double X, double Y, bool valid, bool far)
         const double d1 = X - g.ox, d2 = Y - g.oy;
         g.a = (float)sqrt(wave_max(valid ? d1 * d1 + d2 * d2 : 0.0));
         g.inva = 1.0f / g.a;
-        g.far = g.a > 1e-30f; // (rays at one point: no scale to expand on)
+        // no scale to expand on with all rays at one point, nor with a ray at infinity (the
+        // rays' offsets over the radius would be NaN, also with no box expanded)
+        g.far = g.a > 1e-30f && g.a <= FLT_MAX;
     }
     return g;
 }
 
 // Whether a box that every ray accepts may go through the local expansion:
-// a / (d - r_cm) < kFarRatio, r_cm = theta r_cut.  (Strict, so that a group
-// with an infinite coordinate has no far boxes.)
+// a / (d - r_cm) < kFarRatio, r_cm = theta r_cut.  (Strict, so that a radius or
+// distance whose square overflows gives no far boxes.)
 __device__ inline bool is_far(const RayGroup& g, const CellHdr& h, float theta)
 {
     if (!g.far) return false;

@@ -122,3 +122,35 @@ def test_adjoint_of_one_wavefront_per_group_is_the_sum_over_parts(nfw, lensing):
     for name, whole, parts in zip("mxys", grad(nr), grad(50_000)):
         assert np.abs(whole).max() > 0
         assert np.abs(whole - parts).max() <= 2e-6 * np.abs(parts).max(), name
+
+
+@pytest.mark.parametrize("bad", [(np.inf, 0.1), (0.1, -np.inf), (np.inf, -np.inf), (1e200, 0.1), (np.nan, 0.1)],
+                         ids=lambda b: f"{b[0]:g},{b[1]:g}")
+@pytest.mark.parametrize("nr", [70_000, 300_001])
+def test_a_ray_at_infinity_leaves_its_group_alone(ora, nr, bad):
+    """A ray with an infinite, overflowing or NaN coordinate among rays whose launch
+    expands far boxes (several wavefronts per group and one), and in a batch: the
+    other rays keep the values of the oracle tree."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    lens = lens_of(400, 631)
+    rx, ry = synth.uniform_points(nr, 632, -0.7, 0.7)
+    at = 1000
+    idx = np.setdiff1d(np.union1d(np.arange(at - 130, at + 130), np.arange(0, nr, 97)), [at])
+    T = ora.Tree(lens.x, lens.y, lens.m, lens.s, lens.q, 0.5, 4, 4)
+    ref, ref_psi = T.shoot(rx[idx], ry[idx]), T.shoot_psi(rx[idx], ry[idx])
+    rx[at], ry[at] = bad
+    tree = build(lens, 0.5, 4, 4)
+    say(f"[gpu] ray at {bad} of {nr}")
+    assert_matches_oracle_tree(shoot(tree, rx, ry)[idx], ref)
+    assert_matches_oracle_tree(shoot(tree, rx, ry, counts=True)[0][idx], ref)
+    o = g.shoot_potential(tree, dev(rx), dev(ry))
+    torch.cuda.synchronize()
+    assert np.abs(o["psi"].double().cpu().numpy()[idx] - ref_psi).max() <= 2e-6 * np.abs(ref_psi).max()
+    k = at + 130
+    b = g.shoot_batched([tree, tree], [(dev(rx[:k]), dev(ry[:k])), (dev(rx[at + 1:k]), dev(ry[at + 1:k]))])
+    torch.cuda.synchronize()
+    got = np.stack([b[0][q].double().cpu().numpy() for q in ["a1", "a2", "kappa", "g1", "g2"]], axis=1)
+    near = idx < k
+    assert_matches_oracle_tree(got[idx[near]], ref[near])

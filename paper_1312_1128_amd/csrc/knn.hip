@@ -40,9 +40,9 @@ __global__ __launch_bounds__(kBlock) void k_knn(TreeDev T, BoxArrays b, double x
     const int n = T.n;
     const int g0 = (blockIdx.x * (kBlock / kWave) + w) * kWave; // first particle of the group
     if (g0 >= n) return;
-    const int j = g0 + lane;
-    const bool valid = j < n;
-    const PRec me = T.prt[valid ? j : g0];
+    const int j = knn_particle(g0, lane, n);
+    const bool valid = lane < n - g0;
+    const PRec me = T.prt[j];
     const double X = me.x, Y = me.y;
     __shared__ double lds[kBlock / kWave][kKnnQueue * kWave];
     __shared__ int stack[kBlock / kWave][kKnnStack];
@@ -50,12 +50,11 @@ __global__ __launch_bounds__(kBlock) void k_knn(TreeDev T, BoxArrays b, double x
 
     // each lane's k neighbours along the Morton order on either side first
     for (int o = 1; o <= k; ++o) {
-        const int a = j - o, b2 = j + o;
-        const PRec& pa = T.prt[a >= 0 ? a : 0];
-        const PRec& pb = T.prt[b2 < n ? b2 : 0];
+        const KnnSeed sd = knn_seed(j, o, n);
+        const PRec &pa = T.prt[sd.before], &pb = T.prt[sd.after];
         const double da = knn_d2(X, Y, pa.x, pa.y), db = knn_d2(X, Y, pb.x, pb.y);
-        L.insert(a >= 0 ? da : INFINITY);
-        L.insert(b2 < n ? db : INFINITY);
+        L.insert(sd.has_before ? da : INFINITY);
+        L.insert(sd.has_after ? db : INFINITY);
     }
 
     // then every box that some lane still needs

@@ -79,6 +79,27 @@ struct KnnList {
     }
 };
 
+// The particle of lane `lane` of the wavefront that serves g0 .. g0 + 63 of n
+// particles: its own, or g0 for the idle lanes of the last wavefront.
+__host__ __device__ inline int knn_particle(int g0, int lane, int n) { return lane < n - g0 ? g0 + lane : g0; }
+
+// Particle j's neighbours o places before and after it along the sorted order
+// of n particles, j itself where there is none.  (No sum of the two that could
+// pass 2^31.)
+struct KnnSeed {
+    int before, after;
+    bool has_before, has_after;
+};
+__host__ __device__ inline KnnSeed knn_seed(int j, int o, int n)
+{
+    KnnSeed s;
+    s.has_before = j >= o;
+    s.has_after = n - 1 - j >= o;
+    s.before = s.has_before ? j - o : j;
+    s.after = s.has_after ? j + o : j;
+    return s;
+}
+
 __device__ inline double knn_bcast(double v, int k)
 {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), k), hi = __builtin_amdgcn_readlane(__double2hiint(v), k);

@@ -280,9 +280,8 @@ __global__ __launch_bounds__(kBlock) void k_knn_bvh(const double* __restrict__ x
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int g0 = (blockIdx.x * (kBlock / kWave) + w) * kWave;
     if (g0 >= ns) return;
-    const int j = g0 + lane;
-    const bool valid = j < ns;
-    const int jj = valid ? j : g0;
+    const bool valid = lane < ns - g0;
+    const int jj = knn_particle(g0, lane, ns);
     const double X = xs[jj], Y = ys[jj], Z = D3 ? zs[jj] : 0.0;
     __shared__ double lds[kBlock / kWave][kKnnQueue * kWave];
     __shared__ int stack[kBlock / kWave][kBvhStack];
@@ -291,12 +290,12 @@ __global__ __launch_bounds__(kBlock) void k_knn_bvh(const double* __restrict__ x
 
     // each lane's k neighbours along the sorted order on either side first
     for (int o = 1; o <= k; ++o) {
-        const int a = jj - o, b = jj + o;
-        const int ca = a >= 0 ? a : 0, cb = b < ns ? b : 0;
-        const double da = knn3_d2<D3>(X, Y, Z, xs[ca], ys[ca], D3 ? zs[ca] : 0.0);
-        const double db = knn3_d2<D3>(X, Y, Z, xs[cb], ys[cb], D3 ? zs[cb] : 0.0);
-        L.insert(a >= 0 ? da : INFINITY);
-        L.insert(b < ns ? db : INFINITY);
+        const KnnSeed sd = knn_seed(jj, o, ns);
+        const int a = sd.before, b = sd.after;
+        const double da = knn3_d2<D3>(X, Y, Z, xs[a], ys[a], D3 ? zs[a] : 0.0);
+        const double db = knn3_d2<D3>(X, Y, Z, xs[b], ys[b], D3 ? zs[b] : 0.0);
+        L.insert(sd.has_before ? da : INFINITY);
+        L.insert(sd.has_after ? db : INFINITY);
     }
 
     // bounding box of the wavefront's particles (idle lanes: particle g0)
@@ -381,7 +380,7 @@ __global__ __launch_bounds__(kBlock) void k_knn_bvh(const double* __restrict__ x
         wave_lds_sync();
     }
     L.flush();
-    if (valid) s_out[perm[j]] = sqrt(L.bound());
+    if (valid) s_out[perm[jj]] = sqrt(L.bound());
 }
 
 struct KnnLayout {

@@ -13,7 +13,7 @@ MAIN = r"""
 
 int main()
 {
-    const int64_t sizes[] = {2, 3, 33, 63, 64, 65, 66, 127, 128, 129, 1000, 4097};
+    const int64_t sizes[] = {2, 3, 33, 63, 64, 65, 66, 127, 128, 129, 1000, 4097, 2147483647ll - 64, 2147483647ll};
     for (const int64_t n : sizes)
         for (int64_t g0 = 0; g0 < n; g0 += 64) {
             if (g0 > 4 * 64 && g0 < n - 4 * 64) g0 = (n - 4 * 64) / 64 * 64;

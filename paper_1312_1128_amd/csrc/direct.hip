@@ -60,6 +60,11 @@ __device__ inline bool direct_sum(double* v, double* lds)
     return true;
 }
 
+// x of the massless records that stand in a tile's places without a particle (a step takes
+// several places at once, the last one's may be such): far from every ray, while its square is
+// still finite.  (At the origin, 1 / r^2 of a ray next to it overflows, and 0 inf is no number.)
+constexpr double kNowhere = 1e100;
+
 template <bool AONLY, int KIND, int RB>
 __global__ __launch_bounds__(kWave* dir_waves(RB)) void k_direct32(const double* __restrict__ x, const double* __restrict__ y,
                                                          const double* __restrict__ m, const double* __restrict__ s,
@@ -81,7 +86,7 @@ __global__ __launch_bounds__(kWave* dir_waves(RB)) void k_direct32(const double*
         const int64_t j = base + threadIdx.x;
         PRec t;
         if (j < n) make_rec<KIND>(t, x[j], y[j], m[j], s ? s[j] : 0.0, q, norm, (uint32_t)j);
-        else make_rec<KIND>(t, 0.0, 0.0, 0.0, 0.0, q, norm, 0u); // no mass: adds nothing
+        else make_rec<KIND>(t, kNowhere, 0.0, 0.0, 0.0, q, norm, 0u);
         __syncthreads(); // the previous tile is done
         tile[threadIdx.x] = t;
         __syncthreads();
@@ -143,7 +148,7 @@ __global__ __launch_bounds__(kWave* dir_waves(RB)) void k_direct64(const double*
     for (int64_t base = 0; base < n; base += kDirTile) {
         const int64_t j = base + threadIdx.x;
         const double sj = (j < n && s) ? s[j] : 0.0;
-        double2 xy = make_double2(0.0, 0.0), mq = make_double2(0.0, 0.0); // no mass: adds nothing
+        double2 xy = make_double2(kNowhere, 0.0), mq = make_double2(0.0, 0.0);
         if (j < n) {
 #pragma clang fp contract(off)
             const double qs = KIND == kKindNfw ? sj : q * sj;

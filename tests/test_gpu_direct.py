@@ -84,3 +84,31 @@ def test_direct_at_tile_and_workgroup_edges(ora, n, nr, nfw):
             mag = np.linalg.norm(ref[:, cols], axis=1)
             err = np.linalg.norm(got[:, cols] - ref[:, cols], axis=1)
             assert np.all(err <= tol * (mag + 1e-2 * mag.max() + 1e-300)), (fp64, cols)
+
+
+@pytest.mark.parametrize("n,nr", [(17, 5), (65, 9000), (1025, 30), (257, 131_073)])
+@pytest.mark.parametrize("nfw", [False, True])
+def test_direct_next_to_the_origin(ora, n, nr, nfw):
+    """Rays off the origin by less than FP32 (and FP64) can square, particle counts that fill no
+    step of a workgroup: the places of a step that hold no particle add nothing."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    gen = synth.rng(81)
+    phi, c = gen.uniform(0, 2 * np.pi, n), 3.0
+    x, y, m = 0.4 * np.cos(phi), 0.4 * np.sin(phi), gen.uniform(0.5, 1.0, n)
+    s = gen.uniform(0.01, 0.1, n)
+    rx, ry = synth.uniform_points(nr, 82, -0.7, 0.7)
+    tiny = np.array([1e-21, 3e-20, 1e-22, 1e-158, 1e-161])
+    rx[:5], ry[:5] = tiny, -tiny
+    idx = np.unique(np.r_[np.arange(5), np.arange(0, nr, 37)])
+    say(f"[gpu] direct next to the origin n={n} rays={nr} nfw={nfw}")
+    ref = (ora.direct_nfw if nfw else ora.direct)(x, y, m, s, c, rx[idx], ry[idx])
+    for fp64, tol in ((True, 1e-10), (False, 1e-5)):
+        o = g.shoot_direct(dev(x), dev(y), dev(m), dev(s), c, dev(rx), dev(ry), fp64=fp64, nfw=nfw)
+        torch.cuda.synchronize()
+        got = np.stack([o[q].double().cpu().numpy()[idx] for q in ["a1", "a2", "kappa", "g1", "g2"]], axis=1)
+        for cols in (slice(0, 2), slice(2, 3), slice(3, 5)):
+            mag = np.linalg.norm(ref[:, cols], axis=1)
+            err = np.linalg.norm(got[:, cols] - ref[:, cols], axis=1)
+            assert np.all(err <= tol * (mag + 1e-2 * mag.max() + 1e-300)), (fp64, cols)

@@ -8,6 +8,7 @@
 // shuffles, wavefronts in LDS, in wavefront order).  One thread per ray left the
 // chip mostly idle below about 500,000 rays: 20,480 validation rays made 80 workgroups
 // for 256 compute units.
+#include <float.h>
 #include <math.h>
 
 #include "eval.hpp"
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(kWave* dir_waves(RB)) void k_direct64(const double*
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int64_t r = (int64_t)blockIdx.x * RB + lane % RB;
     const double X = r < nr ? rx[r] : 0.0, Y = r < nr ? ry[r] : 0.0;
-    double sa1 = 0, sa2 = 0, sk = 0, sg1 = 0, sg2 = 0;
+    double sa1 = 0, sa2 = 0, sk = 0, sg1 = 0, sh2 = 0; // sh2: half of -gamma2
     for (int64_t base = 0; base < n; base += kDirTile) {
         const int64_t j = base + threadIdx.x;
         const double sj = (j < n && s) ? s[j] : 0.0;
@@ -168,8 +169,9 @@ __global__ __launch_bounds__(kWave* dir_waves(RB)) void k_direct64(const double*
             double d1, d2;
             const double r2 = sqdist(X, Y, p.x, p.y, &d1, &d2);
             const bool inside = r2 < mm.y;
-            const double ir2 = r2 > 0.0 ? recip64(r2) : 0.0; // (a particle exactly at the ray has no deflection)
-            double hh = mm.x * ir2, tt = hh * ir2; // alpha = hh d, gamma = -tt (d1^2 - d2^2, 2 d1 d2)
+            // (a particle exactly at the ray, or so near that 1 / r^2 overflows, has no deflection)
+            const double ir2 = r2 >= DBL_MIN ? recip64(r2) : 0.0;
+            double hh = mm.x * ir2, G = hh; // alpha = hh d, gamma = -G (cos 2phi, sin 2phi)
             if (inside) {
                 const double sp = ts[k];
                 double K;
@@ -185,18 +187,18 @@ __global__ __launch_bounds__(kWave* dir_waves(RB)) void k_direct64(const double*
                     hh = mm.x * (-expm1(-u) / C) * ir2;
                     K = mm.x * exp(-u) / (2.0 * sp * sp * C);
                 }
-                tt = (hh - K) * ir2;
+                G = hh - K;
                 sk += K;
             }
             sa1 = fma(hh, d1, sa1);
             sa2 = fma(hh, d2, sa2);
             if (!AONLY) {
-                sg1 = fma(-tt, d1 * d1 - d2 * d2, sg1);
-                sg2 = fma(-tt, 2.0 * d1 * d2, sg2);
+                sg1 = fma(-G, (d1 * d1 - d2 * d2) * ir2, sg1); // (hh ir2 can leave the range of an FP64)
+                sh2 = fma(G, d1 * d2 * ir2, sh2);
             }
         }
     }
-    double v[5] = {sa1, sa2, sk, sg1, sg2};
+    double v[5] = {sa1, sa2, sk, sg1, -2.0 * sh2};
     if (!direct_sum<RB, NV>(v, sums) || r >= nr) return;
     a1[r] = v[0];
     a2[r] = v[1];

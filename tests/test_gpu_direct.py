@@ -112,3 +112,31 @@ def test_direct_next_to_the_origin(ora, n, nr, nfw):
             mag = np.linalg.norm(ref[:, cols], axis=1)
             err = np.linalg.norm(got[:, cols] - ref[:, cols], axis=1)
             assert np.all(err <= tol * (mag + 1e-2 * mag.max() + 1e-300)), (fp64, cols)
+
+
+def test_direct64_over_its_range():
+    """One point mass at the origin, rays from 1e-150 to 1e150 away: alpha = d / r^2 and gamma =
+    -(d1^2 - d2^2, 2 d1 d2) / r^4, which are finite numbers however r^4 over- or underflows."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    r, phi = 10.0 ** np.arange(-150, 151, 2.5), 0.7
+    d = np.stack([r * np.cos(phi), r * np.sin(phi)])
+    z = np.zeros(1)
+    o = g.shoot_direct(dev(z), dev(z), dev(z + 1.0), dev(z), 3.0, dev(d[0]), dev(d[1]), fp64=True)
+    torch.cuda.synchronize()
+    got = {k: v.cpu().numpy() for k, v in o.items()}
+    for k, ref in (("a1", np.cos(phi) / r), ("a2", np.sin(phi) / r)):
+        np.testing.assert_allclose(got[k], ref, rtol=1e-13)
+    with np.errstate(over="ignore", under="ignore"):
+        ok = (r > 1e-150) & (r < 1e150)
+        for k, ref in (("g1", -np.cos(2 * phi) / r[ok] / r[ok]), ("g2", -np.sin(2 * phi) / r[ok] / r[ok])):
+            np.testing.assert_allclose(got[k][ok], ref, rtol=1e-12)
+    # inside a Gaussian and just above the range of r^2: its centre's kappa and no shear
+    r = 10.0 ** np.arange(-156, -139, 1.0)
+    o = g.shoot_direct(dev(z), dev(z), dev(z + 1.0), dev(z + 0.1), 3.0, dev(r * np.cos(phi)), dev(r * np.sin(phi)), fp64=True)
+    torch.cuda.synchronize()
+    kappa = 50.0 / -np.expm1(-4.5)
+    np.testing.assert_allclose(o["kappa"].cpu().numpy(), kappa, rtol=1e-13)
+    for k in ("a1", "a2", "g1", "g2"):
+        assert np.abs(o[k].cpu().numpy()).max() <= 1e-9 * kappa, k

@@ -11,6 +11,8 @@
 #include <float.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "eval.hpp"
 #include "walk.hpp"
 
@@ -217,16 +219,12 @@ inline int direct_rays(int64_t nrays)
     return nrays >= 64 * 2048 ? 64 : (nrays >= 16 * 512 ? 16 : 4);
 }
 
-} // namespace
-
-glm_status direct_device(const double* x, const double* y, const double* m, const double* s, int64_t n, double q,
-                         int kind, const double* rx, const double* ry, int64_t nrays, int fp64, void* const out5[5],
-                         hipStream_t st)
+glm_status launch_direct(const double* x, const double* y, const double* m, const double* s, int64_t n, double q,
+                         int kind, const double* rx, const double* ry, int64_t nrays, int rb, int fp64,
+                         void* const out5[5], hipStream_t st)
 {
-    if (nrays == 0) return GLM_OK;
     const double C = kind == kKindNfw ? nfw_g_at(q) : -expm1(-0.5 * q * q);
     const bool aonly = !out5[2] || !out5[3] || !out5[4];
-    const int rb = direct_rays(nrays);
     const dim3 g(ceil_div(nrays, rb)), b(kWave * dir_waves(rb));
 #define GLM_DIRECT(KERNEL, AO, KD, NORM)                                                                                \
     do {                                                                                                                \
@@ -262,6 +260,27 @@ glm_status direct_device(const double* x, const double* y, const double* m, cons
 #undef GLM_KINDS
 #undef GLM_DIRECT
     GLM_HIP(hipGetLastError());
+    return GLM_OK;
+}
+
+// Rays of one launch: a launch has fewer than 2^32 threads, and a ray up to 4 of them
+// where there are so many.
+constexpr int64_t kDirectLaunch = 1ll << 29;
+
+} // namespace
+
+glm_status direct_device(const double* x, const double* y, const double* m, const double* s, int64_t n, double q,
+                         int kind, const double* rx, const double* ry, int64_t nrays, int fp64, void* const out5[5],
+                         hipStream_t st)
+{
+    const int rb = direct_rays(nrays); // for all of its launches
+    for (int64_t at = 0; at < nrays; at += kDirectLaunch) {
+        void* o[5];
+        for (int k = 0; k < 5; ++k) o[k] = out5[k] ? static_cast<char*>(out5[k]) + at * (fp64 ? 8 : 4) : nullptr;
+        const glm_status rc = launch_direct(x, y, m, s, n, q, kind, rx + at, ry + at, std::min(nrays - at, kDirectLaunch),
+                                            rb, fp64, o, st);
+        if (rc != GLM_OK) return rc;
+    }
     return GLM_OK;
 }
 

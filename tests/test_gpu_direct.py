@@ -140,3 +140,19 @@ def test_direct64_over_its_range():
     np.testing.assert_allclose(o["kappa"].cpu().numpy(), kappa, rtol=1e-13)
     for k in ("a1", "a2", "g1", "g2"):
         assert np.abs(o[k].cpu().numpy()).max() <= 1e-9 * kappa, k
+
+
+def test_direct_of_more_rays_than_one_launch_has_threads_for():
+    """2^30 + 300 rays: with four threads to a ray, more than the 2^32 threads of a launch."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    nr = (1 << 30) + 300
+    say("[gpu] direct sum of 2^30 + 300 rays")
+    p = [dev(np.array(v)) for v in ([0.3, -0.2], [0.1, 0.4], [1.0, 0.5], [0.05, 0.0])]
+    rx = torch.linspace(-1.0, 1.0, nr, dtype=torch.float64, device="cuda")
+    o = g.shoot_direct(*p, 3.0, rx, rx, alpha_only=True)
+    for a, b in ((0, 4096), (nr // 2 - 2048, nr // 2 + 2048), (nr - 4096, nr)):
+        e = g.shoot_direct(*p, 3.0, rx[a:b].contiguous(), rx[a:b].contiguous(), alpha_only=True)
+        for k in ("a1", "a2"):
+            torch.testing.assert_close(o[k][a:b], e[k], rtol=1e-6, atol=1e-6)

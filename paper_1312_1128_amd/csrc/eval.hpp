@@ -132,7 +132,9 @@ __device__ inline double sqdist_angles(double X, double Y, double px, double py,
 // Gamma = A - kappa (gamma = -Gamma (cos 2phi, sin 2phi)):
 //   A = mC (1 - e^-u) / r^2 = mh (1 - e^-u)/u,  Gamma = mh ((1 - e^-u)/u - e^-u).
 // Below u = 1/2, where 1 - e^-u cancels, both use their Taylor series.  Each
-// branch is evaluated only if some lane of the wavefront needs it.
+// branch is evaluated only if some lane of the wavefront needs it.  Without WANT_G only A is
+// formed (pick2 would keep Gamma's series alive: its two outputs come together).
+template <bool WANT_G = true>
 __device__ inline void gauss_terms(float u, float e, float ir2, float mC, float mh, float* A, float* G)
 {
     const uint64_t small = __ballot(u < 0.5f);
@@ -153,7 +155,8 @@ __device__ inline void gauss_terms(float u, float e, float ir2, float mC, float 
                                    u * (1.0f / 8 +
                                         u * (-1.0f / 30 +
                                              u * (1.0f / 144 + u * (-1.0f / 840 + u * (1.0f / 5760 + u * (-1.0f / 45360 + u * (1.0f / 403200)))))))));
-        pick2(small, mh * sg, Al, mh * sd, Gl, Al, Gl);
+        if constexpr (WANT_G) pick2(small, mh * sg, Al, mh * sd, Gl, Al, Gl);
+        else Al = u < 0.5f ? mh * sg : Al;
     }
     *A = Al;
     *G = Gl;
@@ -322,7 +325,7 @@ __device__ inline float profile_psi(const PRec& pr, double r2, double psiK, int 
 // Profile terms of one smoothed particle for a lane inside its support (r^2
 // in FP64 and FP32, ir2 = 1 / r^2): alpha = A d, kappa = K and
 // gamma = -G (cos 2phi, sin 2phi) with G = A - K.
-template <int KIND>
+template <int KIND, bool WANT_G = true>
 __device__ inline void profile_terms(const PRec& pr, double r2, float r2f, float ir2, float* A, float* G, float* K)
 {
     if constexpr (KIND == kKindNfw) {
@@ -337,7 +340,7 @@ __device__ inline void profile_terms(const PRec& pr, double r2, float r2f, float
         const float u = r2f * pr.h;
         const float e = __expf(-u);
         const float mh = pr.mC * pr.h;
-        gauss_terms(u, e, ir2, pr.mC, mh, A, G);
+        gauss_terms<WANT_G>(u, e, ir2, pr.mC, mh, A, G);
         *K = mh * e;
     }
 }
@@ -374,8 +377,9 @@ __device__ inline void leaf_particle(const PRec& pr, double X, double Y, Acc& A,
     float coef = pm, Gam = pm;
     if (__any(gauss)) {
         float Ag, Gg, Kg;
-        profile_terms<KIND>(pr, r2, r2f, ir2, &Ag, &Gg, &Kg);
-        pick2(__ballot(gauss), Ag, pm, Gg, pm, coef, Gam);
+        profile_terms<KIND, !AONLY>(pr, r2, r2f, ir2, &Ag, &Gg, &Kg);
+        if constexpr (AONLY) coef = gauss ? Ag : pm;
+        else pick2(__ballot(gauss), Ag, pm, Gg, pm, coef, Gam);
         if (!AONLY) A.k += (double)(gauss ? Kg : 0.0f);
     }
     if constexpr (F64A) {
@@ -416,7 +420,7 @@ __device__ inline void list_particle(const PRec& pr, double X, double Y, Acc& A,
     const float ir2 = r2f > 0.0f ? __builtin_amdgcn_rcpf(r2f) : 0.0f;
     const float pm = pr.m * ir2;
     float Ag, Gg, Kg;
-    profile_terms<KIND>(pr, r2, r2f, ir2, &Ag, &Gg, &Kg);
+    profile_terms<KIND, !AONLY>(pr, r2, r2f, ir2, &Ag, &Gg, &Kg);
     if constexpr (F64A) {
         const double diff = (double)Ag - (double)pm;
         A.a1 = fma(diff, d1, A.a1);

@@ -206,25 +206,30 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
             }
         } else if (todo) {
             int k = __ffsll((unsigned long long)todo) - 1, ck = __builtin_amdgcn_readlane(c, k);
-            typename V::Box bx = v.load(ck);
-            do {
+            typename V::Box even = v.load(ck), odd;
+            // one box of the round: `now` is here, `then` is loaded behind the work on it (two
+            // records that take turns, no copies: the loop issues as many scalar instructions
+            // as vector ones)
+            const auto step = [&](typename V::Box& now, typename V::Box& then) {
                 todo &= todo - 1;
                 const int kn = todo ? __ffsll((unsigned long long)todo) - 1 : k;
                 int cn = __builtin_amdgcn_readlane(c, kn);
-                settle(bx, cn);
-                const typename V::Box bn = v.load(cn);
+                settle(now, cn);
+                then = v.load(cn);
                 const bool act = lane_bit(readlane64(m, k));
                 double w1, w2;
                 const double d2 = sqdist(X, Y, readlane_f64(h.cx, k), readlane_f64(h.cy, k), &w1, &w2);
                 const bool acc = act && d2 > readlane_f64(h.rcut2, k);
                 const uint64_t ak = __ballot(acc);
-                if (ak) v.box(bx, ck, acc, w1, w2);
+                if (ak) v.box(now, ck, acc, w1, w2);
                 if (lane == k) am = ak;
-                if (kn == k) break;
+                const bool more = kn != k;
                 k = kn;
                 ck = cn;
-                bx = bn;
-            } while (true);
+                return more;
+            };
+            while (step(even, odd) && step(odd, even)) {
+            }
         }
         if constexpr (V::stats) {
             uint64_t part = __ballot(has && m != g.full);
@@ -331,19 +336,21 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
             if (i < qn[0]) {
                 int ck = __builtin_amdgcn_readfirstlane(L.qb[i]);
                 uint64_t mk = uniform64(L.qm[i]);
-                HdrBox<typename V::Box> bx{uniform_ld(T.hdr, ck), v.load(ck)};
-                do {
+                HdrBox<typename V::Box> even{uniform_ld(T.hdr, ck), v.load(ck)}, odd;
+                const auto step = [&](HdrBox<typename V::Box>& now, HdrBox<typename V::Box>& then) {
                     i += W;
                     const int in = i < qn[0] ? i : i - W;
                     int cn = __builtin_amdgcn_readfirstlane(L.qb[in]);
                     const uint64_t mn = uniform64(L.qm[in]);
-                    settle(bx, cn);
-                    const HdrBox<typename V::Box> bn{uniform_ld(T.hdr, cn), v.load(cn)};
-                    v.box(bx.box, ck, lane_bit(mk), X - bx.h.cx, Y - bx.h.cy);
+                    settle(now, cn);
+                    then = {uniform_ld(T.hdr, cn), v.load(cn)};
+                    v.box(now.box, ck, lane_bit(mk), X - now.h.cx, Y - now.h.cy);
                     ck = cn;
                     mk = mn;
-                    bx = bn;
-                } while (i < qn[0]);
+                    return i < qn[0];
+                };
+                while (step(even, odd) && step(odd, even)) {
+                }
             }
             rot += qn[0];
             for (i = (w - rot) & (W - 1); i < qn[1]; i += W) {

@@ -95,13 +95,17 @@ struct FwdVisitor {
             if (act) cnt[2] += pend - pbeg;
             cnt[6] += pend - pbeg;
         }
-        PRec pr = uniform_ld(T.prt, pbeg);
-        for (int j = pbeg; j < pend; ++j) {
+        int j = pbeg;
+        PRec even = uniform_ld(T.prt, j), odd;
+        // one particle of the leaf: `now` is here, `then` is loaded behind the work on it
+        const auto step = [&](PRec& now, PRec& then) {
             int next = j + 1 < pend ? j + 1 : j;
-            settle(pr, next);
-            const PRec nx = uniform_ld(T.prt, next);
-            if (act) leaf_particle<AONLY, f64a, PSI, KIND>(pr, X, Y, A, T.psiK, T.einTerms, T.invC);
-            pr = nx;
+            settle(now, next);
+            then = uniform_ld(T.prt, next);
+            if (act) leaf_particle<AONLY, f64a, PSI, KIND>(now, X, Y, A, T.psiK, T.einTerms, T.invC);
+            return ++j < pend;
+        };
+        while (step(even, odd) && step(odd, even)) {
         }
     }
 
@@ -125,15 +129,17 @@ struct FwdVisitor {
                 cnt[7] += __popcll(cm);
             }
             if (!cm) continue;
-            PRec pr = uniform_ld(T.lst, base + __ffsll((unsigned long long)cm) - 1);
-            while (cm) {
+            PRec even = uniform_ld(T.lst, base + __ffsll((unsigned long long)cm) - 1), odd;
+            const auto step = [&](PRec& now, PRec& then) {
                 const uint64_t rest = cm & (cm - 1);
                 int next = base + __ffsll((unsigned long long)(rest ? rest : cm)) - 1;
-                settle(pr, next);
-                const PRec nx = uniform_ld(T.lst, next);
-                if (act) list_particle<AONLY, f64a, PSI, KIND>(pr, X, Y, A, hits, T.psiK, T.einTerms, T.invC);
-                pr = nx;
+                settle(now, next);
+                then = uniform_ld(T.lst, next);
+                if (act) list_particle<AONLY, f64a, PSI, KIND>(now, X, Y, A, hits, T.psiK, T.einTerms, T.invC);
                 cm = rest;
+                return cm != 0;
+            };
+            while (step(even, odd) && step(odd, even)) {
             }
         }
         if constexpr (stats) cnt[3] += hits;

@@ -165,9 +165,15 @@ __device__ inline void write_out(const Acc& A, const int* cnt, int64_t o, const 
         for (int i = 0; i < kCounts; ++i) out.counts[kCounts * o + i] = cnt[i];
 }
 
+// Wavefronts per SIMD that the walk's kernels are held to: `most`, but four for the halos' potential,
+// whose FP64 logarithms and arctangent take 128 registers (with the 80 of six it spilled 100:
+// 1e5 halos, 1e6 rays 25.6 ms, 17.6 with four).
+template <bool PSI, int KIND>
+constexpr int walk_waves(int most) { return PSI && KIND == kKindNfw ? 4 : most; }
+
 // One wavefront (and workgroup) per ray group.
 template <int P, bool AONLY, bool PSI, int KIND>
-__global__ __launch_bounds__(kWave, 6) void k_walk(TreeDev T, const double* __restrict__ rxs,
+__global__ __launch_bounds__(kWave, (walk_waves<PSI, KIND>(6))) void k_walk(TreeDev T, const double* __restrict__ rxs,
                                                const double* __restrict__ rys, const uint32_t* __restrict__ rperm,
                                                int64_t nrays, WalkOut out)
 {
@@ -206,7 +212,7 @@ constexpr size_t walk_coop_lds(int W)
 // W = blockDim.x / 64 wavefronts per group of `rays` (up to 64) rays; their sums meet in wavefront
 // order in LDS.
 template <int P, bool AONLY, int MODE, bool PSI, int KIND, bool FAR>
-__global__ __launch_bounds__(kWave* kMaxGroupWaves, 5) void k_walk_coop(TreeDev T, const double* __restrict__ rxs,
+__global__ __launch_bounds__(kWave* kMaxGroupWaves, (walk_waves<PSI, KIND>(5))) void k_walk_coop(TreeDev T, const double* __restrict__ rxs,
                                                                     const double* __restrict__ rys,
                                                                     const uint32_t* __restrict__ rperm, int64_t nrays,
                                                                     WalkOut out, int rays)

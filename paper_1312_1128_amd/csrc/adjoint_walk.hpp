@@ -528,7 +528,7 @@ constexpr size_t adj_wave_lds() { return 4 * (adj_scratch<P, COOP, FAR>() + kFar
 template <int P, bool KG, int KIND, bool COOP, bool FAR>
 __global__ __launch_bounds__(COOP ? kWave * kMaxGroupWaves : kWave) void k_adjoint_walk(
     TreeDev T, const double* __restrict__ rxs, const double* __restrict__ rys, const uint32_t* __restrict__ rperm,
-    int64_t nrays, CotIn ci, double* __restrict__ pg, double* __restrict__ abar, int rays)
+    int64_t nrays, CotIn ci, double* __restrict__ pg, double* __restrict__ abar, int rays, bool far)
 {
     extern __shared__ __align__(16) char lds[];
     const int lane = threadIdx.x & (kWave - 1);
@@ -552,12 +552,12 @@ __global__ __launch_bounds__(COOP ? kWave * kMaxGroupWaves : kWave) void k_adjoi
             cg.h2 = ci.gg2 ? ci.gg2[o] : 0.0f;
         }
     }
-    const RayGroup g = ray_group(X, Y, valid, FAR);
-    char* own = lds + (COOP ? coop_lds_bytes(W) + w * adj_wave_lds<P, COOP, FAR>() : solo_lds_bytes());
+    const RayGroup g = ray_group(X, Y, valid, FAR && far);
+    char* own = lds + (COOP ? coop_lds_bytes(W) + w * adj_wave_lds<P, COOP, FAR>() : solo_lds_bytes(true));
     float* scratch = reinterpret_cast<float*>(own);
     AdjVisitor<P, KG, KIND, FAR, COOP> v(T, g, X, Y, lane, cg, abar + (size_t)(wid % kAdjCopies) * T.ncells * (2 * (P + 2)),
                                    pg + (size_t)(wid % kPgCopies) * 4 * T.n, scratch, scratch + adj_scratch<P, COOP, FAR>());
-    traverse<COOP>(T, v, g, X, Y, lane, w, W, COOP ? coop_lds(lds, W) : solo_lds(lds));
+    traverse<COOP>(T, v, g, X, Y, lane, w, W, COOP ? coop_lds(lds, W) : solo_lds(lds, true));
 }
 
 // Arguments of an adjoint walk launch.
@@ -580,9 +580,9 @@ void launch_adjoint_kind(const AdjointArgs& a)
     const int W = a.shape.waves;
     const auto go = [&](auto coop, auto far) {
         constexpr bool COOP = decltype(coop)::value, FAR = decltype(far)::value;
-        const size_t lds = COOP ? coop_lds_bytes(W) + W * adj_wave_lds<P, COOP, FAR>() : solo_lds_bytes() + adj_wave_lds<P, COOP, FAR>();
+        const size_t lds = COOP ? coop_lds_bytes(W) + W * adj_wave_lds<P, COOP, FAR>() : solo_lds_bytes(true) + adj_wave_lds<P, COOP, FAR>();
         hipLaunchKernelGGL((k_adjoint_walk<P, KG, KIND, COOP, FAR>), g, dim3(kWave * W), lds, a.st, a.T, a.rxs, a.rys,
-                           a.rperm, a.nrays, a.ci, a.pg, a.abar, a.shape.rays);
+                           a.rperm, a.nrays, a.ci, a.pg, a.abar, a.shape.rays, a.far);
     };
     if (W == 1) go(std::false_type{}, std::true_type{});
     else if (a.far) go(std::true_type{}, std::true_type{});

@@ -34,7 +34,9 @@ namespace glm {
 
 // Stack room that a descent box by box can need: three siblings per level.
 constexpr int kStackReserve = 3 * kMaxLevel;
-constexpr int kSoloStack = 448;   // items of a SOLO stack
+// Items of a SOLO stack.  (Without far boxes the kernels need few enough registers for eight
+// wavefronts per SIMD, which 5 KB of LDS each allow.)
+__host__ __device__ constexpr int solo_stack(bool far) { return far ? 448 : 400; }
 constexpr int kMaxGroupWaves = 16;
 constexpr int kFarQueue = 2 * kWave; // far boxes waiting for their pass
 
@@ -67,19 +69,22 @@ __host__ __device__ constexpr int coop_queue(int W)
     const int by_stack = (coop_stack(W) - kStackReserve) / 3;
     return kWave * W < by_stack ? kWave * W : by_stack;
 }
-__host__ __device__ constexpr size_t solo_lds_bytes() { return 12ull * kSoloStack + 4ull * kFarQueue; }
+__host__ __device__ constexpr size_t solo_lds_bytes(bool far)
+{
+    return 12ull * solo_stack(far) + (far ? 4ull * kFarQueue : 0);
+}
 __host__ __device__ constexpr size_t coop_lds_bytes(int W)
 {
     return 12ull * coop_stack(W) + 48ull * coop_queue(W) + 16ull * kMaxGroupWaves + 4ull * kWave;
 }
 
-__device__ inline TravLds solo_lds(char* base)
+__device__ inline TravLds solo_lds(char* base, bool far)
 {
     TravLds L{};
-    L.cap = kSoloStack;
+    L.cap = solo_stack(far);
     L.stkm = reinterpret_cast<uint64_t*>(base);
-    L.stkb = reinterpret_cast<int*>(base + 8 * kSoloStack);
-    L.fq = L.stkb + kSoloStack;
+    L.stkb = reinterpret_cast<int*>(base + 8 * L.cap);
+    L.fq = L.stkb + L.cap;
     return L;
 }
 

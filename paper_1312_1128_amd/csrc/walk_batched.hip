@@ -17,9 +17,9 @@ __global__ __launch_bounds__(kBlock, 6) void k_walk_batched(const BatchLens* __r
                                                         const double* __restrict__ xs, const double* __restrict__ ys,
                                                         const uint32_t* __restrict__ perm)
 {
-    __shared__ __align__(16) char lds[(kBlock / kWave) * solo_lds_bytes()];
+    __shared__ __align__(16) char lds[(kBlock / kWave) * solo_lds_bytes(true)];
     const int lane = threadIdx.x & (kWave - 1);
-    const TravLds L = solo_lds(lds + (threadIdx.x / kWave) * solo_lds_bytes());
+    const TravLds L = solo_lds(lds + (threadIdx.x / kWave) * solo_lds_bytes(true), true);
     const int64_t total = gprefix[nlens];
     for (;;) {
         int it = 0;

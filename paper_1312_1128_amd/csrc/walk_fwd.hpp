@@ -172,29 +172,29 @@ template <bool PSI, int KIND>
 constexpr int walk_waves(int most) { return PSI && KIND == kKindNfw ? 4 : most; }
 
 // One wavefront (and workgroup) per ray group.
-template <int P, bool AONLY, bool PSI, int KIND>
+template <int P, bool AONLY, int MODE, bool PSI, int KIND, bool FAR>
 __global__ __launch_bounds__(kWave, (walk_waves<PSI, KIND>(6))) void k_walk(TreeDev T, const double* __restrict__ rxs,
                                                const double* __restrict__ rys, const uint32_t* __restrict__ rperm,
                                                int64_t nrays, WalkOut out)
 {
-    __shared__ __align__(16) char lds[solo_lds_bytes()];
+    __shared__ __align__(16) char lds[solo_lds_bytes(FAR)];
     const int lane = threadIdx.x;
     int64_t grp;
     if (!group_task(blockIdx.x, (nrays + kWave - 1) / kWave, &grp)) return;
     const int64_t r = grp * kWave + lane;
     const bool valid = r < nrays;
     const double X = valid ? rxs[r] : 0.0, Y = valid ? rys[r] : 0.0;
-    const RayGroup g = ray_group(X, Y, valid, true);
-    FwdVisitor<P, AONLY, 0, PSI, KIND, true> v(T, g, X, Y, lane, valid);
-    traverse<false>(T, v, g, X, Y, lane, 0, 1, solo_lds(lds));
-    if (g.far) {
+    const RayGroup g = ray_group(X, Y, valid, FAR);
+    FwdVisitor<P, AONLY, MODE, PSI, KIND, FAR> v(T, g, X, Y, lane, valid);
+    traverse<false>(T, v, g, X, Y, lane, 0, 1, solo_lds(lds, FAR));
+    if (FAR && g.far) {
         double* words = reinterpret_cast<double*>(lds);
         v.put_words(words);
         wave_lds_sync();
         v.finish(words);
     }
     if constexpr (!AONLY) join_shear(v.A);
-    if (valid) write_out<AONLY, false, PSI>(v.A, v.cnt, rperm ? (int64_t)rperm[r] : r, out);
+    if (valid) write_out<AONLY, MODE == 1, PSI>(v.A, v.cnt, rperm ? (int64_t)rperm[r] : r, out);
 }
 
 // FP64 words per ray that the wavefronts of a group sum up at the end.
@@ -298,22 +298,23 @@ template <int P, bool AONLY, int MODE, bool PSI, int KIND>
 void launch_walk_kind(const WalkArgs& a)
 {
     const dim3 g((unsigned)group_grid((a.nrays + a.shape.rays - 1) / a.shape.rays));
-    if constexpr (MODE == 0) {
-        if (a.shape.waves == 1) {
-            hipLaunchKernelGGL((k_walk<P, AONLY, PSI, KIND>), g, dim3(kWave), 0, a.st, a.T, a.rxs, a.rys, a.rperm,
-                               a.nrays, a.out);
-            return;
+    const auto launch = [&](auto far) {
+        constexpr bool FAR = decltype(far)::value;
+        if constexpr (MODE == 0) {
+            if (a.shape.waves == 1 && a.shape.rays == kWave) {
+                hipLaunchKernelGGL((k_walk<P, AONLY, MODE, PSI, KIND, FAR>), g, dim3(kWave), 0, a.st, a.T, a.rxs, a.rys,
+                                   a.rperm, a.nrays, a.out);
+                return;
+            }
         }
-    }
-    const auto coop = [&](auto far) {
-        hipLaunchKernelGGL((k_walk_coop<P, AONLY, MODE, PSI, KIND, decltype(far)::value>), g, dim3(kWave * a.shape.waves),
+        hipLaunchKernelGGL((k_walk_coop<P, AONLY, MODE, PSI, KIND, FAR>), g, dim3(kWave * a.shape.waves),
                            (walk_coop_lds<AONLY, PSI, MODE == 1>(a.shape.waves)), a.st, a.T, a.rxs, a.rys, a.rperm,
                            a.nrays, a.out, a.shape.rays);
     };
     if constexpr (MODE != 2) {
-        if (a.far) return coop(std::true_type{});
+        if (a.far) return launch(std::true_type{});
     }
-    coop(std::false_type{});
+    launch(std::false_type{});
 }
 
 template <bool AONLY, int MODE, bool PSI>

@@ -154,3 +154,33 @@ def test_a_ray_at_infinity_leaves_its_group_alone(ora, nr, bad):
     got = np.stack([b[0][q].double().cpu().numpy() for q in ["a1", "a2", "kappa", "g1", "g2"]], axis=1)
     near = idx < k
     assert_matches_oracle_tree(got[idx[near]], ref[near])
+
+
+@pytest.mark.parametrize("n", [1, 5, 90, 160, 300])
+@pytest.mark.parametrize("nr", [70_000, 300_001, 530_001])
+def test_small_trees_under_many_rays(ora, n, nr):
+    """Trees of a few boxes up to the size from which far boxes are expanded (64), under
+    launches that expand them on larger trees, with several wavefronts per group and
+    one: the product walk, with counts, alpha only, plain FP32 sums and the potential."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    lens = lens_of(n, 641)
+    rx, ry = synth.uniform_points(nr, 642, -0.7, 0.7)
+    idx = np.union1d(synth.sample_rays(rx, ry, 1500, 643), np.arange(nr - 70, nr))
+    tree = build(lens, 0.5, 6, 5)
+    say(f"[gpu] {n} particles in {tree.info()['ncells']} boxes, {nr} rays")
+    T = ora.Tree(lens.x, lens.y, lens.m, lens.s, lens.q, 0.5, 6, 5)
+    ref, rc = T.shoot(rx[idx], ry[idx], counts=True)
+    got = shoot(tree, rx, ry)[idx]
+    assert_matches_oracle_tree(got, ref)
+    withc, cnt = shoot(tree, rx, ry, counts=True)
+    np.testing.assert_array_equal(cnt[idx], rc[:, [0, 1, 2, 4]])
+    np.testing.assert_array_equal(withc[idx], got)
+    np.testing.assert_array_equal(shoot(tree, rx, ry, alpha_only=True)[idx], got[:, :2])
+    plain = shoot(tree, rx, ry, fp32_alpha=True)[idx]
+    assert np.abs(plain[:, :2] - ref[:, :2]).max() <= 1e-4 * np.abs(ref[:, :2]).max()
+    o = g.shoot_potential(tree, dev(rx), dev(ry))
+    torch.cuda.synchronize()
+    ref_psi = T.shoot_psi(rx[idx], ry[idx])
+    assert np.abs(o["psi"].double().cpu().numpy()[idx] - ref_psi).max() <= 2e-6 * np.abs(ref_psi).max()

@@ -379,7 +379,7 @@ glm_status shoot_device(const TreeStorage& ts, const double* rx, const double* r
     }
     const WalkArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, WalkOut{a1, a2, k, g1, g2, counts}, walk_shape(nrays, ts.n), walk_far(nrays, ts.ncells), st};
     const bool aonly = (flags & GLM_ALPHA_ONLY) != 0;
-    // counts requested: the product walk with counters; else the product or the plain-FP32 walk
+    // the product walk with counters where counts are asked for, else the product or the plain-FP32 walk
     if (counts) launch_walk_counts(a, aonly);
     else if (flags & GLM_FP32_ALPHA) launch_walk_fp32(a, aonly);
     else if (aonly) launch_walk_alpha(a);

@@ -300,16 +300,13 @@ void launch_walk_kind(const WalkArgs& a)
     const dim3 g((unsigned)group_grid((a.nrays + a.shape.rays - 1) / a.shape.rays));
     const auto launch = [&](auto far) {
         constexpr bool FAR = decltype(far)::value;
-        if constexpr (MODE == 0) {
-            if (a.shape.waves == 1 && a.shape.rays == kWave) {
-                hipLaunchKernelGGL((k_walk<P, AONLY, MODE, PSI, KIND, FAR>), g, dim3(kWave), 0, a.st, a.T, a.rxs, a.rys,
-                                   a.rperm, a.nrays, a.out);
-                return;
-            }
-        }
-        hipLaunchKernelGGL((k_walk_coop<P, AONLY, MODE, PSI, KIND, FAR>), g, dim3(kWave * a.shape.waves),
-                           (walk_coop_lds<AONLY, PSI, MODE == 1>(a.shape.waves)), a.st, a.T, a.rxs, a.rys, a.rperm,
-                           a.nrays, a.out, a.shape.rays);
+        if (a.shape.waves == 1 && a.shape.rays == kWave)
+            hipLaunchKernelGGL((k_walk<P, AONLY, MODE, PSI, KIND, FAR>), g, dim3(kWave), 0, a.st, a.T, a.rxs, a.rys, a.rperm,
+                               a.nrays, a.out);
+        else
+            hipLaunchKernelGGL((k_walk_coop<P, AONLY, MODE, PSI, KIND, FAR>), g, dim3(kWave * a.shape.waves),
+                               (walk_coop_lds<AONLY, PSI, MODE == 1>(a.shape.waves)), a.st, a.T, a.rxs, a.rys, a.rperm,
+                               a.nrays, a.out, a.shape.rays);
     };
     if constexpr (MODE != 2) {
         if (a.far) return launch(std::true_type{});

@@ -102,8 +102,11 @@ StagedRays staged_rays_view(int64_t nrays, void* ws, const RayLayout& L);
 //    large one the groups of the dense core cost many times the others.
 //    262,144 rays (4,096 groups) with 1, 2, 4, 8 wavefronts each, in us: on 1e4
 //    particles 520, 464, 480, 666; on 6e4 863, 684, 610, 787; on 1e6 -, 2405,
-//    1682, 1617.
+//    1682, 1617.  Each has at least kWaveParticles particles of the lens to share
+//    (60 particles: 1e4 rays in their order 25.7 us with 16, 19.5 with one; 2e5 rays 31.7
+//    with two, 27.4 with one).
 constexpr int kMaxGroupRays = 64;
+constexpr int kWaveParticles = 64;
 struct WalkShape {
     int rays, waves;
 };
@@ -114,16 +117,7 @@ inline WalkShape walk_shape(int64_t nrays, int64_t n)
     WalkShape s{kMaxGroupRays, 1};
     while (s.rays > 4 && nrays < min_groups * s.rays) s.rays /= 2;
     const int64_t groups = (nrays + s.rays - 1) / s.rays;
-    while (s.waves < 16 && 2 * s.waves * groups <= fill) s.waves *= 2;
-    return s;
-}
-
-// The same for the adjoint walk: at most 8 wavefronts, whose LDS (a ray table
-// each) still fits twice on a CU.
-inline WalkShape adjoint_shape(int64_t nrays, int64_t n)
-{
-    WalkShape s = walk_shape(nrays, n);
-    if (s.waves > 8) s.waves = 8;
+    while (s.waves < 16 && 2 * s.waves * groups <= fill && s.waves * kWaveParticles < n) s.waves *= 2;
     return s;
 }
 
@@ -136,6 +130,20 @@ inline WalkShape adjoint_shape(int64_t nrays, int64_t n)
 constexpr int64_t kFarRays = 65536;
 constexpr int64_t kFarBoxes = 64;
 inline bool walk_far(int64_t nrays, int64_t ncells) { return nrays >= kFarRays && ncells >= kFarBoxes; }
+
+// The same for the adjoint walk: at most 8 wavefronts, whose LDS (a ray table
+// each) still fits twice on a CU, and fewer on a small lens, where all groups' wavefronts queue on
+// the same few particles' atomics, the more so the more rays there are (1, 2, 4, 8 wavefronts, in
+// us: 300 particles, 1e4 rays 273, -, 169, -; 1.3e5 rays 344, -, 593, -; 1,200 smoothed
+// particles, 1.3e5 rays 295, 397, 400, -).
+inline WalkShape adjoint_shape(int64_t nrays, int64_t n)
+{
+    WalkShape s = walk_shape(nrays, n);
+    const int64_t share = nrays >= kFarRays ? 8 * kWaveParticles : kWaveParticles;
+    if (s.waves > 8) s.waves = 8;
+    while (s.waves > 1 && s.waves * share > n) s.waves /= 2;
+    return s;
+}
 
 glm_status shoot_device(const TreeStorage& ts, const double* rx, const double* ry, int64_t nrays, float* a1,
                         float* a2, float* k, float* g1, float* g2, int32_t* counts, uint32_t flags, void* ws,

@@ -13,6 +13,7 @@
 #include <stddef.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -1105,6 +1106,10 @@ glm_status build_tree_device(TreeStorage& ts, const double* x, const double* y, 
             off += lt.cnt[l];
         }
         if (off != nc) return fail(GLM_EHIP, "build_tree: per-level box counts disagree with the box total");
+        // one box in 16 more than two levels below the depth of an even tree of as many boxes
+        int even = 0;
+        while ((1ll << (2 * even)) < nc) ++even;
+        ts.uneven = 16ll * (nc - lt.off[std::min(even + 3, kMaxLevel + 1)]) > nc;
     }
 
     const int gc = ceil_div(nc, kBlock);

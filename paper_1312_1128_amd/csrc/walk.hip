@@ -377,7 +377,7 @@ glm_status shoot_device(const TreeStorage& ts, const double* rx, const double* r
         glm_status rc = stage_rays(rx, ry, nrays, ws, L, &sr, st);
         if (rc != GLM_OK) return rc;
     }
-    const WalkArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, WalkOut{a1, a2, k, g1, g2, counts}, walk_shape(nrays, ts.n), walk_far(nrays, ts.ncells), st};
+    const WalkArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, WalkOut{a1, a2, k, g1, g2, counts}, walk_shape(nrays, ts.n, ts.uneven), walk_far(nrays, ts.ncells), st};
     const bool aonly = (flags & GLM_ALPHA_ONLY) != 0;
     // the product walk with counters where counts are asked for, else the product or the plain-FP32 walk
     if (counts) launch_walk_counts(a, aonly);
@@ -401,7 +401,7 @@ glm_status potential_device(const TreeStorage& ts, const double* rx, const doubl
     WalkOut out{a1, a2, nullptr, nullptr, nullptr, nullptr};
     out.psi = psi;
     out.td = td;
-    launch_walk_potential(WalkArgs{ts.dev, sr.xs, sr.ys, sr.perm, nrays, out, walk_shape(nrays, ts.n), walk_far(nrays, ts.ncells), st});
+    launch_walk_potential(WalkArgs{ts.dev, sr.xs, sr.ys, sr.perm, nrays, out, walk_shape(nrays, ts.n, ts.uneven), walk_far(nrays, ts.ncells), st});
     GLM_HIP(hipGetLastError());
     return GLM_OK;
 }

@@ -105,15 +105,23 @@ StagedRays staged_rays_view(int64_t nrays, void* ws, const RayLayout& L);
 //    1682, 1617.  Each has at least kWaveParticles particles of the lens to share
 //    (60 particles: 1e4 rays in their order 25.7 us with 16, 19.5 with one; 2e5 rays 31.7
 //    with two, 27.4 with one).
+//  - Over an uneven lens (TreeStorage::uneven: a core far denser than the rest) the few groups
+//    there are the whole launch's length: four times the `fill`, from kUnevenParticles particles.
+//    Equal mass per octave of radius, 3e4 particles, 2.8e5 rays: 2,230 us with one
+//    wavefront per group, 1,286 with two, 780 with four; adjoint 3,190, 1,456, 958; 1e5
+//    particles, 7e5 rays: adjoint 5,720, 2,618, 1,681.  (An NFW halo counts as even, and on
+//    even lenses the even fill is the better one: 1e5 uniform particles, 3e5 rays 424 us with four, 569 with eight.)
 constexpr int kMaxGroupRays = 64;
 constexpr int kWaveParticles = 64;
+constexpr int64_t kUnevenParticles = 2048;
 struct WalkShape {
     int rays, waves;
 };
-inline WalkShape walk_shape(int64_t nrays, int64_t n)
+inline WalkShape walk_shape(int64_t nrays, int64_t n, bool uneven)
 {
     const int64_t min_groups = n < 131072 ? 256 : (n < 524288 ? 512 : 1024);
-    const int64_t fill = n < 32768 ? 8192 : (n < 524288 ? 20480 : 40960);
+    int64_t fill = n < 32768 ? 8192 : (n < 524288 ? 20480 : 40960);
+    if (uneven && n >= kUnevenParticles) fill *= 4;
     WalkShape s{kMaxGroupRays, 1};
     while (s.rays > 4 && nrays < min_groups * s.rays) s.rays /= 2;
     const int64_t groups = (nrays + s.rays - 1) / s.rays;
@@ -136,10 +144,10 @@ inline bool walk_far(int64_t nrays, int64_t ncells) { return nrays >= kFarRays &
 // the same few particles' atomics, the more so the more rays there are (1, 2, 4, 8 wavefronts, in
 // us: 300 particles, 1e4 rays 273, -, 169, -; 1.3e5 rays 344, -, 593, -; 1,200 smoothed
 // particles, 1.3e5 rays 295, 397, 400, -).
-inline WalkShape adjoint_shape(int64_t nrays, int64_t n)
+inline WalkShape adjoint_shape(int64_t nrays, int64_t n, bool uneven)
 {
-    WalkShape s = walk_shape(nrays, n);
-    const int64_t share = nrays >= kFarRays ? 8 * kWaveParticles : kWaveParticles;
+    WalkShape s = walk_shape(nrays, n, uneven);
+    const int64_t share = nrays >= kFarRays && !uneven ? 8 * kWaveParticles : kWaveParticles;
     if (s.waves > 8) s.waves = 8;
     while (s.waves > 1 && s.waves * share > n) s.waves /= 2;
     return s;

@@ -184,3 +184,38 @@ def test_small_trees_under_many_rays(ora, n, nr):
     torch.cuda.synchronize()
     ref_psi = T.shoot_psi(rx[idx], ry[idx])
     assert np.abs(o["psi"].double().cpu().numpy()[idx] - ref_psi).max() <= 2e-6 * np.abs(ref_psi).max()
+
+
+@pytest.mark.parametrize("n", [2047, 2500])
+def test_uneven_lens(ora, n):
+    """Equal mass per octave of radius over four decades, below and above the size from which
+    such a lens's groups get more wavefronts: the walk against the oracle tree, the
+    adjoint against its sum over parts that take other launch shapes."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    gen = synth.rng(651)
+    rad, phi, nr = 10.0 ** gen.uniform(-4, -0.3, n), gen.uniform(0, 2 * np.pi, n), 280_001
+    x, y, m, s = rad * np.cos(phi), rad * np.sin(phi), gen.uniform(0.5, 1.0, n), 6 * rad / np.sqrt(n)
+    rx, ry = synth.uniform_points(nr, 652)
+    rx[::3], ry[::3] = 1e-2 * rx[::3], 1e-2 * ry[::3]
+    idx = np.union1d(synth.sample_rays(rx, ry, 2000, 653), np.arange(0, nr, 211))
+    say(f"[gpu] uneven lens of {n}")
+    tree = g.Tree().build(dev(x), dev(y), dev(m), dev(s), theta=0.4, q=3.0, leaf_size=8, order=6)
+    T = ora.Tree(x, y, m, s, 3.0, 0.4, 8, 6)
+    ref, rc = T.shoot(rx[idx], ry[idx], counts=True)
+    got, cnt = shoot(tree, rx, ry, counts=True)
+    np.testing.assert_array_equal(cnt[idx], rc[:, [0, 1, 2, 4]])
+    assert_matches_oracle_tree(got[idx], ref)
+    X, Y = dev(rx), dev(ry)
+    cot = torch.as_tensor(gen.normal(size=(5, nr)).astype(np.float32), device="cuda")
+    whole = g.shoot_adjoint(tree, X, Y, cot[0], cot[1], gk=cot[2], gg1=cot[3], gg2=cot[4])
+    parts = None
+    for a in range(0, nr, 30_000):
+        c = [v[a:a + 30_000].contiguous() for v in cot]
+        parts = g.shoot_adjoint(tree, X[a:a + 30_000].contiguous(), Y[a:a + 30_000].contiguous(), c[0], c[1],
+                                *(parts or ()), gk=c[2], gg1=c[3], gg2=c[4])
+    for name, w, p in zip("mxys", whole, parts):
+        w, p = w.cpu().numpy(), p.cpu().numpy()
+        assert np.abs(w).max() > 0
+        assert np.abs(w - p).max() <= 2e-6 * np.abs(p).max(), name

@@ -13,7 +13,6 @@
 #include <stddef.h>
 #include <string.h>
 
-#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -1106,10 +1105,12 @@ glm_status build_tree_device(TreeStorage& ts, const double* x, const double* y, 
             off += lt.cnt[l];
         }
         if (off != nc) return fail(GLM_EHIP, "build_tree: per-level box counts disagree with the box total");
-        // one box in 16 more than two levels below the depth of an even tree of as many boxes
-        int even = 0;
+        // four levels or more with a good many boxes (one in 64), all over two levels below the depth
+        // of an even tree: density rising over octaves, not a dense patch, whose boxes lie on one or two
+        int even = 0, deep = 0;
         while ((1ll << (2 * even)) < nc) ++even;
-        ts.uneven = 16ll * (nc - lt.off[std::min(even + 3, kMaxLevel + 1)]) > nc;
+        for (int l = even + 3; l <= kMaxLevel; ++l) deep += 64ll * lt.cnt[l] >= nc;
+        ts.uneven = deep >= 4;
     }
 
     const int gc = ceil_div(nc, kBlock);

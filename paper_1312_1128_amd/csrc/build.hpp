@@ -82,7 +82,7 @@ struct TreeStorage {
     int32_t* perm = nullptr;   // Morton position -> original index
     uint64_t* key = nullptr;   // sorted Morton keys
     bool deep = false;         // the last build had a box below level kTopLevel
-    bool uneven = false;       // many boxes lie far deeper than an even lens's would (see walk_shape)
+    bool uneven = false;       // boxes on many levels far below an even lens's (see walk_shape)
     double *ccx = nullptr, *ccy = nullptr;
     double* ms = nullptr;      // FP64 masses in Morton order
     TreeDev dev{};

@@ -109,8 +109,10 @@ StagedRays staged_rays_view(int64_t nrays, void* ws, const RayLayout& L);
 //    there are the whole launch's length: four times the `fill`, from kUnevenParticles particles.
 //    Equal mass per octave of radius, 3e4 particles, 2.8e5 rays: 2,230 us with one
 //    wavefront per group, 1,286 with two, 780 with four; adjoint 3,190, 1,456, 958; 1e5
-//    particles, 7e5 rays: adjoint 5,720, 2,618, 1,681.  (An NFW halo counts as even, and on
-//    even lenses the even fill is the better one: 1e5 uniform particles, 3e5 rays 424 us with four, 569 with eight.)
+//    particles, 7e5 rays: adjoint 5,720, 2,618, 1,681.  (NFW halos and patches of stars count as
+//    even, and over those the even fill is the better one: 1e5 uniform particles, 3e5 rays
+//    424 us with four, 569 with eight; 1.4e5 rays of a refinement over 3e5 particles, 3e4 of them
+//    stars in one patch, 564 us with eight, 784 with sixteen.)
 constexpr int kMaxGroupRays = 64;
 constexpr int kWaveParticles = 64;
 constexpr int64_t kUnevenParticles = 2048;

@@ -246,7 +246,8 @@ GLM_API glm_status glm_shoot_workspace_bytes(int64_t nrays, size_t* bytes);
  * (single-wavefront groups and launches of 65,536 rays or more), so there a ray's result
  * depends on its group by rounding.
  *   workspace: device buffer of at least glm_shoot_workspace_bytes(nrays)
- *   (the ray sort and the sorted rays).
+ *   (the ray sort, the sorted rays, and the sums of a walk split over box
+ *   ranges); a buffer for nrays rays also serves fewer.
  *   flags: GLM_ALPHA_ONLY, GLM_FP32_ALPHA, GLM_RAYS_ORDERED or GLM_RAYS_STAGED
  *   (not both; see glm_stage_rays), or-ed with the tree's.
  * nrays may be 0 (nothing is launched).

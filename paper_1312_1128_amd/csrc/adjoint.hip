@@ -149,7 +149,7 @@ glm_status launch_adjoint(const TreeStorage& ts, const StagedRays& sr, int64_t n
     const int64_t nbox = (int64_t)ts.ncells * NA;
     double* pg = abar + (size_t)kAdjCopies * nbox;
     hipLaunchKernelGGL(k_fill_zero, dim3(ceil_div((int64_t)words, kBlock)), dim3(kBlock), 0, st, abar, (int64_t)words);
-    const AdjointArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, ci, pg, abar, adjoint_shape(nrays, ts.n, ts.uneven), walk_far(nrays, ts.ncells), st};
+    const AdjointArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, ci, pg, abar, adjoint_shape(nrays, ts), walk_far(nrays, ts), st};
     if (ci.gk || ci.gg1 || ci.gg2) launch_adjoint_all(a);
     else launch_adjoint_alpha(a);
     hipLaunchKernelGGL(k_sum_copies, dim3(ceil_div(nbox, (int64_t)kBlock)), dim3(kBlock), 0, st, abar, nbox);

@@ -528,14 +528,16 @@ constexpr size_t adj_wave_lds() { return 4 * (adj_scratch<P, COOP, FAR>() + kFar
 template <int P, bool KG, int KIND, bool COOP, bool FAR>
 __global__ __launch_bounds__(COOP ? kWave * kMaxGroupWaves : kWave) void k_adjoint_walk(
     TreeDev T, const double* __restrict__ rxs, const double* __restrict__ rys, const uint32_t* __restrict__ rperm,
-    int64_t nrays, CotIn ci, double* __restrict__ pg, double* __restrict__ abar, int rays, bool far)
+    int64_t nrays, CotIn ci, double* __restrict__ pg, double* __restrict__ abar, int rays, int split, bool far)
 {
     extern __shared__ __align__(16) char lds[];
     const int lane = threadIdx.x & (kWave - 1);
     const int w = COOP ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) : 0;
     const int W = COOP ? (int)(blockDim.x / kWave) : 1;
     int64_t grp;
-    if (!group_task(blockIdx.x, (nrays + rays - 1) / rays, &grp)) return; // (whole workgroups)
+    int c0, c1;
+    box_range(split, T.ncells, &c0, &c1);
+    if (!group_task(blockIdx.x / split, (nrays + rays - 1) / rays, &grp)) return; // (whole workgroups)
     // this wavefront's copies of the box adjoints and of the particle sums (see kAdjCopies)
     const int wid = (int)blockIdx.x * W + w;
     const int64_t r = grp * rays + lane;
@@ -557,7 +559,7 @@ __global__ __launch_bounds__(COOP ? kWave * kMaxGroupWaves : kWave) void k_adjoi
     float* scratch = reinterpret_cast<float*>(own);
     AdjVisitor<P, KG, KIND, FAR, COOP> v(T, g, X, Y, lane, cg, abar + (size_t)(wid % kAdjCopies) * T.ncells * (2 * (P + 2)),
                                    pg + (size_t)(wid % kPgCopies) * 4 * T.n, scratch, scratch + adj_scratch<P, COOP, FAR>());
-    traverse<COOP>(T, v, g, X, Y, lane, w, W, COOP ? coop_lds(lds, W) : solo_lds(lds, true));
+    traverse<COOP, true>(T, v, g, X, Y, lane, w, W, COOP ? coop_lds(lds, W) : solo_lds(lds, true), c0, c1);
 }
 
 // Arguments of an adjoint walk launch.
@@ -576,13 +578,13 @@ struct AdjointArgs {
 template <int P, bool KG, int KIND>
 void launch_adjoint_kind(const AdjointArgs& a)
 {
-    const dim3 g((unsigned)group_grid((a.nrays + a.shape.rays - 1) / a.shape.rays));
+    const dim3 g((unsigned)(group_grid((a.nrays + a.shape.rays - 1) / a.shape.rays) * a.shape.split));
     const int W = a.shape.waves;
     const auto go = [&](auto coop, auto far) {
         constexpr bool COOP = decltype(coop)::value, FAR = decltype(far)::value;
         const size_t lds = COOP ? coop_lds_bytes(W) + W * adj_wave_lds<P, COOP, FAR>() : solo_lds_bytes(true) + adj_wave_lds<P, COOP, FAR>();
         hipLaunchKernelGGL((k_adjoint_walk<P, KG, KIND, COOP, FAR>), g, dim3(kWave * W), lds, a.st, a.T, a.rxs, a.rys,
-                           a.rperm, a.nrays, a.ci, a.pg, a.abar, a.shape.rays, a.far);
+                           a.rperm, a.nrays, a.ci, a.pg, a.abar, a.shape.rays, a.shape.split, a.far);
     };
     if (W == 1) go(std::false_type{}, std::true_type{});
     else if (a.far) go(std::true_type{}, std::true_type{});

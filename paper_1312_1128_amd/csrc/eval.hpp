@@ -549,4 +549,13 @@ __device__ inline bool group_task(int b, int64_t groups, int64_t* group)
     return *group < groups;
 }
 
+// The box range [c0, c1) of workgroup b % split of a group, of `split` even ones.
+__device__ inline int box_range(int split, int ncells, int* c0, int* c1)
+{
+    const int part = (int)(blockIdx.x % split);
+    *c0 = (int)((int64_t)ncells * part / split);
+    *c1 = (int)((int64_t)ncells * (part + 1) / split);
+    return part;
+}
+
 } // namespace glm

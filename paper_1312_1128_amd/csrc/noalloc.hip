@@ -1,5 +1,5 @@
 // glm_shoot for callers that cannot allocate device memory: the ray workspace
-// (ray sort keys and values, sorted ray copies)
+// (ray sort keys and values, sorted ray copies, sums of a split walk)
 // is a file-scope device array instead of a caller buffer.  Each GPU the
 // library runs on holds one copy of the array until the process ends; every
 // call on that GPU shares it, so calls that overlap on one GPU (on different

@@ -150,9 +150,11 @@ __device__ inline void box_dist2(const RayGroup& g, double cx, double cy, double
 
 // The traversal (see the file comment).  Every lane of the group's W
 // wavefronts calls it; X, Y is the lane's ray (the same in every wavefront).
-template <bool COOP, class V>
+// RANGE: only the boxes [c0, c1) of the preorder go to the visitor, their
+// ancestors are passed through (a group's work over several workgroups).
+template <bool COOP, bool RANGE, class V>
 __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, double X, double Y, int lane, int w, int W,
-                                const TravLds& L)
+                                const TravLds& L, int c0 = 0, int c1 = 0)
 {
     int top = 1;
     if (w == 0 && lane == 0) {
@@ -180,14 +182,17 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
             m = L.stkm[top + idx];
         }
         const CellHdr h = T.hdr[c];
+        const bool in = RANGE ? has && h.next > c0 && c < c1 : has;
+        const bool own = RANGE ? in && c >= c0 : has;
+        const uint64_t ownm = RANGE && !COOP ? __ballot(own) : 0;
         double dn2, df2;
         box_dist2(g, h.cx, h.cy, &dn2, &df2);
-        const bool all = has && dn2 > h.rcut2;
-        const bool mixed = has && !all && df2 > h.rcut2;
+        const bool all = in && dn2 > h.rcut2;
+        const bool mixed = in && !all && df2 > h.rcut2;
         const bool leaf = (h.info & kInfoLeaf) != 0;
         bool fa = false;
         if constexpr (V::farfield) {
-            fa = all && m == g.full && is_far(g, h, T.theta);
+            fa = own && all && m == g.full && is_far(g, h, T.theta);
             const uint64_t fb = __ballot(fa);
             if constexpr (!COOP) {
                 if (fa) L.fq[nf + rank_in(fb)] = c;
@@ -195,10 +200,10 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
             }
             if constexpr (V::stats) v.accepted(__popcll(fb));
         }
-        if constexpr (V::stats) v.visited(__popcll(__ballot(has && m == g.full)));
+        if constexpr (V::stats) v.visited(__popcll(__ballot(own && m == g.full)));
         // the boxes that only some rays accept, and (SOLO) all the work of the accepted ones
         uint64_t am = all ? m : 0ull;
-        uint64_t todo = COOP ? __ballot(mixed) : __ballot(mixed || (all && !fa));
+        uint64_t todo = COOP ? __ballot(mixed) : __ballot(mixed || (own && all && !fa));
         if constexpr (COOP) {
             while (todo) {
                 const int k = __ffsll((unsigned long long)todo) - 1;
@@ -226,7 +231,7 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
                 const double d2 = sqdist(X, Y, readlane_f64(h.cx, k), readlane_f64(h.cy, k), &w1, &w2);
                 const bool acc = act && d2 > readlane_f64(h.rcut2, k);
                 const uint64_t ak = __ballot(acc);
-                if (ak) v.box(now, ck, acc, w1, w2);
+                if (ak && (!RANGE || ((ownm >> k) & 1))) v.box(now, ck, acc, w1, w2);
                 if (lane == k) am = ak;
                 const bool more = kn != k;
                 k = kn;
@@ -237,7 +242,7 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
             }
         }
         if constexpr (V::stats) {
-            uint64_t part = __ballot(has && m != g.full);
+            uint64_t part = __ballot(own && m != g.full);
             while (part) {
                 const int k = __ffsll((unsigned long long)part) - 1;
                 part &= part - 1;
@@ -246,11 +251,11 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
         }
         const uint64_t om = m & ~am; // the rays that open the box
         bool lr = false;
-        if (has && (h.info & kInfoList)) {
+        if (own && (h.info & kInfoList)) {
             const double* q = T.lreach + 4 * (size_t)c;
             lr = (g.gx1 >= q[0]) & (g.gx0 <= q[1]) & (g.gy1 >= q[2]) & (g.gy0 <= q[3]);
         }
-        const bool opl = has && leaf && om != 0;
+        const bool opl = own && leaf && om != 0;
         CellExt e{};
         if (lr || opl) e = T.ext[c];
         if constexpr (!COOP) {
@@ -269,7 +274,7 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
             }
         }
         // children of the opened boxes
-        const bool push = has && !leaf && om != 0;
+        const bool push = in && !leaf && om != 0;
         int4 kc = make_int4(-1, -1, -1, -1);
         if (push) kc = *reinterpret_cast<const int4*>(T.kids + 4 * (size_t)c);
         const int kid[4] = {kc.x, kc.y, kc.z, kc.w};
@@ -282,7 +287,7 @@ __device__ inline void traverse(const TreeDev& T, V& v, const RayGroup& g, doubl
         }
         int at = top; // where this wavefront's children go
         if constexpr (COOP) {
-            const uint64_t qa[4] = {__ballot(am != 0 && !fa), __ballot(opl), __ballot(lr), __ballot(fa)};
+            const uint64_t qa[4] = {__ballot(own && am != 0 && !fa), __ballot(opl), __ballot(lr), __ballot(fa)};
             // counts of this wavefront, two to a word (a round's are below 2^16)
             const int pk[2] = {(int)(__popcll(qa[0]) | (__popcll(qa[1]) << 16)),
                                (int)(__popcll(qa[2]) | (__popcll(qa[3]) << 16))};

@@ -123,6 +123,14 @@ __global__ __launch_bounds__(kBlock) void k_ray_gather(const uint32_t* __restric
 
 } // namespace
 
+// Slots for the sums of a split walk, growing with nrays (a workspace for a launch also serves
+// every smaller one).
+static int64_t split_slots(int64_t nrays)
+{
+    const int64_t groups = (nrays + kWave - 1) / kWave;
+    return kWave * std::min(kMaxSplit * groups, kOpenGroups);
+}
+
 RayLayout ray_layout(int64_t nrays)
 {
     RayLayout L;
@@ -135,6 +143,7 @@ RayLayout ray_layout(int64_t nrays)
     L.ys = a.take(8ull * nrays);
     L.hist = a.take(4ull * radix_hist_words(nrays));
     L.part = a.take(sizeof(double) * 4 * (kRayBboxBlocks + 1));
+    L.parts = a.take(sizeof(Partial) * (size_t)split_slots(nrays));
     L.bytes = a.size;
     return L;
 }
@@ -364,6 +373,46 @@ glm_status shoot_batched_device(const BatchLens* host_table, int nlens, int orde
     return GLM_OK;
 }
 
+namespace {
+
+// Per ray, the sums of its box ranges in range order.
+__global__ __launch_bounds__(kBlock) void k_walk_merge(const Partial* __restrict__ parts, int split, int64_t nrays,
+                                                      const uint32_t* __restrict__ rperm, WalkOut out)
+{
+    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (r >= nrays) return;
+    Partial s = parts[r];
+    for (int k = 1; k < split; ++k) {
+        const Partial& q = parts[(int64_t)k * nrays + r];
+        s.a1 += q.a1;
+        s.a2 += q.a2;
+        s.k += q.k;
+        s.g1 += q.g1;
+        s.g2 += q.g2;
+        s.ps += q.ps;
+        for (int i = 0; i < kCounts; ++i) s.cnt[i] += q.cnt[i];
+    }
+    const int64_t o = rperm ? (int64_t)rperm[r] : r;
+    out.a1[o] = (float)s.a1;
+    out.a2[o] = (float)s.a2;
+    if (out.k) out.k[o] = (float)s.k;
+    if (out.g1) out.g1[o] = (float)s.g1;
+    if (out.g2) out.g2[o] = (float)s.g2;
+    if (out.psi) out.psi[o] = (float)s.ps;
+    if (out.td) out.td[o] = (float)(0.5 * (s.a1 * s.a1 + s.a2 * s.a2) - s.ps);
+    if (out.counts)
+        for (int i = 0; i < kCounts; ++i) out.counts[kCounts * o + i] = s.cnt[i];
+}
+
+void merge_parts(const WalkArgs& a)
+{
+    if (a.shape.split > 1)
+        hipLaunchKernelGGL(k_walk_merge, dim3(ceil_div(a.nrays, kBlock)), dim3(kBlock), 0, a.st, a.parts, a.shape.split,
+                           a.nrays, a.rperm, a.out);
+}
+
+} // namespace
+
 glm_status shoot_device(const TreeStorage& ts, const double* rx, const double* ry, int64_t nrays, float* a1,
                         float* a2, float* k, float* g1, float* g2, int32_t* counts, uint32_t flags, void* ws,
                         hipStream_t st)
@@ -377,13 +426,17 @@ glm_status shoot_device(const TreeStorage& ts, const double* rx, const double* r
         glm_status rc = stage_rays(rx, ry, nrays, ws, L, &sr, st);
         if (rc != GLM_OK) return rc;
     }
-    const WalkArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, WalkOut{a1, a2, k, g1, g2, counts}, walk_shape(nrays, ts.n, ts.uneven), walk_far(nrays, ts.ncells), st};
     const bool aonly = (flags & GLM_ALPHA_ONLY) != 0;
+    if (aonly) k = g1 = g2 = nullptr;
+    Partial* parts = reinterpret_cast<Partial*>(static_cast<char*>(ws) + L.parts);
+    const WalkArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, WalkOut{a1, a2, k, g1, g2, counts}, walk_shape(nrays, ts),
+                     walk_far(nrays, ts), parts, st};
     // the product walk with counters where counts are asked for, else the product or the plain-FP32 walk
     if (counts) launch_walk_counts(a, aonly);
     else if (flags & GLM_FP32_ALPHA) launch_walk_fp32(a, aonly);
     else if (aonly) launch_walk_alpha(a);
     else launch_walk_full(a);
+    merge_parts(a);
     GLM_HIP(hipGetLastError());
     return GLM_OK;
 }
@@ -401,7 +454,10 @@ glm_status potential_device(const TreeStorage& ts, const double* rx, const doubl
     WalkOut out{a1, a2, nullptr, nullptr, nullptr, nullptr};
     out.psi = psi;
     out.td = td;
-    launch_walk_potential(WalkArgs{ts.dev, sr.xs, sr.ys, sr.perm, nrays, out, walk_shape(nrays, ts.n, ts.uneven), walk_far(nrays, ts.ncells), st});
+    Partial* parts = reinterpret_cast<Partial*>(static_cast<char*>(ws) + L.parts);
+    const WalkArgs a{ts.dev, sr.xs, sr.ys, sr.perm, nrays, out, walk_shape(nrays, ts), walk_far(nrays, ts), parts, st};
+    launch_walk_potential(a);
+    merge_parts(a);
     GLM_HIP(hipGetLastError());
     return GLM_OK;
 }

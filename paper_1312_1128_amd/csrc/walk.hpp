@@ -1,6 +1,8 @@
 // Ray staging and the forward / adjoint walks.
 #pragma once
 
+#include <algorithm>
+
 #include "build.hpp"
 
 namespace glm {
@@ -69,9 +71,15 @@ size_t shoot_indexed_workspace_bytes(int64_t count);
 // wavefront's give the lane use of each phase.
 constexpr int kCounts = 8;
 
+// Sums of one ray over one range of boxes.
+struct Partial {
+    double a1, a2, k, g1, g2, ps;
+    int32_t cnt[kCounts];
+};
+
 // Byte offsets of the ray workspace pieces.
 struct RayLayout {
-    size_t k0, k1, v0, v1, xs, ys, hist, part, bytes;
+    size_t k0, k1, v0, v1, xs, ys, hist, part, parts, bytes;
 };
 RayLayout ray_layout(int64_t nrays);
 
@@ -117,14 +125,44 @@ constexpr int kMaxGroupRays = 64;
 constexpr int kWaveParticles = 64;
 constexpr int64_t kUnevenParticles = 2048;
 struct WalkShape {
-    int rays, waves;
+    int rays, waves, split;
 };
-inline WalkShape walk_shape(int64_t nrays, int64_t n, bool uneven)
+
+// Whether a walk opens most of the tree: a box of side d is opened within about d / theta, and
+// below this the leaves' opened squares cover most of the lens from everywhere.  Then
+// smaller groups need no less each, far boxes are rare, and the work lies evenly along the preorder:
+// a launch of few groups splits it into `split` box ranges with workgroups of
+// their own (up to kOpenGroups, of kOpenWaves wavefronts), whose sums
+// meet in range order.  theta = 0, 60 rays on 3e5 particles: 9.4 ms in groups of 4
+// rays, 0.28 in 64 ranges of one group; 5,000 rays 24.9, 2.1.  2e4 rays on 3e4 particles,
+// 1,024 workgroups of 8 wavefronts 716 us, 4,096 of 8 616, of 4 593.  Where the rule ends (n theta^2
+// per leaf size, unsplit and split): 3e4 particles, 2e4 rays at 6.8 355 us, 334; at 15 238,
+// 340; 1,000 rays at 15 174, 89; at 27 123, 89.
+constexpr int64_t kOpenParticles = 2048;
+constexpr int64_t kOpenGroups = 4096;
+constexpr int kOpenWaves = 4;
+constexpr int64_t kMaxSplit = 64;
+inline int64_t full_groups(int64_t nrays) { return (nrays + kMaxGroupRays - 1) / kMaxGroupRays; }
+inline bool walk_opens(int64_t nrays, const TreeStorage& ts)
 {
+    const double reach = full_groups(nrays) < 64 ? 20.0 : 8.0;
+    return ts.n >= kOpenParticles && ts.n * ts.params.theta * ts.params.theta < reach * ts.params.leaf_size;
+}
+// Box ranges of at least 64 boxes that make up to `groups` workgroups.
+inline int open_split(int64_t nrays, const TreeStorage& ts, int64_t groups)
+{
+    return (int)std::max<int64_t>(1, std::min<int64_t>(groups / full_groups(nrays), ts.ncells / 64));
+}
+
+inline WalkShape walk_shape(int64_t nrays, const TreeStorage& ts)
+{
+    const int64_t n = ts.n;
+    if (walk_opens(nrays, ts) && full_groups(nrays) < kOpenGroups)
+        return WalkShape{kMaxGroupRays, kOpenWaves, (int)std::min<int64_t>(kMaxSplit, open_split(nrays, ts, kOpenGroups))};
     const int64_t min_groups = n < 131072 ? 256 : (n < 524288 ? 512 : 1024);
     int64_t fill = n < 32768 ? 8192 : (n < 524288 ? 20480 : 40960);
-    if (uneven && n >= kUnevenParticles) fill *= 4;
-    WalkShape s{kMaxGroupRays, 1};
+    if (ts.uneven && n >= kUnevenParticles) fill *= 4;
+    WalkShape s{kMaxGroupRays, 1, 1};
     while (s.rays > 4 && nrays < min_groups * s.rays) s.rays /= 2;
     const int64_t groups = (nrays + s.rays - 1) / s.rays;
     while (s.waves < 16 && 2 * s.waves * groups <= fill && s.waves * kWaveParticles < n) s.waves *= 2;
@@ -139,19 +177,30 @@ inline WalkShape walk_shape(int64_t nrays, int64_t n, bool uneven)
 // particles 728, 853).
 constexpr int64_t kFarRays = 65536;
 constexpr int64_t kFarBoxes = 64;
-inline bool walk_far(int64_t nrays, int64_t ncells) { return nrays >= kFarRays && ncells >= kFarBoxes; }
+inline bool walk_far(int64_t nrays, const TreeStorage& ts)
+{
+    return nrays >= kFarRays && ts.ncells >= kFarBoxes && !walk_opens(nrays, ts);
+}
 
 // The same for the adjoint walk: at most 8 wavefronts, whose LDS (a ray table
 // each) still fits twice on a CU, and fewer on a small lens, where all groups' wavefronts queue on
 // the same few particles' atomics, the more so the more rays there are (1, 2, 4, 8 wavefronts, in
 // us: 300 particles, 1e4 rays 273, -, 169, -; 1.3e5 rays 344, -, 593, -; 1,200 smoothed
-// particles, 1.3e5 rays 295, 397, 400, -).
-inline WalkShape adjoint_shape(int64_t nrays, int64_t n, bool uneven)
+// particles, 1.3e5 rays 295, 397, 400, -).  A walk that opens most of the tree has full ray
+// masks, for which one wavefront per range, lanes as rays, is the better particle pass from
+// kOpenSolo groups (theta = 0: 2e5 rays on 2,500 particles 2,012 us with four, 1,058 with one; 3,000
+// rays 115, 206).
+constexpr int64_t kOpenSolo = 128;
+constexpr int64_t kOpenSoloGroups = 32768;
+inline WalkShape adjoint_shape(int64_t nrays, const TreeStorage& ts)
 {
-    WalkShape s = walk_shape(nrays, n, uneven);
-    const int64_t share = nrays >= kFarRays && !uneven ? 8 * kWaveParticles : kWaveParticles;
+    if (walk_opens(nrays, ts) && full_groups(nrays) >= kOpenSolo)
+        return WalkShape{kMaxGroupRays, 1, open_split(nrays, ts, kOpenSoloGroups)};
+    WalkShape s = walk_shape(nrays, ts);
+    if (s.split > 1) return s;
+    const int64_t share = nrays >= kFarRays && !ts.uneven ? 8 * kWaveParticles : kWaveParticles;
     if (s.waves > 8) s.waves = 8;
-    while (s.waves > 1 && s.waves * share > n) s.waves /= 2;
+    while (s.waves > 1 && s.waves * share > ts.n) s.waves /= 2;
     return s;
 }
 

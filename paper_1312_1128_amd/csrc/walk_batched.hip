@@ -39,7 +39,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_walk_batched(const BatchLens* __r
         const double X = valid ? xs[gi] : 0.0, Y = valid ? ys[gi] : 0.0;
         const RayGroup g = ray_group(X, Y, valid, MODE != 2);
         FwdVisitor<P, AONLY, MODE, false, KIND, MODE != 2> v(B.tree, g, X, Y, lane, valid);
-        traverse<false>(B.tree, v, g, X, Y, lane, 0, 1, L);
+        traverse<false, false>(B.tree, v, g, X, Y, lane, 0, 1, L);
         if (g.far) {
             double* words = reinterpret_cast<double*>(L.stkm);
             v.put_words(words);

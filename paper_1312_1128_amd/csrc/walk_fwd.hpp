@@ -186,7 +186,7 @@ __global__ __launch_bounds__(kWave, (walk_waves<PSI, KIND>(6))) void k_walk(Tree
     const double X = valid ? rxs[r] : 0.0, Y = valid ? rys[r] : 0.0;
     const RayGroup g = ray_group(X, Y, valid, FAR);
     FwdVisitor<P, AONLY, MODE, PSI, KIND, FAR> v(T, g, X, Y, lane, valid);
-    traverse<false>(T, v, g, X, Y, lane, 0, 1, solo_lds(lds, FAR));
+    traverse<false, false>(T, v, g, X, Y, lane, 0, 1, solo_lds(lds, FAR));
     if (FAR && g.far) {
         double* words = reinterpret_cast<double*>(lds);
         v.put_words(words);
@@ -215,7 +215,7 @@ template <int P, bool AONLY, int MODE, bool PSI, int KIND, bool FAR>
 __global__ __launch_bounds__(kWave* kMaxGroupWaves, (walk_waves<PSI, KIND>(5))) void k_walk_coop(TreeDev T, const double* __restrict__ rxs,
                                                                     const double* __restrict__ rys,
                                                                     const uint32_t* __restrict__ rperm, int64_t nrays,
-                                                                    WalkOut out, int rays)
+                                                                    WalkOut out, int rays, int split, Partial* __restrict__ parts)
 {
     extern __shared__ __align__(16) char lds[];
     constexpr bool STATS = MODE == 1;
@@ -223,13 +223,15 @@ __global__ __launch_bounds__(kWave* kMaxGroupWaves, (walk_waves<PSI, KIND>(5))) 
     const int lane = threadIdx.x & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), W = blockDim.x / kWave;
     int64_t grp;
-    if (!group_task(blockIdx.x, (nrays + rays - 1) / rays, &grp)) return; // (whole workgroups)
+    int c0, c1;
+    const int part = box_range(split, T.ncells, &c0, &c1);
+    if (!group_task(blockIdx.x / split, (nrays + rays - 1) / rays, &grp)) return; // (whole workgroups)
     const int64_t r = grp * rays + lane;
     const bool valid = lane < rays && r < nrays;
     const double X = valid ? rxs[r] : 0.0, Y = valid ? rys[r] : 0.0;
     const RayGroup g = ray_group(X, Y, valid, FAR);
     FwdVisitor<P, AONLY, MODE, PSI, KIND, FAR> v(T, g, X, Y, lane, valid);
-    traverse<true>(T, v, g, X, Y, lane, w, W, coop_lds(lds, W));
+    traverse<true, true>(T, v, g, X, Y, lane, w, W, coop_lds(lds, W), c0, c1);
     Acc& A = v.A;
     if constexpr (!AONLY) join_shear(A);
     __syncthreads(); // the traversal's LDS is free
@@ -279,7 +281,20 @@ __global__ __launch_bounds__(kWave* kMaxGroupWaves, (walk_waves<PSI, KIND>(5))) 
         if constexpr (STATS)
             for (int i = 0; i < kCounts; ++i) v.cnt[i] += csum[(u * kCounts + i) * kWave + lane];
     }
-    write_out<AONLY, STATS, PSI>(A, v.cnt, rperm ? (int64_t)rperm[r] : r, out);
+    if (split == 1) {
+        write_out<AONLY, STATS, PSI>(A, v.cnt, rperm ? (int64_t)rperm[r] : r, out);
+        return;
+    }
+    Partial q{};
+    q.a1 = alpha1(A);
+    q.a2 = alpha2(A);
+    q.k = A.k;
+    q.g1 = A.g1;
+    q.g2 = A.g2;
+    q.ps = A.ps;
+    if constexpr (STATS)
+        for (int i = 0; i < kCounts; ++i) q.cnt[i] = v.cnt[i];
+    parts[(int64_t)part * nrays + r] = q;
 }
 
 // Arguments of a walk launch.
@@ -291,22 +306,23 @@ struct WalkArgs {
     WalkOut out;
     WalkShape shape;
     bool far;  // expand far boxes over the groups
+    Partial* parts; // of shape.split box ranges per ray
     hipStream_t st;
 };
 
 template <int P, bool AONLY, int MODE, bool PSI, int KIND>
 void launch_walk_kind(const WalkArgs& a)
 {
-    const dim3 g((unsigned)group_grid((a.nrays + a.shape.rays - 1) / a.shape.rays));
+    const dim3 g((unsigned)(group_grid((a.nrays + a.shape.rays - 1) / a.shape.rays) * a.shape.split));
     const auto launch = [&](auto far) {
         constexpr bool FAR = decltype(far)::value;
-        if (a.shape.waves == 1 && a.shape.rays == kWave)
+        if (a.shape.waves == 1 && a.shape.rays == kWave && a.shape.split == 1)
             hipLaunchKernelGGL((k_walk<P, AONLY, MODE, PSI, KIND, FAR>), g, dim3(kWave), 0, a.st, a.T, a.rxs, a.rys, a.rperm,
                                a.nrays, a.out);
         else
             hipLaunchKernelGGL((k_walk_coop<P, AONLY, MODE, PSI, KIND, FAR>), g, dim3(kWave * a.shape.waves),
                                (walk_coop_lds<AONLY, PSI, MODE == 1>(a.shape.waves)), a.st, a.T, a.rxs, a.rys, a.rperm,
-                               a.nrays, a.out, a.shape.rays);
+                               a.nrays, a.out, a.shape.rays, a.shape.split, a.parts);
     };
     if constexpr (MODE != 2) {
         if (a.far) return launch(std::true_type{});

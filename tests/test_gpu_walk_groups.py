@@ -219,3 +219,50 @@ def test_uneven_lens(ora, n):
         w, p = w.cpu().numpy(), p.cpu().numpy()
         assert np.abs(w).max() > 0
         assert np.abs(w - p).max() <= 2e-6 * np.abs(p).max(), name
+
+
+@pytest.mark.parametrize("n,nr", [(2048, 1), (2048, 4097), (9000, 64), (9000, 65), (9000, 3000), (9000, 70_000),
+                                  (9000, 140_000), (9000, 262_145)])
+@pytest.mark.parametrize("theta", [0.0, 0.05, 0.1])
+@pytest.mark.parametrize("nfw", [False, True])
+def test_walks_that_open_most_of_the_tree(ora, n, nr, theta, nfw):
+    """Opening angles so small that a launch of few groups splits the tree into box ranges (and
+    just above), from 64 ranges to one: values and decision counts against the oracle tree, the
+    walk's variants against each other, and the adjoint against its sum over parts."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    if nfw:
+        lens, c = synth.nfw_halo_field(n, 661)
+    else:
+        lens, c = lens_of(n, 661), 3.0
+    leaf, order = 10, 3
+    rx, ry = synth.uniform_points(nr, 662, -0.6, 0.6)
+    idx = np.unique(np.r_[0, nr - 1, np.linspace(0, nr - 1, 400).astype(int)])
+    say(f"[gpu] open walk n={n} rays={nr} theta={theta} nfw={nfw}")
+    tree = g.Tree().build(dev(lens.x), dev(lens.y), dev(lens.m), dev(lens.s), theta=theta, q=c, leaf_size=leaf, order=order,
+                          nfw=nfw)
+    T = ora.Tree(lens.x, lens.y, lens.m, lens.s, c, theta, leaf, order, nfw=nfw)
+    ref, rc = T.shoot(rx[idx], ry[idx], counts=True)
+    got = shoot(tree, rx, ry)
+    assert_matches_oracle_tree(got[idx], ref)
+    withc, cnt = shoot(tree, rx, ry, counts=True)
+    np.testing.assert_array_equal(cnt[idx], rc[:, [0, 1, 2, 4]])
+    np.testing.assert_array_equal(withc, got)
+    np.testing.assert_array_equal(shoot(tree, rx, ry, alpha_only=True), got[:, :2])
+    o = g.shoot_potential(tree, dev(rx), dev(ry))
+    torch.cuda.synchronize()
+    psi, ref_psi = o["psi"].double().cpu().numpy()[idx], T.shoot_psi(rx[idx], ry[idx])
+    assert np.abs(psi - ref_psi).max() <= 2e-6 * np.abs(ref_psi).max()
+    X, Y = dev(rx), dev(ry)
+    cot = torch.as_tensor(synth.rng(663).normal(size=(5, nr)).astype(np.float32), device="cuda")
+    whole = g.shoot_adjoint(tree, X, Y, cot[0], cot[1], gk=cot[2], gg1=cot[3], gg2=cot[4])
+    parts, step = None, max(1, nr // 3 + 1)
+    for a in range(0, nr, step):
+        k = [v[a:a + step].contiguous() for v in cot]
+        parts = g.shoot_adjoint(tree, X[a:a + step].contiguous(), Y[a:a + step].contiguous(), k[0], k[1], *(parts or ()),
+                                gk=k[2], gg1=k[3], gg2=k[4])
+    for name, w, p in zip("mxys", whole, parts):
+        w, p = w.cpu().numpy(), p.cpu().numpy()
+        assert np.abs(w).max() > 0
+        assert np.abs(w - p).max() <= 2e-6 * np.abs(p).max(), name

@@ -266,3 +266,40 @@ def test_walks_that_open_most_of_the_tree(ora, n, nr, theta, nfw):
         w, p = w.cpu().numpy(), p.cpu().numpy()
         assert np.abs(w).max() > 0
         assert np.abs(w - p).max() <= 2e-6 * np.abs(p).max(), name
+
+
+@pytest.mark.parametrize("nr", [70_000, 530_001])
+@pytest.mark.parametrize("order", range(13))
+def test_far_adjoint_and_potential_at_every_order(ora, order, nr):
+    """Rays in a small patch, in launches that expand far boxes (several wavefronts per
+    group and one), at each order: the potential against the oracle tree, and
+    the adjoint with alpha and with all cotangents against the sum over parts that expand none
+    (FP32 words summed in FP64 on both sides: 2e-6 of the largest, as against the oracle)."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    lens = lens_of(1500, 651)
+    gen = synth.rng(652)
+    rx, ry = 0.2 + 0.02 * gen.random(nr), 0.1 + 0.02 * gen.random(nr)
+    rx[:nr // 3] += 0.9
+    tree = build(lens, 0.5, 4, order)
+    say(f"[gpu] far adjoint and potential at order {order}, {nr} rays")
+    drx, dry = dev(rx), dev(ry)
+    idx = np.arange(0, nr, 61)
+    T = ora.Tree(lens.x, lens.y, lens.m, lens.s, lens.q, 0.5, 4, order)
+    ref = T.shoot_psi(rx[idx], ry[idx])
+    psi = g.shoot_potential(tree, drx, dry)["psi"].double().cpu().numpy()[idx]
+    assert np.abs(psi - ref).max() <= 2e-6 * np.abs(ref).max()
+    cot = torch.as_tensor(gen.normal(size=(5, nr)).astype(np.float32), device="cuda")
+    for lensing in (False, True):
+        def grad(parts):
+            out = [torch.zeros(lens.x.size, dtype=torch.float64, device="cuda") for _ in range(4)]
+            for a in range(0, nr, parts):
+                c = [v[a:a + parts].contiguous() for v in cot]
+                kw = dict(gk=c[2], gg1=c[3], gg2=c[4]) if lensing else {}
+                g.shoot_adjoint(tree, drx[a:a + parts].contiguous(), dry[a:a + parts].contiguous(), c[0], c[1], *out, **kw)
+            return [o.cpu().numpy() for o in out]
+
+        for name, whole, parts in zip("mxys", grad(nr), grad(50_000)):
+            assert np.abs(whole).max() > 0
+            assert np.abs(whole - parts).max() <= 2e-6 * np.abs(parts).max(), (name, lensing)

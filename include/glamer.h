@@ -241,10 +241,10 @@ GLM_API glm_status glm_shoot_workspace_bytes(int64_t nrays, size_t* bytes);
  * is tested 64 entries at a time, and not at all when the bounding box of its
  * particles' supports misses the group.  The walk evaluates its terms in FP32
  * and sums them in FP64; ray-particle and ray-box offsets and every
- * accept/inside decision are taken in FP64.  Boxes that every ray of a group
- * accepts from far enough are summed into one local expansion about the group
- * (single-wavefront groups and launches of 65,536 rays or more), so there a ray's result
- * depends on its group by rounding.
+ * accept/inside decision are taken in FP64.  In launches of 65,536 rays or more, over
+ * trees of 64 boxes or more (unless theta is so small that nearly every box is opened), boxes that
+ * every ray of a group accepts from far enough are summed into one local expansion
+ * about the group, so there a ray's result depends on its group by rounding.
  *   workspace: device buffer of at least glm_shoot_workspace_bytes(nrays)
  *   (the ray sort, the sorted rays, and the sums of a walk split over box
  *   ranges); a buffer for nrays rays also serves fewer.
@@ -383,8 +383,9 @@ GLM_API glm_status glm_shoot_batched_workspace_bytes(const int64_t* nrays, int n
  * of every lens are sorted along a Hilbert curve, cut into 64-ray groups,
  * and the wavefronts of one launch take (lens, group) items from a device
  * counter, lenses with the most expected work (rays x log2 particles) first.
- * Results equal glm_shoot per lens.  `lenses` is a HOST array of nlens
- * entries.  Copies the small lens table host->device (not graph-capturable).
+ * Every ray's decisions are glm_shoot's, its values equal glm_shoot's to FP32
+ * rounding (far boxes go through the groups' local expansions here at any number of
+ * rays).  `lenses` is a HOST array of nlens entries.  Copies the small lens table host->device (not graph-capturable).
  */
 GLM_API glm_status glm_shoot_batched(const glm_lens_rays* lenses, int nlens, uint32_t flags,
                                      void* workspace, size_t workspace_bytes, void* stream);

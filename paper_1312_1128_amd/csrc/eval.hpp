@@ -15,7 +15,7 @@ namespace glm {
 // point-mass terms of big-list particles that a ray lies inside (added once
 // with each sign, see leaf_particle) thus cancel there without leaving FP32
 // rounding of size m / r behind.  kappa is summed in FP64 too, so that a
-// ray's result does not depend on how its terms were grouped into partial sums.
+// ray's kappa does not depend on how its terms were grouped into partial sums.
 // The debug mode without FP64 alpha sums the alpha terms in plain FP32 (p1,
 // p2) and keeps only the balanced point terms in a1, a2.
 struct Acc {

@@ -7,9 +7,16 @@
 //   alpha1 - i alpha2 = F(w0 + delta) = sum_j L_j z^j,
 //   L_j = v e^j sum_k C(k + j, j) u_k,  v = 1 / w0, e = -a v, u_k = (Q_k / r_cm^k) t^k, t = r_cm v,
 // the exact re-expansion of the box's own multipole series (order P), cut at
-// order kFarOrder where (a / (d - r_cm))^j has fallen below FP32 rounding: with
-// a / (d - r_cm) <= kFarRatio = 0.3 and order 15 the first term left out is
-// 4e-9 of the field and 7e-8 of its derivative at the group's edge.  Every
+// order kFarOrder.  With a / (d - r_cm) < kFarRatio = 0.3 and order 15 the first
+// term left out is at most 0.3^16 = 4e-9 of the field and 16 0.3^15 = 2.3e-7 of
+// its derivative, and the rest of the derivative's series sums to 3.4e-7 of it: below FP32
+// rounding for alpha, a few roundings for gamma, in the worst direction at the edge of a
+// group at the limit.  One box evaluated per ray in FP32 has more
+// than that: a clump under a 400^2 grid, rays 18 spacings off (groups at the
+// limit), error of gamma over gamma, far boxes and without, rms 1.07e-7 and 1.23e-7, largest
+// 3.4e-7 and 3.4e-7; 24 to 40 spacings off 9.4e-8, 1.24e-7; of alpha 3.6e-8, 6.5e-8.  The 1e6-particle
+// halo (theta = 0.2, order 12, 400^2 rays against the FP64 direct sum): alpha 2.7e-8, 2.9e-8,
+// gamma 6.3e-8, 6.5e-8; ratios of 0.28, 0.27 and 0.25 give the same to 1%.  Every
 // ray's decisions are unchanged; only the evaluation of accepted boxes is.
 //
 // Per ray a box costs about 95 instructions of a wavefront; here the lanes are
@@ -79,8 +86,8 @@ __host__ __device__ constexpr float far_binomial(int k, int j)
 
 // Offset of the group's centre from box c's centre of mass, per lane: v = 1/w0
 // (0 on lanes without a box) and |w0|^2.  v in FP64: its error is the same for every ray
-// of the group, and with FP32's the 1e6-particle halo's alpha had 5% more error than the
-// box-by-box evaluation (rms 4.9e-8 against 4.7e-8, now 4.5e-8); a few instructions of 600.
+// of the group, and with FP32's the 1e6-particle halo's alpha had 5% more error than with
+// every box evaluated per ray; a few instructions of 600.
 struct FarOffset {
     double v1, v2;
     float r2;

@@ -148,9 +148,9 @@ RayLayout ray_layout(int64_t nrays)
     return L;
 }
 
-// Bits per axis of the ray sort key.  The key only forms the 64-ray groups
-// (per-ray results do not depend on them): about four cells per ray suffice,
-// 8 to 16 bits per axis.
+// Bits per axis of the ray sort key.  The key only forms the ray groups (a ray's
+// decisions do not depend on them, and where far boxes are expanded its values do by rounding):
+// about four cells per ray suffice, 8 to 16 bits per axis.
 static int ray_key_bits(int64_t nrays)
 {
     int bits = 8;

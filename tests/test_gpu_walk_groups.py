@@ -303,3 +303,37 @@ def test_far_adjoint_and_potential_at_every_order(ora, order, nr):
         for name, whole, parts in zip("mxys", grad(nr), grad(50_000)):
             assert np.abs(whole).max() > 0
             assert np.abs(whole - parts).max() <= 2e-6 * np.abs(parts).max(), (name, lensing)
+
+
+@pytest.mark.parametrize("n,nr", [(9000, 10_001), (9000, 25_001), (33_000, 10_001), (33_000, 60_001)])
+@pytest.mark.parametrize("theta", [0.05, 0.1])
+def test_open_adjoint_of_an_uneven_lens(n, nr, theta):
+    """Over a lens with equal mass per octave of radius the adjoint is split into box ranges up to
+    larger opening angles, by one or several wavefronts per range: against its sum over
+    parts of 97 rays (two groups, in 64 ranges, several wavefronts each) and of 3,000."""
+    import paper_1312_1128_amd as g
+    import torch
+
+    gen = synth.rng(671)
+    rad, phi = 10.0 ** gen.uniform(-4, -0.3, n), gen.uniform(0, 2 * np.pi, n)
+    x, y, m, s = rad * np.cos(phi), rad * np.sin(phi), gen.uniform(0.5, 1.0, n), 6 * rad / np.sqrt(n)
+    rx, ry = synth.uniform_points(nr, 672)
+    rx[::3], ry[::3] = 1e-2 * rx[::3], 1e-2 * ry[::3]
+    say(f"[gpu] open adjoint of an uneven lens n={n} rays={nr} theta={theta}")
+    tree = g.Tree().build(dev(x), dev(y), dev(m), dev(s), theta=theta, q=3.0, leaf_size=16, order=5)
+    X, Y = dev(rx), dev(ry)
+    cot = torch.as_tensor(gen.normal(size=(5, nr)).astype(np.float32), device="cuda")
+
+    def grad(lo, hi, step):
+        out = None
+        for a in range(lo, hi, step):
+            b = min(a + step, hi)
+            c = [v[a:b].contiguous() for v in cot]
+            out = g.shoot_adjoint(tree, X[a:b].contiguous(), Y[a:b].contiguous(), c[0], c[1], *(out or ()), gk=c[2], gg1=c[3],
+                                  gg2=c[4])
+        return [o.cpu().numpy() for o in out]
+
+    for step, hi in ((97, 1500), (3000, nr)):
+        for name, w, p in zip("mxys", grad(0, hi, hi), grad(0, hi, step)):
+            assert np.abs(w).max() > 0
+            assert np.abs(w - p).max() <= 2e-6 * np.abs(p).max(), (name, step)

@@ -135,13 +135,16 @@ struct WalkShape {
 // their own (up to kOpenGroups, of kOpenWaves wavefronts), whose sums
 // meet in range order.  theta = 0, 60 rays on 3e5 particles: 9.4 ms in groups of 4
 // rays, 0.28 in 64 ranges of one group; 5,000 rays 24.9, 2.1.  2e4 rays on 3e4 particles,
-// 1,024 workgroups of 8 wavefronts 716 us, 4,096 of 8 616, of 4 593.  The rule goes by
-// n theta^2 per leaf size (`reach`).  The fewer the groups, the further it reaches (not split and
-// split, in us: 2e5 particles, 1.5e4 rays at 11: 1,700, 620; at 17 1.6 to 2.3 times; 6e4 rays at 11
-// +-5%, at 17 5e4 particles 0.9 to 1.3 times, beyond less).  The adjoint gains less on
-// a small lens (1.2e4 particles, 1.5e4 rays at 11: 0.7 to 1.2 times), and more on an uneven one,
-// whose few long groups the ranges even out (1.5e4 rays at 17: 5e4 particles 1,332, 470; 2e5
-// 5,500, 1,405; 6e4 rays on 2e5 at 28: 1.3 times).
+// 1,024 workgroups of 8 wavefronts 716 us, 4,096 of 8 616, of 4 593.  The rule goes by r =
+// n theta^2 / max(16, leaf size): smaller leaves split no earlier (leaves of 2, 6e4 particles, 1.5e4
+// rays at r = 3.4: 3,215 us not split; adjoint of 5,000 particles at 2: 709), large ones a little later,
+// half as late with many groups (leaves of 64, 1.5e4 rays, adjoint of 6e4 points at r = 15 370 us not
+// split, 832; walk of a core 612, 390).  The fewer the groups, the further it reaches (not
+// split and split, leaves of 16: 2e5 particles, 1.5e4 rays at r = 11 1,700, 620; at 17 1.6 to 2.3
+// times; 6e4 rays at 11 +-5%, at 17 5e4 particles 0.9 to 1.3 times, beyond less).  The adjoint
+// gains less on a small lens (1.2e4 particles, 1.5e4 rays at 11: 0.7 to 1.2 times), and more on an uneven
+// one, whose few long groups the ranges even out (1.5e4 rays at 17: 5e4 particles 1,332, 470;
+// 2e5 5,500, 1,405; 6e4 rays on 2e5 at 28: 1.3 times).
 constexpr int64_t kOpenParticles = 2048;
 constexpr int64_t kOpenGroups = 4096;
 constexpr int kOpenWaves = 4;
@@ -153,7 +156,8 @@ inline bool walk_opens(int64_t nrays, const TreeStorage& ts, bool adjoint = fals
     double reach = groups < 512 ? 20.0 : 8.0;
     if (adjoint && n < 32768 && groups >= 128) reach = 8.0;
     if (adjoint && ts.uneven && n >= 8192 && groups < 1024) reach = 40.0;
-    return n >= kOpenParticles && n * ts.params.theta * ts.params.theta < reach * ts.params.leaf_size;
+    const double leaf = groups < (adjoint ? 128 : 512) ? ts.params.leaf_size : 0.5 * ts.params.leaf_size;
+    return n >= kOpenParticles && n * ts.params.theta * ts.params.theta < reach * std::max(16.0, leaf);
 }
 // Box ranges of at least 64 boxes that make up to `groups` workgroups.
 inline int open_split(int64_t nrays, const TreeStorage& ts, int64_t groups)
@@ -195,14 +199,15 @@ inline bool walk_far(int64_t nrays, const TreeStorage& ts)
 // us: 300 particles, 1e4 rays 273, -, 169, -; 1.3e5 rays 344, -, 593, -; 1,200 smoothed
 // particles, 1.3e5 rays 295, 397, 400, -).  A walk that opens most of the tree has full ray
 // masks, for which one wavefront per range, lanes as rays, is the better particle pass from 128
-// groups, or from 320 on a small lens (theta = 0: 2e5 rays on 2,500 particles 2,012 us with four,
-// 1,058 with one; 3,000 rays 115, 206; 1.5e4 rays at n theta^2 = 6 per leaf size on 3,000
+// groups, or from 320 on a small lens of leaves that fill the lanes (theta = 0: 2e5 rays on 2,500
+// particles 2,012 us with four, 1,058 with one; 3,000 rays 115, 206; 1.5e4 rays at r = 6 on 3,000
 // particles 120 to 208, 246 to 340, on 1.2e4 223 to 326, 322 to 455, on 5e4 points or halo equal, on
-// an uneven lens 632, 511, on 2e5 particles 2,206, 1,588; 3e4 rays, theta = 0.04 on 1.2e4 568, 419).
+// an uneven lens 632, 511, on 2e5 particles 2,206, 1,588; 3e4 rays, theta = 0.04 on 1.2e4 568,
+// 419; leaves of 2, 1.5e4 rays on 1.2e4 particles 585, 341).
 constexpr int64_t kOpenSoloGroups = 32768;
 inline WalkShape adjoint_shape(int64_t nrays, const TreeStorage& ts)
 {
-    if (walk_opens(nrays, ts, true) && full_groups(nrays) >= (ts.n < 32768 ? 320 : 128))
+    if (walk_opens(nrays, ts, true) && full_groups(nrays) >= (ts.n < 32768 && ts.params.leaf_size >= 8 ? 320 : 128))
         return WalkShape{kMaxGroupRays, 1, open_split(nrays, ts, kOpenSoloGroups)};
     WalkShape s = walk_shape(nrays, ts, true);
     if (s.split > 1) return s;
